@@ -5,7 +5,6 @@
 
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -18,19 +17,11 @@ using namespace surrdev;
 
 namespace {
 
-constexpr int NL = 4;
-// padded layer shapes [N x K] and the real ones
-constexpr int LN[NL] = {NHID, NHID, NHID, NOUTP};
-constexpr int LK[NL] = {KIN, NHID, NHID, NHID};
-constexpr int RN[NL] = {NHID, NHID, NHID, NOUT};
-constexpr int RK[NL] = {NIN, NHID, NHID, NHID};
-
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct SLayout {
-  size_t p[NL], m1[NL], m2[NL], g[NL], wb[NL], wt[NL];
-  size_t x0, x0t, hf[3], hb[3], ht[3], y, t, dy, dyt, dhb[3], dht[3];
-  size_t X, Y, RW, perm, qx, qy, lo, hi, lw, rw, loss, total;
+  size_t p[NL], m1[NL], m2[NL], wf[NL], wt[NL], at[NL], dt[NL];
+  size_t X, Y, RW, perm, qx, qy, lo, hi, lw, loss, total;
   int Bp, max_data;
 };
 
@@ -40,33 +31,20 @@ SLayout slayout(int max_batch, int max_data) {
   S.max_data = max_data;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = a256(off + bytes); return o; };
+  const size_t B = S.Bp;
   for (int l = 0; l < NL; ++l) {
     const size_t cnt = (size_t)LN[l] * LK[l] + LN[l];
     S.p[l] = take(cnt * 4);
     S.m1[l] = take(cnt * 4);
     S.m2[l] = take(cnt * 4);
-    S.g[l] = take(cnt * 4);
-    S.wb[l] = take((size_t)LN[l] * LK[l] * 2);
+    S.wf[l] = take((size_t)LN[l] * LK[l] * 2);
     S.wt[l] = take((size_t)LN[l] * LK[l] * 2);
+    S.at[l] = take(B * LK[l] * 2);
+    S.dt[l] = take(B * LN[l] * 2);
   }
-  const size_t B = S.Bp;
-  S.x0 = take(B * KIN * 2);
-  S.x0t = take(B * KIN * 2);
-  for (int i = 0; i < 3; ++i) {
-    S.hf[i] = take(B * NHID * 4);
-    S.hb[i] = take(B * NHID * 2);
-    S.ht[i] = take(B * NHID * 2);
-    S.dhb[i] = take(B * NHID * 2);
-    S.dht[i] = take(B * NHID * 2);
-  }
-  S.y = take(B * NOUTP * 4);
-  S.t = take(B * NOUTP * 4);
-  S.dy = take(B * NOUTP * 2);
-  S.dyt = take(B * NOUTP * 2);
   S.X = take((size_t)max_data * NIN * 4);
   S.Y = take((size_t)max_data * NOUT * 4);
   S.RW = take((size_t)max_data * 4);
-  S.rw = take(B * 4);
   S.perm = take((size_t)max_data * 4);
   S.qx = take(B * NIN * 4);
   S.qy = take(B * NOUT * 4);
@@ -78,43 +56,20 @@ SLayout slayout(int max_batch, int max_data) {
   return S;
 }
 
-// ---- scratch of the prediction that allocates nothing ---------------------
-// surr_predict_noalloc keeps its activations in this file-scope device array
-// instead of the handle's workspace; every GPU the library runs on holds its
-// own copy until the process ends.  In host code `scratch` names a host-side
-// stand-in, not a device address: host code uses the address that
-// scratch_ptr() looked up for the device.
-constexpr int SCRATCH_ROWS = 1024;  // most query rows per call
-constexpr size_t SC_X0 = 0;                                             // BF16 [R x KIN]
-constexpr size_t SC_X0T = SC_X0 + (size_t)SCRATCH_ROWS * KIN * 2;        // BF16 [KIN x R]
-constexpr size_t SC_HA = SC_X0T + (size_t)KIN * SCRATCH_ROWS * 2;        // BF16 [R x NHID]
-constexpr size_t SC_HB = SC_HA + (size_t)SCRATCH_ROWS * NHID * 2;        // BF16 [R x NHID]
-constexpr size_t SC_HF = SC_HB + (size_t)SCRATCH_ROWS * NHID * 2;        // FP32 [R x NHID] (unread)
-constexpr size_t SC_HT = SC_HF + (size_t)SCRATCH_ROWS * NHID * 4;        // BF16 [NHID x R] (unread)
-constexpr size_t SC_Y = SC_HT + (size_t)NHID * SCRATCH_ROWS * 2;         // FP32 [R x NOUTP]
-constexpr size_t SCRATCH_BYTES = SC_Y + (size_t)SCRATCH_ROWS * NOUTP * 4;  // 3.2 MB
+constexpr int NOALLOC_ROWS = 1024;  // most query rows of one surr_predict_noalloc
 
-static __device__ __align__(256) char scratch[SCRATCH_BYTES];
-
-constexpr int MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-char* g_scratch[MAX_DEVICES] = {};
-
-// Device address of `scratch` on device dev, which must be the current
-// device; looked up once per device and kept.
-lbm_status scratch_ptr(int dev, char** out) {
-  if (dev < 0 || dev >= MAX_DEVICES) return fail(LBM_EDEVICE, "device %d out of range", dev);
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch[dev]) {
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !p)
-      return fail(LBM_EDEVICE, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
-    g_scratch[dev] = (char*)p;
-  }
-  *out = g_scratch[dev];
-  return LBM_OK;
-}
+// Pinned host memory of a handle (0.9 MB).  Queries, answers, gradients, the
+// loss and the packed parameters pass through it: the kernels read and write
+// it themselves, so a call is its launches and one wait.  Copies to and from
+// pageable memory cost 10-20 us each, and the copy of the answers' columns out
+// of their padded rows went row by row (1.8 ms for 256 rows).
+constexpr int HOST_ROWS = 1024;  // rows per launch that reads its samples here
+struct HostBuffer {
+  double loss;
+  float x[HOST_ROWS * NIN];
+  float y[HOST_ROWS * NOUT];
+  float packed[NPARAMS];
+};
 
 }  // namespace
 
@@ -124,6 +79,9 @@ struct surr_net {
   hipStream_t stream;
   int n_data;
   long long adam_t;
+  float wsum;    // sum of the loss weights, added in order in FP32
+  bool loss_dirty;     // the loss accumulator may hold a failed call's part
+  HostBuffer* host;    // pinned
   template <typename T> T* at(size_t off) const { return (T*)(ws + off); }
 };
 
@@ -135,90 +93,97 @@ namespace {
     if (e_ != hipSuccess) return fail(LBM_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
-// forward pass for `rows` samples gathered from (X, Y) by idx (or in order)
-lbm_status forward(surr_net* s, const float* X, const float* Y, const float* RW,
-                   const int32_t* idx, int rows) {
-  const SLayout& S = s->S;
-  const int B = S.Bp;
-  HC(gather(X, Y, RW, idx, rows, B, s->at<float>(S.lo), s->at<float>(S.hi), s->at<__bf16>(S.x0),
-            s->at<__bf16>(S.x0t), Y ? s->at<float>(S.t) : nullptr, s->at<float>(S.rw), s->stream));
-  const __bf16* in = s->at<__bf16>(S.x0);
-  int ldin = KIN;
-  for (int l = 0; l < 3; ++l) {
-    GemmArgs g{};
-    g.A = in; g.lda = ldin; g.Bt = s->at<__bf16>(S.wb[l]); g.ldb = LK[l];
-    g.M = B; g.N = LN[l]; g.K = LK[l];
-    g.bias = s->at<float>(S.p[l]) + (size_t)LN[l] * LK[l];
-    g.outf = s->at<float>(S.hf[l]); g.outb = s->at<__bf16>(S.hb[l]); g.outt = s->at<__bf16>(S.ht[l]);
-    g.ldo = NHID; g.ldt = B;
-    HC(gemm(EPI_HIDDEN, g, s->stream));
-    in = s->at<__bf16>(S.hb[l]);
-    ldin = NHID;
-  }
-  GemmArgs g{};
-  g.A = in; g.lda = NHID; g.Bt = s->at<__bf16>(S.wb[3]); g.ldb = NHID;
-  g.M = B; g.N = NOUTP; g.K = NHID;
-  g.bias = s->at<float>(S.p[3]) + (size_t)NOUTP * NHID;
-  g.outf = s->at<float>(S.y); g.ldo = NOUTP;
-  HC(gemm(EPI_OUTPUT, g, s->stream));
-  return LBM_OK;
-}
-
-// loss gradient and the parameter gradients of every layer (into S.g)
-lbm_status backward(surr_net* s, int rows) {
-  const SLayout& S = s->S;
-  const int B = S.Bp;
-  HC(loss(s->at<float>(S.y), s->at<float>(S.t), s->at<float>(S.lw), s->at<float>(S.rw), rows, B,
-          s->at<__bf16>(S.dy), s->at<__bf16>(S.dyt), s->at<double>(S.loss), s->stream));
-  // layer l has input activations in[l] (BF16 transposed) and output gradient dout
-  const __bf16* dout_t = s->at<__bf16>(S.dyt);   // [N_l x B]
-  const __bf16* dout_b = s->at<__bf16>(S.dy);    // [B x N_l]
-  int ld_dout = NOUTP;
-  for (int l = NL - 1; l >= 0; --l) {
-    const __bf16* in_t = l == 0 ? s->at<__bf16>(S.x0t) : s->at<__bf16>(S.ht[l - 1]);
-    float* gw = s->at<float>(S.g[l]);
-    GemmArgs w{};
-    w.A = dout_t; w.lda = B; w.Bt = in_t; w.ldb = B;
-    w.M = LN[l]; w.N = LK[l]; w.K = B;
-    w.outf = gw; w.ldo = LK[l];
-    HC(gemm(EPI_WGRAD, w, s->stream));
-    HC(colsum(dout_t, B, LN[l], gw + (size_t)LN[l] * LK[l], s->stream));
-    if (l == 0) break;
-    GemmArgs d{};
-    d.A = dout_b; d.lda = ld_dout; d.Bt = s->at<__bf16>(S.wt[l]); d.ldb = LN[l];
-    d.M = B; d.N = LK[l]; d.K = LN[l];
-    d.act = s->at<float>(S.hf[l - 1]);
-    d.outb = s->at<__bf16>(S.dhb[l - 1]); d.outt = s->at<__bf16>(S.dht[l - 1]);
-    d.ldo = NHID; d.ldt = B;
-    HC(gemm(EPI_BACKWARD, d, s->stream));
-    dout_b = s->at<__bf16>(S.dhb[l - 1]);
-    dout_t = s->at<__bf16>(S.dht[l - 1]);
-    ld_dout = NHID;
-  }
-  return LBM_OK;
-}
-
-lbm_status adam_all(surr_net* s, float lr) {
-  const SLayout& S = s->S;
-  s->adam_t += 1;
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = (float)(1.0 - std::pow(0.9, (double)s->adam_t));
-  const float c2 = (float)(1.0 - std::pow(0.999, (double)s->adam_t));
+NetArgs net_args(const surr_net* s) {
+  NetArgs n{};
   for (int l = 0; l < NL; ++l) {
-    const int cnt = LN[l] * LK[l] + LN[l];
-    HC(adam(s->at<float>(S.p[l]), s->at<float>(S.m1[l]), s->at<float>(S.m2[l]),
-            s->at<float>(S.g[l]), cnt, LN[l] * LK[l], LN[l], LK[l], lr, b1, b2, eps, c1, c2,
-            s->at<__bf16>(S.wb[l]), s->at<__bf16>(S.wt[l]), s->stream));
+    n.wf[l] = s->at<__bf16>(s->S.wf[l]);
+    n.wt[l] = s->at<__bf16>(s->S.wt[l]);
+    n.bias[l] = s->at<float>(s->S.p[l]) + (size_t)LN[l] * LK[l];
   }
+  n.lo = s->at<float>(s->S.lo);
+  n.hi = s->at<float>(s->S.hi);
+  return n;
+}
+
+// Forward and backward pass of `rows` samples gathered from (X, Y, RW) by idx
+// (or in order); the loss is added to S.loss.
+lbm_status sample_pass(surr_net* s, const float* X, const float* Y, const float* RW,
+                       const int32_t* idx, int rows) {
+  const SLayout& S = s->S;
+  TrainArgs t{};
+  t.Y = Y;
+  t.RW = RW;
+  t.lw = s->at<float>(S.lw);
+  t.scale = 1.0f / ((float)rows * s->wsum);
+  for (int l = 0; l < NL; ++l) {
+    t.at[l] = s->at<__bf16>(S.at[l]);
+    t.dt[l] = s->at<__bf16>(S.dt[l]);
+  }
+  t.ks = S.Bp / 16;
+  t.loss = s->at<double>(S.loss);
+  HC(forward_backward(net_args(s), RowArgs{X, idx, rows}, t, s->stream));
   return LBM_OK;
 }
 
-// packed (real) <-> padded layout
-void pack_offsets(int l, size_t* w_off, size_t* b_off) {
-  size_t o = 0;
-  for (int k = 0; k < l; ++k) o += (size_t)RN[k] * RK[k] + RN[k];
-  *w_off = o;
-  *b_off = o + (size_t)RN[l] * RK[l];
+// The loss accumulator is zero between calls: the last update of a call hands
+// the sum over and clears it.
+lbm_status begin_loss(surr_net* s) {
+  if (s->loss_dirty) HC(hipMemsetAsync(s->ws + s->S.loss, 0, 8, s->stream));
+  s->loss_dirty = true;
+  return LBM_OK;
+}
+
+// Waits for a call's last update, after which s->host holds its loss.
+lbm_status end_loss(surr_net* s) {
+  HC(hipStreamSynchronize(s->stream));
+  s->loss_dirty = false;
+  return LBM_OK;
+}
+
+// Gradients of the last sample_pass: packed, or applied by Adam.
+UpdateArgs update_args(surr_net* s, int rows) {
+  const SLayout& S = s->S;
+  UpdateArgs u{};
+  for (int l = 0; l < NL; ++l) {
+    u.at[l] = s->at<__bf16>(S.at[l]);
+    u.dt[l] = s->at<__bf16>(S.dt[l]);
+    u.p[l] = s->at<float>(S.p[l]);
+    u.m1[l] = s->at<float>(S.m1[l]);
+    u.m2[l] = s->at<float>(S.m2[l]);
+    u.wf[l] = s->at<__bf16>(S.wf[l]);
+    u.wt[l] = s->at<__bf16>(S.wt[l]);
+  }
+  u.ks = S.Bp / 16;
+  u.steps = (rows + 31) / 32 * 2;
+  u.loss = s->at<double>(S.loss);
+  return u;
+}
+
+lbm_status adam_step(surr_net* s, int rows, float lr, bool last) {
+  UpdateArgs u = update_args(s, rows);
+  if (last) u.loss_out = &s->host->loss;
+  s->adam_t += 1;
+  u.lr = lr;
+  u.b1 = 0.9f;
+  u.b2 = 0.999f;
+  u.eps = 1e-8f;
+  u.c1 = (float)(1.0 - std::pow(0.9, (double)s->adam_t));
+  u.c2 = (float)(1.0 - std::pow(0.999, (double)s->adam_t));
+  HC(update(u, s->stream));
+  return LBM_OK;
+}
+
+PackArgs pack_args(surr_net* s) {
+  PackArgs a{};
+  a.packed = s->host->packed;
+  for (int l = 0; l < NL; ++l) {
+    a.p[l] = s->at<float>(s->S.p[l]);
+    a.m1[l] = s->at<float>(s->S.m1[l]);
+    a.m2[l] = s->at<float>(s->S.m2[l]);
+    a.wf[l] = s->at<__bf16>(s->S.wf[l]);
+    a.wt[l] = s->at<__bf16>(s->S.wt[l]);
+  }
+  return a;
 }
 
 }  // namespace
@@ -251,40 +216,30 @@ lbm_status surr_init(const double* lo, const double* hi, int32_t max_batch, int3
   s->stream = (hipStream_t)stream;
   s->n_data = 0;
   s->adam_t = 0;
+  s->wsum = (float)NOUT;
+  s->loss_dirty = false;
   float lof[NIN], hif[NIN], lw[NOUT];
   for (int j = 0; j < NIN; ++j) { lof[j] = (float)lo[j]; hif[j] = (float)hi[j]; }
   for (int j = 0; j < NOUT; ++j) lw[j] = 1.0f;
-  hipError_t e = hipMemsetAsync(s->ws, 0, s->S.total, s->stream);
+  hipError_t e = hipHostMalloc((void**)&s->host, sizeof(HostBuffer), hipHostMallocMapped | hipHostMallocPortable);
+  if (e != hipSuccess) { delete s; return fail(LBM_ENOMEM, "pinned buffer: %s", hipGetErrorString(e)); }
+  e = hipMemsetAsync(s->ws, 0, s->S.total, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.lo, lof, sizeof lof, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.hi, hif, sizeof hif, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.lw, lw, sizeof lw, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-  if (e != hipSuccess) { delete s; return fail(LBM_EDEVICE, "surrogate init: %s", hipGetErrorString(e)); }
-  // the scratch of surr_predict_noalloc on this (the current) device
-  int dev = 0;
-  char* sc = nullptr;
-  if (hipGetDevice(&dev) != hipSuccess) { delete s; return fail(LBM_EDEVICE, "no current device"); }
-  if ((st = scratch_ptr(dev, &sc)) != LBM_OK) { delete s; return st; }
+  if (e != hipSuccess) {
+    surr_destroy(s);
+    return fail(LBM_EDEVICE, "surrogate init: %s", hipGetErrorString(e));
+  }
   *out = s;
   return LBM_OK;
 }
 
 lbm_status surr_set_params(surr_net* s, const float* packed) {
   if (!s || !packed) return fail(LBM_EINVAL, "NULL argument");
-  for (int l = 0; l < NL; ++l) {
-    std::vector<float> pad((size_t)LN[l] * LK[l] + LN[l], 0.0f);
-    size_t wo, bo;
-    pack_offsets(l, &wo, &bo);
-    for (int r = 0; r < RN[l]; ++r) {
-      for (int c = 0; c < RK[l]; ++c) pad[(size_t)r * LK[l] + c] = packed[wo + (size_t)r * RK[l] + c];
-      pad[(size_t)LN[l] * LK[l] + r] = packed[bo + r];
-    }
-    HC(hipMemcpyAsync(s->ws + s->S.p[l], pad.data(), pad.size() * 4, hipMemcpyHostToDevice, s->stream));
-    HC(hipMemsetAsync(s->ws + s->S.m1[l], 0, pad.size() * 4, s->stream));
-    HC(hipMemsetAsync(s->ws + s->S.m2[l], 0, pad.size() * 4, s->stream));
-    HC(weight_copies(s->at<float>(s->S.p[l]), LN[l], LK[l], s->at<__bf16>(s->S.wb[l]),
-                     s->at<__bf16>(s->S.wt[l]), s->stream));
-  }
+  memcpy(s->host->packed, packed, sizeof s->host->packed);
+  HC(unpack_params(pack_args(s), s->stream));
   HC(hipStreamSynchronize(s->stream));
   s->adam_t = 0;
   return LBM_OK;
@@ -292,17 +247,9 @@ lbm_status surr_set_params(surr_net* s, const float* packed) {
 
 lbm_status surr_get_params(surr_net* s, float* packed) {
   if (!s || !packed) return fail(LBM_EINVAL, "NULL argument");
-  for (int l = 0; l < NL; ++l) {
-    std::vector<float> pad((size_t)LN[l] * LK[l] + LN[l]);
-    HC(hipMemcpyAsync(pad.data(), s->ws + s->S.p[l], pad.size() * 4, hipMemcpyDeviceToHost, s->stream));
-    HC(hipStreamSynchronize(s->stream));
-    size_t wo, bo;
-    pack_offsets(l, &wo, &bo);
-    for (int r = 0; r < RN[l]; ++r) {
-      for (int c = 0; c < RK[l]; ++c) packed[wo + (size_t)r * RK[l] + c] = pad[(size_t)r * LK[l] + c];
-      packed[bo + r] = pad[(size_t)LN[l] * LK[l] + r];
-    }
-  }
+  HC(pack_params(pack_args(s), s->stream));
+  HC(hipStreamSynchronize(s->stream));
+  memcpy(packed, s->host->packed, sizeof s->host->packed);
   return LBM_OK;
 }
 
@@ -312,6 +259,8 @@ lbm_status surr_set_loss_weights(surr_net* s, const float* w) {
     if (!(w[j] >= 0.0f) || !std::isfinite(w[j])) return fail(LBM_EINVAL, "bad loss weight %d", j);
   HC(hipMemcpyAsync(s->ws + s->S.lw, w, NOUT * 4, hipMemcpyHostToDevice, s->stream));
   HC(hipStreamSynchronize(s->stream));
+  s->wsum = 0.0f;
+  for (int j = 0; j < NOUT; ++j) s->wsum += w[j];
   return LBM_OK;
 }
 
@@ -340,110 +289,79 @@ lbm_status surr_train_epoch(surr_net* s, const int32_t* perm, int32_t batch, flo
   for (int i = 0; i < s->n_data; ++i)
     if (perm[i] < 0 || perm[i] >= s->n_data) return fail(LBM_EINVAL, "perm[%d] out of range", i);
   HC(hipMemcpyAsync(s->ws + s->S.perm, perm, (size_t)s->n_data * 4, hipMemcpyHostToDevice, s->stream));
-  HC(hipMemsetAsync(s->ws + s->S.loss, 0, 8, s->stream));
+  lbm_status st = begin_loss(s);
+  if (st != LBM_OK) return st;
   const float* X = s->at<float>(s->S.X);
   const float* Y = s->at<float>(s->S.Y);
   int nb = 0;
   for (int off = 0; off < s->n_data; off += batch, ++nb) {
     const int rows = std::min(batch, s->n_data - off);
-    lbm_status st;
-    if ((st = forward(s, X, Y, s->at<float>(s->S.RW), s->at<int32_t>(s->S.perm) + off, rows)) != LBM_OK)
+    if ((st = sample_pass(s, X, Y, s->at<float>(s->S.RW), s->at<int32_t>(s->S.perm) + off, rows)) != LBM_OK)
       return st;
-    if ((st = backward(s, rows)) != LBM_OK) return st;
-    if ((st = adam_all(s, lr)) != LBM_OK) return st;
+    if ((st = adam_step(s, rows, lr, off + rows >= s->n_data)) != LBM_OK) return st;
   }
-  double acc = 0.0;
-  HC(hipMemcpyAsync(&acc, s->ws + s->S.loss, 8, hipMemcpyDeviceToHost, s->stream));
-  HC(hipStreamSynchronize(s->stream));
-  if (mean_loss) *mean_loss = acc / nb;
+  if ((st = end_loss(s)) != LBM_OK) return st;
+  if (mean_loss) *mean_loss = s->host->loss / nb;
   return LBM_OK;
 }
 
 lbm_status surr_gradients(surr_net* s, const float* x, const float* y, int32_t n, float* grad,
                           double* loss_out) {
   if (!s || !x || !y || !grad || n < 1 || n > s->S.Bp) return fail(LBM_EINVAL, "bad arguments");
-  HC(hipMemcpyAsync(s->ws + s->S.qx, x, (size_t)n * NIN * 4, hipMemcpyHostToDevice, s->stream));
-  HC(hipMemcpyAsync(s->ws + s->S.qy, y, (size_t)n * NOUT * 4, hipMemcpyHostToDevice, s->stream));
-  HC(hipMemsetAsync(s->ws + s->S.loss, 0, 8, s->stream));
-  lbm_status st;
-  if ((st = forward(s, s->at<float>(s->S.qx), s->at<float>(s->S.qy), nullptr, nullptr, n)) != LBM_OK)
-    return st;
-  if ((st = backward(s, n)) != LBM_OK) return st;
-  for (int l = 0; l < NL; ++l) {
-    std::vector<float> pad((size_t)LN[l] * LK[l] + LN[l]);
-    HC(hipMemcpyAsync(pad.data(), s->ws + s->S.g[l], pad.size() * 4, hipMemcpyDeviceToHost, s->stream));
-    HC(hipStreamSynchronize(s->stream));
-    size_t wo, bo;
-    pack_offsets(l, &wo, &bo);
-    for (int r = 0; r < RN[l]; ++r) {
-      for (int c = 0; c < RK[l]; ++c) grad[wo + (size_t)r * RK[l] + c] = pad[(size_t)r * LK[l] + c];
-      grad[bo + r] = pad[(size_t)LN[l] * LK[l] + r];
-    }
+  const float *X = s->host->x, *Y = s->host->y;
+  if (n <= HOST_ROWS) {
+    memcpy(s->host->x, x, (size_t)n * NIN * 4);
+    memcpy(s->host->y, y, (size_t)n * NOUT * 4);
+  } else {
+    X = s->at<float>(s->S.qx);
+    Y = s->at<float>(s->S.qy);
+    HC(hipMemcpyAsync(s->ws + s->S.qx, x, (size_t)n * NIN * 4, hipMemcpyHostToDevice, s->stream));
+    HC(hipMemcpyAsync(s->ws + s->S.qy, y, (size_t)n * NOUT * 4, hipMemcpyHostToDevice, s->stream));
   }
-  double acc = 0.0;
-  HC(hipMemcpyAsync(&acc, s->ws + s->S.loss, 8, hipMemcpyDeviceToHost, s->stream));
-  HC(hipStreamSynchronize(s->stream));
-  if (loss_out) *loss_out = acc;
+  lbm_status st = begin_loss(s);
+  if (st != LBM_OK) return st;
+  if ((st = sample_pass(s, X, Y, nullptr, nullptr, n)) != LBM_OK) return st;
+  UpdateArgs u = update_args(s, n);
+  u.packed = s->host->packed;
+  u.loss_out = &s->host->loss;
+  HC(update(u, s->stream));
+  if ((st = end_loss(s)) != LBM_OK) return st;
+  memcpy(grad, s->host->packed, sizeof s->host->packed);
+  if (loss_out) *loss_out = s->host->loss;
   return LBM_OK;
 }
 
 lbm_status surr_predict(surr_net* s, const float* x, int32_t n, float* y) {
   if (!s || !x || !y || n < 0) return fail(LBM_EINVAL, "bad arguments");
-  for (int off = 0; off < n; off += s->S.Bp) {
-    const int rows = std::min(s->S.Bp, n - off);
-    HC(hipMemcpyAsync(s->ws + s->S.qx, x + (size_t)off * NIN, (size_t)rows * NIN * 4,
-                      hipMemcpyHostToDevice, s->stream));
-    lbm_status st = forward(s, s->at<float>(s->S.qx), nullptr, nullptr, nullptr, rows);
-    if (st != LBM_OK) return st;
-    HC(hipMemcpy2DAsync(y + (size_t)off * NOUT, NOUT * 4, s->ws + s->S.y, NOUTP * 4, NOUT * 4, rows,
-                        hipMemcpyDeviceToHost, s->stream));
+  for (int off = 0; off < n; off += HOST_ROWS) {
+    const int rows = std::min(HOST_ROWS, n - off);
+    memcpy(s->host->x, x + (size_t)off * NIN, (size_t)rows * NIN * 4);
+    HC(predict(net_args(s), RowArgs{s->host->x, nullptr, rows}, s->host->y, s->stream));
+    HC(hipStreamSynchronize(s->stream));
+    memcpy(y + (size_t)off * NOUT, s->host->y, (size_t)rows * NOUT * 4);
   }
-  HC(hipStreamSynchronize(s->stream));
   return LBM_OK;
 }
 
 lbm_status surr_predict_noalloc(const surr_net* s, const float* x, int32_t n, float* y,
                                 void* stream) {
   if (!s || !x || !y) return fail(LBM_EINVAL, "NULL argument");
-  if (n < 1 || n > SCRATCH_ROWS)
-    return fail(LBM_EINVAL, "surr_predict_noalloc takes 1..%d rows per call, got %d", SCRATCH_ROWS, n);
+  if (n < 1 || n > NOALLOC_ROWS)
+    return fail(LBM_EINVAL, "surr_predict_noalloc takes 1..%d rows per call, got %d", NOALLOC_ROWS, n);
   const hipStream_t st = (hipStream_t)stream;
   int cur = 0, dev = 0;
   HC(hipGetDevice(&cur));
   dev = cur;
   if (st) HC(hipStreamGetDevice(st, &dev));
   if (dev != cur) return fail(LBM_EINVAL, "the stream's device %d is not the current device %d", dev, cur);
-  char* sc = nullptr;
-  lbm_status r = scratch_ptr(dev, &sc);
-  if (r != LBM_OK) return r;
-  const SLayout& S = s->S;
-  const int B = (n + 31) / 32 * 32;
-  HC(gather(x, nullptr, nullptr, nullptr, n, B, s->at<float>(S.lo), s->at<float>(S.hi),
-            (__bf16*)(sc + SC_X0), (__bf16*)(sc + SC_X0T), nullptr, nullptr, st));
-  const __bf16* in = (const __bf16*)(sc + SC_X0);
-  int ldin = KIN;
-  for (int l = 0; l < 3; ++l) {
-    __bf16* out = (__bf16*)(sc + (l % 2 == 0 ? SC_HA : SC_HB));
-    GemmArgs g{};
-    g.A = in; g.lda = ldin; g.Bt = s->at<__bf16>(S.wb[l]); g.ldb = LK[l];
-    g.M = B; g.N = LN[l]; g.K = LK[l];
-    g.bias = s->at<float>(S.p[l]) + (size_t)LN[l] * LK[l];
-    g.outf = (float*)(sc + SC_HF); g.outb = out; g.outt = (__bf16*)(sc + SC_HT);
-    g.ldo = NHID; g.ldt = B;
-    HC(gemm(EPI_HIDDEN, g, st));
-    in = out;
-    ldin = NHID;
-  }
-  GemmArgs g{};
-  g.A = in; g.lda = NHID; g.Bt = s->at<__bf16>(S.wb[3]); g.ldb = NHID;
-  g.M = B; g.N = NOUTP; g.K = NHID;
-  g.bias = s->at<float>(S.p[3]) + (size_t)NOUTP * NHID;
-  g.outf = (float*)(sc + SC_Y); g.ldo = NOUTP;
-  HC(gemm(EPI_OUTPUT, g, st));
-  HC(hipMemcpy2DAsync(y, NOUT * 4, sc + SC_Y, NOUTP * 4, NOUT * 4, n, hipMemcpyDeviceToDevice, st));
+  HC(predict(net_args(s), RowArgs{x, nullptr, n}, y, st));
   return LBM_OK;
 }
 
-void surr_destroy(surr_net* s) { delete s; }
+void surr_destroy(surr_net* s) {
+  if (!s) return;
+  if (s->host) (void)hipHostFree(s->host);
+  delete s;
+}
 
 }  // extern "C"

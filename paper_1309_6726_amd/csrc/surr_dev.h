@@ -11,31 +11,84 @@ constexpr int KIN = 32;     // padded input width
 constexpr int NHID = 256;   // hidden units
 constexpr int NOUT = 65;    // 64 front positions + closure time
 constexpr int NOUTP = 96;   // padded output width
+constexpr int NL = 4;       // layers
 
-enum { EPI_HIDDEN = 0, EPI_OUTPUT = 1, EPI_BACKWARD = 2, EPI_WGRAD = 3 };
+// padded layer shapes [N x K] and the real ones
+constexpr int LN[NL] = {NHID, NHID, NHID, NOUTP};
+constexpr int LK[NL] = {KIN, NHID, NHID, NHID};
+constexpr int RN[NL] = {NHID, NHID, NHID, NOUT};
+constexpr int RK[NL] = {NIN, NHID, NHID, NHID};
+constexpr int NPARAMS = NHID * NIN + NHID + 2 * (NHID * NHID + NHID) + NOUT * NHID + NOUT;
 
-struct GemmArgs {
-  const __bf16* A;   // [M x K], leading dimension lda
-  const __bf16* Bt;  // [N x K], leading dimension ldb
-  int M, N, K, lda, ldb;
-  const float* bias; // [N] (hidden, output)
-  const float* act;  // [M x ldo] activations of this layer (backward mask)
-  float* outf;       // FP32 output [M x ldo]
-  __bf16* outb;      // BF16 output [M x ldo]
-  __bf16* outt;      // BF16 transposed output [N x ldt]
-  int ldo, ldt;
+// Matrix operands are kept in the order in which the matrix instruction takes
+// them ("fragments"): an operand with R rows and contraction length K is
+// stored as [R / 32 tiles][K / 16 steps][64 lanes][8], lane l holding the
+// elements 8 (l / 32) .. +7 of its step for row l mod 32, so a wavefront's
+// load of one fragment is 1 KB in a row.
+
+// The trained network as the kernels read it.
+struct NetArgs {
+  const __bf16* wf[NL];    // W_l as forward operand (rows = units of layer l)
+  const __bf16* wt[NL];    // W_l^T as backward operand (rows = inputs of layer l); l >= 1
+  const float* bias[NL];
+  const float *lo, *hi;    // normalisation box
 };
 
-hipError_t gemm(int epi, const GemmArgs& g, hipStream_t st);
-hipError_t gather(const float* X, const float* Y, const float* RW, const int32_t* idx, int rows,
-                  int Bp, const float* lo, const float* hi, __bf16* x0, __bf16* x0t, float* t,
-                  float* rw, hipStream_t st);
-hipError_t loss(const float* y, const float* t, const float* w, const float* rw, int rows, int Bp,
-                __bf16* dy, __bf16* dyt, double* acc, hipStream_t st);
-hipError_t colsum(const __bf16* dht, int Bp, int n_units, float* db, hipStream_t st);
-hipError_t adam(float* p, float* m1, float* m2, const float* grad, int count, int nw, int N, int K,
-                float lr, float b1, float b2, float eps, float c1, float c2, __bf16* wb,
-                __bf16* wt, hipStream_t st);
-hipError_t weight_copies(const float* w, int N, int K, __bf16* wb, __bf16* wt, hipStream_t st);
+// Samples of one call: row r is sample idx[r] (r itself without idx).
+struct RowArgs {
+  const float* X;
+  const int32_t* idx;
+  int rows;
+};
+
+// What training needs beyond the forward pass.  at / dt hold the activations
+// entering layer l and the gradient of its pre-activations as fragments with
+// the units as rows and the batch as contraction (ks steps of 16 samples per
+// tile).
+struct TrainArgs {
+  const float* Y;      // targets [n x NOUT]
+  const float* RW;     // row weights or null
+  const float* lw;     // output weights
+  float scale;         // 1 / (rows * sum of output weights)
+  __bf16* at[NL];
+  __bf16* dt[NL];
+  int ks;
+  double* loss;
+};
+
+// Parameters, Adam moments and operand copies of every layer; padded W [N x K]
+// followed by the bias [N].
+struct UpdateArgs {
+  const __bf16* at[NL];
+  const __bf16* dt[NL];
+  int ks, steps;           // allocated and used steps of 16 samples
+  float* p[NL];
+  float* m1[NL];
+  float* m2[NL];
+  __bf16* wf[NL];
+  __bf16* wt[NL];
+  float lr, b1, b2, eps, c1, c2;
+  float* packed;           // gradients only: packed output, nothing is updated
+  double* loss;            // with loss_out: the accumulated loss is handed over
+  double* loss_out;        // there and its accumulator cleared
+};
+
+// Packed parameters and what is kept of them; the launchers fill in the shapes.
+struct PackArgs {
+  float* packed;
+  float* p[NL];
+  float* m1[NL];
+  float* m2[NL];
+  __bf16* wf[NL];
+  __bf16* wt[NL];
+  int first[NL], rn[NL], rk[NL], n[NL], k[NL];
+};
+
+// y [rows x NOUT] (host-visible or device memory).
+hipError_t predict(const NetArgs& net, const RowArgs& r, float* y, hipStream_t st);
+hipError_t forward_backward(const NetArgs& net, const RowArgs& r, const TrainArgs& t, hipStream_t st);
+hipError_t update(const UpdateArgs& u, hipStream_t st);
+hipError_t unpack_params(const PackArgs& a, hipStream_t st);
+hipError_t pack_params(const PackArgs& a, hipStream_t st);
 
 }  // namespace surrdev

@@ -4,14 +4,17 @@
 //
 // Every dense-layer product, forward and backward, has the form
 //   C[M x N] = A[M x K] * Bt[N x K]^T
-// with both operands BF16 and contiguous along K, computed on the matrix
-// cores with v_mfma_f32_32x32x16_bf16 (FP32 accumulation).  One wavefront
-// owns one 32 x 32 tile of C; lane l loads the 8 consecutive K elements
-// k0 + 8 (l / 32) .. +7 of row m0 + (l mod 32) of A and of row n0 + (l mod 32)
-// of Bt with one 16-byte load each.  The 16 accumulators of lane l hold
-// C[m0 + 8 (i / 4) + 4 (l / 32) + (i mod 4)][n0 + (l mod 32)], i = 0..15.
-// Shapes are padded: M, N multiples of 32, K a multiple of 16, leading
-// dimensions multiples of 8 elements.
+// on the matrix cores with v_mfma_f32_32x32x16_bf16 (BF16 operands, FP32
+// accumulation, K in ascending steps of 16).  One wavefront owns one 32 x 32
+// tile of C.  Lane l passes the elements k0 + 8 (l / 32) .. +7 of row l mod 32
+// of its A tile and of its Bt tile; its 16 accumulators hold
+// C[8 (i / 4) + 4 (l / 32) + (i mod 4)][l mod 32], i = 0..15.
+//
+// The network is small (149,825 parameters, 300 KB in BF16), so what a call
+// costs is latency: kernel launches and round trips to memory between them.
+// One workgroup therefore takes 32 samples through all layers, activations in
+// LDS, and training is two launches per minibatch: k_rows (forward, loss,
+// backward) and k_update (weight and bias gradients, Adam, operand copies).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -20,207 +23,416 @@
 namespace surrdev {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-template <int EPI>
-__global__ void __launch_bounds__(256) k_gemm_nt(const GemmArgs g) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * 4 + wave;
-  const int tn = g.N >> 5;
-  if (tile >= (g.M >> 5) * tn) return;  // whole wavefront leaves; no barriers below
-  const int m0 = (tile / tn) << 5, n0 = (tile % tn) << 5;
-  const __bf16* a = g.A + (size_t)(m0 + (lane & 31)) * g.lda + 8 * (lane >> 5);
-  const __bf16* b = g.Bt + (size_t)(n0 + (lane & 31)) * g.ldb + 8 * (lane >> 5);
-  floatx16 acc;
+constexpr int ROWS = 32;          // samples per workgroup of k_rows
+constexpr int HS = NHID + 8;      // LDS row strides in elements: 16-byte aligned,
+constexpr int XS = KIN + 8;       // and the 16-byte reads of 16 consecutive rows
+constexpr int YS = NOUTP + 8;     // fall on all 64 banks
+
+__device__ __forceinline__ floatx16 zero16() {
+  floatx16 z;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  for (int k = 0; k < g.K; k += 16) {
-    const bf16x8 av = *(const bf16x8*)(a + k);
-    const bf16x8 bv = *(const bf16x8*)(b + k);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-  }
-  const int n = n0 + (lane & 31);
+  for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+  return z;
+}
+
+// Row of accumulator i in lane l of a 32 x 32 tile.
+__device__ __forceinline__ int acc_row(int i, int half) { return 8 * (i >> 2) + 4 * half + (i & 3); }
+
+template <int KS>
+__device__ __forceinline__ void load_frags(bf16x8* w, const __bf16* frags, int tile, int lane) {
+  const bf16x8* p = (const bf16x8*)frags + (size_t)tile * KS * 64 + lane;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int m = m0 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-    const float v = acc[i];
-    if (EPI == EPI_HIDDEN) {          // h = relu(v + b): FP32, BF16, BF16 transposed
-      const float h = fmaxf(v + g.bias[n], 0.0f);
-      g.outf[(size_t)m * g.ldo + n] = h;
-      g.outb[(size_t)m * g.ldo + n] = (__bf16)h;
-      g.outt[(size_t)n * g.ldt + m] = (__bf16)h;
-    } else if (EPI == EPI_OUTPUT) {   // y = v + b
-      g.outf[(size_t)m * g.ldo + n] = v + g.bias[n];
-    } else if (EPI == EPI_BACKWARD) { // dh = v * relu'(h)
-      const float d = g.act[(size_t)m * g.ldo + n] > 0.0f ? v : 0.0f;
-      g.outb[(size_t)m * g.ldo + n] = (__bf16)d;
-      g.outt[(size_t)n * g.ldt + m] = (__bf16)d;
-    } else {                          // EPI_WGRAD: raw FP32 product
-      g.outf[(size_t)m * g.ldo + n] = v;
-    }
+  for (int s = 0; s < KS; ++s) w[s] = p[s * 64];
+}
+
+// One 32 x 32 tile: A rows from LDS (row stride `stride` elements).
+template <int KS>
+__device__ __forceinline__ floatx16 product(const __bf16* a, int stride, const bf16x8* w, int lane) {
+  const __bf16* ap = a + (lane & 31) * stride + 8 * (lane >> 5);
+  floatx16 acc = zero16();
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(ap + 16 * s), w[s], acc, 0, 0, 0);
+  return acc;
+}
+
+// Element offset of accumulators 4 q .. 4 q + 3 of lane `lane` in fragments
+// that have a tile's columns as rows and its rows as contraction: row tile
+// `tile` of `ks` steps, contraction elements 32 block .. +31.
+__device__ __forceinline__ size_t transposed_at(int ks, int tile, int block, int q, int lane) {
+  return ((size_t)tile * ks + 2 * block + (q >> 1)) * 512 + (q & 1) * 256 + (lane & 31) * 8 + 4 * (lane >> 5);
+}
+
+__device__ __forceinline__ void store_transposed(__bf16* frags, int ks, int tile, int block,
+                                                 const __bf16* v, int lane) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bf16x4 o = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+    *(bf16x4*)(frags + transposed_at(ks, tile, block, q, lane)) = o;
   }
 }
 
-// Rows idx[r] (or r when idx is null) of the raw inputs and targets of the
-// resident data set: normalised inputs (BF16, row-major and transposed) and
-// FP32 targets; padding rows and columns are zero.  Inputs x = (W, L, k_r,
-// theta, threshold); x' = 2 (x - lo) / (hi - lo) - 1, with log10 applied to
-// k_r and its bounds.  One thread per (row, column) of the KIN input columns
-// followed by the NOUTP target columns, rows fastest (so the transposed input
-// stores are coalesced); the row weight is written by column 0.
-__global__ void k_gather(const float* __restrict__ X, const float* __restrict__ Y,
-                         const float* __restrict__ RW, const int32_t* __restrict__ idx, int rows,
-                         int Bp, const float* __restrict__ lo, const float* __restrict__ hi,
-                         __bf16* __restrict__ x0, __bf16* __restrict__ x0t, float* __restrict__ t,
-                         float* __restrict__ rw) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int ncol = KIN + (t ? NOUTP : 0);
-  if (e >= Bp * ncol) return;
-  const int r = e % Bp, j = e / Bp;
-  const bool real = r < rows;
-  const int src = real ? (idx ? idx[r] : r) : 0;
-  if (j < KIN) {
+// Forward pass of 32 samples by one workgroup of eight wavefronts, wavefront
+// w owning units 32 w .. +31 of a hidden layer; with TRAIN also the loss
+// gradient and the backward pass.
+//
+// Inputs x = (W, L, k_r, theta, threshold) are normalised to
+// 2 (x - lo) / (hi - lo) - 1, with log10 applied to k_r and its bounds; rows
+// beyond the last sample have zero inputs and zero loss gradient.
+//
+// Loss: sum_rows c_r sum_j w_j (y - t)^2 * scale with per-output weights w and
+// per-row weights c, added to *loss.
+//
+// What bounds it: one workgroup reads every weight once (328 KB forward, as
+// much again backward) through one CU's memory port, so the fragments of a
+// layer are requested two layers ahead of their use.  32 samples is the
+// matrix instruction's tile; fewer workgroups than CUs run for small batches.
+// Measured: 5.6 us for 8 prediction rows (33 us as six launches and a copy),
+// 16.0 us for a training minibatch of 256, which with k_update's 6.4 us took
+// 21 launches and 120 us when every layer product, bias sum and update was a
+// launch of its own.
+template <bool TRAIN>
+__global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs ra,
+                                              const TrainArgs ta, float* __restrict__ y) {
+  __shared__ __align__(16) __bf16 sx[ROWS * XS];
+  __shared__ __align__(16) __bf16 sa[ROWS * HS];
+  __shared__ __align__(16) __bf16 sb[ROWS * HS];
+  __shared__ __align__(16) __bf16 sy[TRAIN ? ROWS * YS : 8];
+  __shared__ float st[TRAIN ? ROWS * NOUT : 1];  // targets
+  __shared__ float sc[TRAIN ? ROWS : 1];         // row weights
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int col = lane & 31, half = lane >> 5;
+  const int r0 = blockIdx.x * ROWS;
+  const int unit = 32 * wave + col;
+
+  bf16x8 w0[2], wa[16], wb[16];
+  load_frags<2>(w0, net.wf[0], wave, lane);
+  load_frags<16>(wa, net.wf[1], wave, lane);
+  float bias[NL];
+#pragma unroll
+  for (int l = 0; l < 3; ++l) bias[l] = net.bias[l][unit];
+  bias[3] = wave < 3 ? net.bias[3][unit] : 0.0f;
+
+  for (int e = threadIdx.x; e < ROWS * KIN; e += 512) {
+    const int r = e / KIN, j = e % KIN;
     float v = 0.0f;
-    if (real && j < NIN) {
-      float x = X[(size_t)src * NIN + j], a = lo[j], b = hi[j];
+    if (r0 + r < ra.rows && j < NIN) {
+      const int src = ra.idx ? ra.idx[r0 + r] : r0 + r;
+      float x = ra.X[(size_t)src * NIN + j], a = net.lo[j], b = net.hi[j];
       if (j == 2) { x = log10f(x); a = log10f(a); b = log10f(b); }
       v = 2.0f * (x - a) / (b - a) - 1.0f;
     }
-    x0[(size_t)r * KIN + j] = (__bf16)v;
-    x0t[(size_t)j * Bp + r] = (__bf16)v;
-    if (j == 0 && rw) rw[r] = real ? (RW ? RW[src] : 1.0f) : 0.0f;
-  } else {
-    const int c = j - KIN;
-    t[(size_t)r * NOUTP + c] = (real && Y && c < NOUT) ? Y[(size_t)src * NOUT + c] : 0.0f;
+    sx[r * XS + j] = (__bf16)v;
+    if (TRAIN)  // samples as contraction: unit j, sample r of block blockIdx.x
+      ta.at[0][((size_t)2 * blockIdx.x + (r >> 4)) * 512 + (((r >> 3) & 1) * 32 + j) * 8 + (r & 7)] = (__bf16)v;
   }
-}
-
-// Weighted mean-squared error over the real rows and outputs:
-// loss = sum_rows c_r sum_j w_j (y - t)^2 / (rows * sum_j w_j) with per-output
-// weights w and per-row weights c, its gradient dY (BF16 row-major and
-// transposed) and the loss added to *loss_acc.
-__global__ void __launch_bounds__(256) k_loss(const float* __restrict__ y, const float* __restrict__ t,
-                                              const float* __restrict__ w, const float* __restrict__ rw,
-                                              int rows, int Bp,
-                                              __bf16* __restrict__ dy, __bf16* __restrict__ dyt,
-                                              double* __restrict__ loss_acc) {
-  __shared__ double red[256];
-  double s = 0.0;
-  float wsum = 0.0f;
-  for (int j = 0; j < NOUT; ++j) wsum += w[j];
-  const float scale = 1.0f / ((float)rows * wsum);
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < Bp * NOUTP; e += gridDim.x * blockDim.x) {
-    const int r = e / NOUTP, j = e - r * NOUTP;
-    float d = 0.0f;
-    if (r < rows && j < NOUT) {
-      const float diff = y[e] - t[e];
-      const float c = w[j] * rw[r] * scale;
-      d = 2.0f * c * diff;
-      s += (double)(c * diff * diff);
+  if (TRAIN) {
+    // requested with the inputs, so the loss waits on no further round trip
+    for (int e = threadIdx.x; e < ROWS * NOUT; e += 512) {
+      const int r = r0 + e / NOUT;
+      if (r < ra.rows) st[e] = ta.Y[(size_t)(ra.idx ? ra.idx[r] : r) * NOUT + e % NOUT];
     }
-    dy[e] = (__bf16)d;
-    dyt[(size_t)j * Bp + r] = (__bf16)d;
+    const int r = r0 + (int)threadIdx.x;
+    if (threadIdx.x < ROWS && r < ra.rows) sc[threadIdx.x] = ta.RW ? ta.RW[ra.idx ? ra.idx[r] : r] : 1.0f;
   }
-  red[threadIdx.x] = s;
+  load_frags<16>(wb, net.wf[2], wave, lane);
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicAdd(loss_acc, red[0]);
-}
 
-// Bias gradients: column sums of dH, read from its transposed copy (one
-// wavefront per output unit, fixed summation order).
-__global__ void __launch_bounds__(64) k_colsum(const __bf16* __restrict__ dht, int Bp, int n_units,
-                                               float* __restrict__ db) {
-  const int n = blockIdx.x;
-  if (n >= n_units) return;
-  float s = 0.0f;
-  for (int m = threadIdx.x; m < Bp; m += 64) s += (float)dht[(size_t)n * Bp + m];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
-  if (threadIdx.x == 0) db[n] = s;
-}
+  unsigned live[3];  // units with a positive activation, one bit per accumulator
+  // h = relu(v + b) of one tile: into LDS and, for training, as the next
+  // layer's transposed operand
+  auto hidden = [&](const floatx16& acc, int l, __bf16* dst) {
+    __bf16 h[16];
+    live[l] = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float v = fmaxf(acc[i] + bias[l], 0.0f);
+      live[l] |= v > 0.0f ? 1u << i : 0u;
+      h[i] = (__bf16)v;
+      dst[acc_row(i, half) * HS + unit] = h[i];
+    }
+    if (TRAIN) store_transposed(ta.at[l + 1], ta.ks, wave, blockIdx.x, h, lane);
+  };
+  hidden(product<2>(sx, XS, w0, lane), 0, sa);
+  __syncthreads();
+  hidden(product<16>(sa, HS, wa, lane), 1, sb);
+  if (wave < 3) load_frags<16>(wa, net.wf[3], wave, lane);
+  bf16x8 wc[6];
+  if (TRAIN) load_frags<6>(wc, net.wt[3], wave, lane);
+  __syncthreads();
+  hidden(product<16>(sb, HS, wb, lane), 2, sa);
+  if (TRAIN) load_frags<16>(wb, net.wt[2], wave, lane);
+  __syncthreads();
 
-// Adam on the padded FP32 master parameters, then the BF16 copies used by the
-// GEMMs: W (row-major [N x K]) and W^T ([K x N]).  Entries of a weight matrix
-// at index < nw; biases follow.
-__global__ void k_adam(float* __restrict__ p, float* __restrict__ m1, float* __restrict__ m2,
-                       const float* __restrict__ grad, int count, int nw, int N, int K,
-                       float lr, float b1, float b2, float eps, float c1, float c2,
-                       __bf16* __restrict__ wb, __bf16* __restrict__ wt) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
-    const float gi = grad[i];
-    const float a = b1 * m1[i] + (1.0f - b1) * gi;
-    const float v = b2 * m2[i] + (1.0f - b2) * gi * gi;
-    m1[i] = a;
-    m2[i] = v;
-    const float w = p[i] - lr * (a / c1) / (sqrtf(v / c2) + eps);
-    p[i] = w;
-    if (i < nw) {
-      const int r = i / K, c = i - r * K;
-      wb[i] = (__bf16)w;
-      wt[(size_t)c * N + r] = (__bf16)w;
+  if (wave < 3) {
+    const floatx16 acc = product<16>(sa, HS, wa, lane);
+    if (!TRAIN) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = r0 + acc_row(i, half);
+        if (r < ra.rows && unit < NOUT) y[(size_t)r * NOUT + unit] = acc[i] + bias[3];
+      }
+    } else {
+      double sum = 0.0;
+      __bf16 dy[16];
+      const float lw = unit < NOUT ? ta.lw[unit] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = acc_row(i, half);
+        float d = 0.0f;
+        if (r0 + r < ra.rows && unit < NOUT) {
+          const float yv = acc[i] + bias[3];
+          const float diff = yv - st[r * NOUT + unit];
+          const float c = lw * sc[r] * ta.scale;
+          d = 2.0f * c * diff;
+          sum += (double)(c * diff * diff);
+        }
+        dy[i] = (__bf16)d;
+        sy[r * YS + unit] = dy[i];
+      }
+      store_transposed(ta.dt[3], ta.ks, wave, blockIdx.x, dy, lane);
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
+      if (lane == 0) atomicAdd(ta.loss, sum);
     }
   }
+  if (!TRAIN) return;
+
+  load_frags<16>(wa, net.wt[1], wave, lane);
+  __syncthreads();
+  // dh = v where the unit was live: into LDS for the next product and as the
+  // transposed operand of the weight gradient
+  auto masked = [&](const floatx16& acc, int l, __bf16* dst) {
+    __bf16 d[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      d[i] = (__bf16)(live[l] & (1u << i) ? acc[i] : 0.0f);
+      if (dst) dst[acc_row(i, half) * HS + unit] = d[i];
+    }
+    store_transposed(ta.dt[l], ta.ks, wave, blockIdx.x, d, lane);
+  };
+  masked(product<6>(sy, YS, wc, lane), 2, sb);
+  __syncthreads();
+  masked(product<16>(sb, HS, wb, lane), 1, sa);
+  __syncthreads();
+  masked(product<16>(sa, HS, wa, lane), 0, nullptr);
 }
 
-// BF16 copies of one padded weight matrix (after parameters are set).
-__global__ void k_weight_copies(const float* __restrict__ w, int N, int K, __bf16* __restrict__ wb,
-                                __bf16* __restrict__ wt) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N * K; i += gridDim.x * blockDim.x) {
-    const int r = i / K, c = i - r * K;
-    wb[i] = (__bf16)w[i];
-    wt[(size_t)c * N + r] = (__bf16)w[i];
+// ---- parameter update ------------------------------------------------------
+// Tiles of 32 x 32 weights of each layer, then groups of eight biases.
+constexpr int BIAS_GROUP = 8;
+__host__ __device__ constexpr int weight_tiles(int l) { return (LN[l] / 32) * (LK[l] / 32); }
+constexpr int WEIGHT_TILES = weight_tiles(0) + weight_tiles(1) + weight_tiles(2) + weight_tiles(3);
+constexpr int BIAS_GROUPS = (3 * NHID + NOUTP) / BIAS_GROUP;
+static_assert(BIAS_GROUPS % 4 == 0, "four bias groups per workgroup");
+
+// Offset of W_l in the packed parameters; b_l follows it.
+__host__ __device__ constexpr int packed_weights(int l) {
+  constexpr int first = RN[0] * RK[0] + RN[0], hidden = NHID * NHID + NHID;
+  return l == 0 ? 0 : first + (l - 1) * hidden;
+}
+
+// Adam on one FP32 parameter, the fused multiply-adds written out so that
+// every inlined copy rounds alike.
+__device__ __forceinline__ float adam(const UpdateArgs& u, float g, float p, float& m1, float& m2) {
+  const float a = fmaf(1.0f - u.b1, g, u.b1 * m1);
+  const float v = fmaf(g, (1.0f - u.b2) * g, u.b2 * m2);
+  m1 = a;
+  m2 = v;
+  return p - u.lr * (a / u.c1) / (sqrtf(v / u.c2) + u.eps);
+}
+
+// Gradient of 32 x 32 weights of layer L (contraction over the batch), then
+// Adam on the FP32 master weights and both BF16 operand copies.  Each of the
+// four wavefronts forms the whole product (16 matrix instructions for 256
+// samples, operands shared in L1) and updates four of its sixteen rows per
+// lane: the divisions and square roots of Adam are what this launch waits on
+// otherwise (7.8 us a minibatch with one wavefront per tile).
+template <int L>
+__device__ __forceinline__ void update_weights(const UpdateArgs& u, int tile, __bf16* lds) {
+  constexpr int N = LN[L], K = LK[L], TK = K / 32;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+  const int tn = tile / TK, tk = tile % TK;
+  const bf16x8* a = (const bf16x8*)u.dt[L] + (size_t)tn * u.ks * 64 + lane;
+  const bf16x8* b = (const bf16x8*)u.at[L] + (size_t)tk * u.ks * 64 + lane;
+  const int k = 32 * tk + col;
+  const int n0 = 32 * tn + acc_row(4 * wave, half);  // rows n0 .. n0 + 3 of this lane
+  float p[4], m1[4], m2[4];
+  if (!u.packed) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = (n0 + i) * K + k;
+      p[i] = u.p[L][e];
+      m1[i] = u.m1[L][e];
+      m2[i] = u.m2[L][e];
+    }
   }
+  floatx16 acc = zero16();
+  // eight steps of operands in flight; u.steps is even
+  int s = 0;
+  for (; s + 8 <= u.steps; s += 8) {
+    bf16x8 av[8], bv[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { av[q] = a[(s + q) * 64]; bv[q] = b[(s + q) * 64]; }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[q], bv[q], acc, 0, 0, 0);
+  }
+  for (; s < u.steps; ++s)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s * 64], b[s * 64], acc, 0, 0, 0);
+  float g[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    g[i] = wave < 2 ? (wave == 0 ? acc[i] : acc[4 + i]) : (wave == 2 ? acc[8 + i] : acc[12 + i]);
+  if (u.packed) {
+    constexpr int w0 = packed_weights(L);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (n0 + i < RN[L] && k < RK[L]) u.packed[w0 + (n0 + i) * RK[L] + k] = g[i];
+    return;
+  }
+  bf16x4 w;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int e = (n0 + i) * K + k;
+    const float v = adam(u, g[i], p[i], m1[i], m2[i]);
+    u.p[L][e] = v;
+    u.m1[L][e] = m1[i];
+    u.m2[L][e] = m2[i];
+    w[i] = (__bf16)v;
+    lds[(acc_row(4 * wave, half) + i) * XS + col] = w[i];
+  }
+  if (L > 0) *(bf16x4*)(u.wt[L] + transposed_at(N / 16, tk, tn, wave, lane)) = w;
+  __syncthreads();
+  if (wave >= 2) return;
+  bf16x8* wf = (bf16x8*)u.wf[L] + ((size_t)tn * (K / 16) + 2 * tk) * 64 + lane;
+  wf[wave * 64] = *(const bf16x8*)(lds + col * XS + 16 * wave + 8 * half);
+}
+
+// Eight biases from n0 on: sum over the batch of the pre-activation gradient
+// (lane t adds samples t, t + 64, ..., then a fixed tree), then Adam.
+template <int L>
+__device__ __forceinline__ void update_biases(const UpdateArgs& u, int n0) {
+  const int lane = threadIdx.x & 63;
+  const __bf16* d = u.dt[L] + (size_t)(n0 >> 5) * u.ks * 512 + (n0 & 31) * 8;
+  float s[BIAS_GROUP];
+#pragma unroll
+  for (int j = 0; j < BIAS_GROUP; ++j) s[j] = 0.0f;
+  for (int m = lane; m < 16 * u.steps; m += 64) {
+    const __bf16* dm = d + (m >> 4) * 512 + ((m >> 3) & 1) * 256 + (m & 7);
+#pragma unroll
+    for (int j = 0; j < BIAS_GROUP; ++j) s[j] += (float)dm[8 * j];
+  }
+  float g = 0.0f;  // lane j: gradient of bias n0 + j
+#pragma unroll
+  for (int j = 0; j < BIAS_GROUP; ++j) {
+    for (int o = 32; o > 0; o >>= 1) s[j] += __shfl_down(s[j], o);
+    const float t = __shfl(s[j], 0);
+    if (lane == j) g = t;
+  }
+  if (lane >= BIAS_GROUP) return;
+  const int n = n0 + lane;
+  if (u.packed) {
+    if (n < RN[L]) u.packed[packed_weights(L) + RN[L] * RK[L] + n] = g;
+    return;
+  }
+  const int e = LN[L] * LK[L] + n;
+  u.p[L][e] = adam(u, g, u.p[L][e], u.m1[L][e], u.m2[L][e]);
+}
+
+// One workgroup per weight tile, one wavefront per bias group: 187
+// workgroups, each one chain of loads, products and stores.
+__global__ void __launch_bounds__(256) k_update(const UpdateArgs u) {
+  __shared__ __align__(16) __bf16 lds[32 * XS];
+  int t = blockIdx.x;
+  if (t < weight_tiles(0)) return update_weights<0>(u, t, lds);
+  t -= weight_tiles(0);
+  if (t < weight_tiles(1)) return update_weights<1>(u, t, lds);
+  t -= weight_tiles(1);
+  if (t < weight_tiles(2)) return update_weights<2>(u, t, lds);
+  t -= weight_tiles(2);
+  if (t < weight_tiles(3)) return update_weights<3>(u, t, lds);
+  if (t == weight_tiles(3) && threadIdx.x == 0 && u.loss_out) {
+    *u.loss_out = *u.loss;
+    *u.loss = 0.0;
+  }
+  t = 4 * (t - weight_tiles(3)) + (int)(threadIdx.x >> 6);  // bias group
+  constexpr int G = NHID / BIAS_GROUP;
+  if (t < G) return update_biases<0>(u, t * BIAS_GROUP);
+  if (t < 2 * G) return update_biases<1>(u, (t - G) * BIAS_GROUP);
+  if (t < 3 * G) return update_biases<2>(u, (t - 2 * G) * BIAS_GROUP);
+  update_biases<3>(u, (t - 3 * G) * BIAS_GROUP);
+}
+
+// Padded parameters of layer blockIdx.y from the packed ones (zero in the
+// padding), Adam moments cleared, and both BF16 operand copies of the weights.
+__global__ void k_unpack(const PackArgs a) {
+  const int l = blockIdx.y, N = a.n[l], K = a.k[l];
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N * K + N) return;
+  const bool weight = i < N * K;
+  const int r = weight ? i / K : i - N * K, c = weight ? i - r * K : 0;
+  const float* in = a.packed + a.first[l] + (weight ? r * a.rk[l] + c : a.rn[l] * a.rk[l] + r);
+  const float v = r < a.rn[l] && c < a.rk[l] ? *in : 0.0f;
+  a.p[l][i] = v;
+  a.m1[l][i] = 0.0f;
+  a.m2[l][i] = 0.0f;
+  if (!weight) return;
+  auto at = [](int row, int k, int len) {
+    return ((size_t)(row >> 5) * (len >> 4) + (k >> 4)) * 512 + (((k >> 3) & 1) * 32 + (row & 31)) * 8 + (k & 7);
+  };
+  a.wf[l][at(r, c, K)] = (__bf16)v;
+  if (l > 0) a.wt[l][at(c, r, N)] = (__bf16)v;
+}
+
+// Real entries of the padded parameters (layer blockIdx.y) into the packed
+// layout.
+__global__ void k_pack(const PackArgs a) {
+  const int l = blockIdx.y;
+  const int nw = a.rn[l] * a.rk[l], i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nw + a.rn[l])
+    a.packed[a.first[l] + i] = i < nw ? a.p[l][(i / a.rk[l]) * a.k[l] + i % a.rk[l]]
+                                      : a.p[l][a.n[l] * a.k[l] + i - nw];
 }
 
 // ---- launchers ------------------------------------------------------------
-hipError_t gemm(int epi, const GemmArgs& g, hipStream_t st) {
-  const int tiles = (g.M / 32) * (g.N / 32);
-  const dim3 grid((tiles + 3) / 4), block(256);
-  switch (epi) {
-    case EPI_HIDDEN: hipLaunchKernelGGL(k_gemm_nt<EPI_HIDDEN>, grid, block, 0, st, g); break;
-    case EPI_OUTPUT: hipLaunchKernelGGL(k_gemm_nt<EPI_OUTPUT>, grid, block, 0, st, g); break;
-    case EPI_BACKWARD: hipLaunchKernelGGL(k_gemm_nt<EPI_BACKWARD>, grid, block, 0, st, g); break;
-    default: hipLaunchKernelGGL(k_gemm_nt<EPI_WGRAD>, grid, block, 0, st, g); break;
+hipError_t predict(const NetArgs& net, const RowArgs& r, float* y, hipStream_t st) {
+  hipLaunchKernelGGL(k_rows<false>, dim3((r.rows + ROWS - 1) / ROWS), dim3(512), 0, st, net, r, TrainArgs{}, y);
+  return hipGetLastError();
+}
+
+hipError_t forward_backward(const NetArgs& net, const RowArgs& r, const TrainArgs& t, hipStream_t st) {
+  hipLaunchKernelGGL(k_rows<true>, dim3((r.rows + ROWS - 1) / ROWS), dim3(512), 0, st, net, r, t, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t update(const UpdateArgs& u, hipStream_t st) {
+  hipLaunchKernelGGL(k_update, dim3(WEIGHT_TILES + BIAS_GROUPS / 4), dim3(256), 0, st, u);
+  return hipGetLastError();
+}
+
+static PackArgs with_shapes(PackArgs a) {
+  for (int l = 0; l < NL; ++l) {
+    a.first[l] = packed_weights(l);
+    a.rn[l] = RN[l];
+    a.rk[l] = RK[l];
+    a.n[l] = LN[l];
+    a.k[l] = LK[l];
   }
+  return a;
+}
+
+static dim3 pack_grid() { return dim3((NHID * NHID + NHID + 255) / 256, NL); }
+
+hipError_t unpack_params(const PackArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_unpack, pack_grid(), dim3(256), 0, st, with_shapes(a));
   return hipGetLastError();
 }
 
-hipError_t gather(const float* X, const float* Y, const float* RW, const int32_t* idx, int rows,
-                  int Bp, const float* lo, const float* hi, __bf16* x0, __bf16* x0t, float* t,
-                  float* rw, hipStream_t st) {
-  const int n = Bp * (KIN + (t ? NOUTP : 0));
-  hipLaunchKernelGGL(k_gather, dim3((n + 255) / 256), dim3(256), 0, st, X, Y, RW, idx, rows, Bp,
-                     lo, hi, x0, x0t, t, rw);
-  return hipGetLastError();
-}
-
-hipError_t loss(const float* y, const float* t, const float* w, const float* rw, int rows, int Bp,
-                __bf16* dy, __bf16* dyt, double* acc, hipStream_t st) {
-  const int blocks = (Bp * NOUTP + 255) / 256 < 256 ? (Bp * NOUTP + 255) / 256 : 256;
-  hipLaunchKernelGGL(k_loss, dim3(blocks), dim3(256), 0, st, y, t, w, rw, rows, Bp, dy, dyt, acc);
-  return hipGetLastError();
-}
-
-hipError_t colsum(const __bf16* dht, int Bp, int n_units, float* db, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsum, dim3(n_units), dim3(64), 0, st, dht, Bp, n_units, db);
-  return hipGetLastError();
-}
-
-hipError_t adam(float* p, float* m1, float* m2, const float* grad, int count, int nw, int N, int K,
-                float lr, float b1, float b2, float eps, float c1, float c2, __bf16* wb,
-                __bf16* wt, hipStream_t st) {
-  const int blocks = (count + 255) / 256 < 1024 ? (count + 255) / 256 : 1024;
-  hipLaunchKernelGGL(k_adam, dim3(blocks), dim3(256), 0, st, p, m1, m2, grad, count, nw, N, K, lr,
-                     b1, b2, eps, c1, c2, wb, wt);
-  return hipGetLastError();
-}
-
-hipError_t weight_copies(const float* w, int N, int K, __bf16* wb, __bf16* wt, hipStream_t st) {
-  const int blocks = (N * K + 255) / 256 < 1024 ? (N * K + 255) / 256 : 1024;
-  hipLaunchKernelGGL(k_weight_copies, dim3(blocks), dim3(256), 0, st, w, N, K, wb, wt);
+hipError_t pack_params(const PackArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_pack, pack_grid(), dim3(256), 0, st, with_shapes(a));
   return hipGetLastError();
 }
 
