@@ -183,8 +183,10 @@ lbm_status lbm_save(lbm_sim* sim, void* blob, size_t cap, size_t* n);
 lbm_status lbm_load(lbm_sim* sim, const void* blob, size_t n);
 
 /* Launch shape of the fused step: tx threads per workgroup (64, 128 or 256)
- * covering tx-2 owned columns (tx-4 in the moment scheme), sy owned rows per
- * workgroup (1..4096).  The shape changes no result bit. */
+ * covering tx-2 owned columns, sy owned rows per workgroup (1..4096).  In the
+ * moment scheme tx is 64 lanes covering 60 columns, and a workgroup runs one
+ * wavefront, or one per row where the library finds that faster.  Until a shape
+ * is set, one is chosen from the lattice.  The shape changes no result bit. */
 lbm_status lbm_set_tile(lbm_sim* sim, int32_t tx, int32_t sy);
 lbm_status lbm_get_tile(const lbm_sim* sim, int32_t* tx, int32_t* sy);
 

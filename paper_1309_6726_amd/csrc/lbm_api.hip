@@ -126,7 +126,7 @@ struct lbm_sim {
   char* ws;
   int cur;         // buffer holding the current state
   long long step;  // current state index
-  int tx, sy;
+  int tx, sy;      // launch shape; 0: not set, default_tile decides
   int nt;          // 1: the step's loads carry the non-temporal cache hint
   int scheme;      // LBM_SCHEME_*
   bool mom;        // f[cur] holds moments of the last step, not populations
@@ -153,13 +153,36 @@ lbm_status guard(const lbm_sim* s) {
 
 bool tile_ok(int tx, int sy) { return (tx == 64 || tx == 128 || tx == 256) && sy >= 1 && sy <= 4096; }
 
-void default_tile(const lbm_params& p, int* tx, int* sy) {
-  *tx = p.nx >= 1024 ? 256 : (p.nx >= 256 ? 128 : 64);
-  *sy = 16;
-}
-
 bool use_moments(int scheme, const lbm_params& p) {
   return scheme == LBM_SCHEME_MOMENTS || (scheme == LBM_SCHEME_AUTO && p.tau == 1.0);
+}
+
+// Launch shape of a handle that none was set for.
+//
+// Moment step: the lowest tiles (one wavefront per row) that give every CU no
+// more than one workgroup, since rows in series cost 1.5 us each and an idle
+// CU nothing; where eight rows per tile do not get there, eight (12 wavefronts,
+// two workgroups per CU).  us per step, against 16 rows per tile before: 256x32
+// without solute 3.65 at 1 row, 23.3; 1024x64 5.1 at 5 rows, 29.6; 509x40 with
+// the variants 4.4 at 2 rows, 37; 700x500 10.9 at 8 rows, 34 (4 rows 11.8,
+// 12 rows 11.6); 1448^2 44 at 8 rows, 61.  Beyond the cache (moment_kind) one
+// wavefront per tile, where 9 rows take 113 us at 2048^2 and 16 take 123.
+//
+// Population step: one row per workgroup while that leaves a CU at most a dozen
+// wavefronts, else two: its halo rows come from the caches and rows in series
+// cost 2 us each.  256x32 5.0 us at 1 row, 35 at 16; 1024x64 7.2, 33; 700x500
+// 16.3 at 2 rows, 38; 1023x1024 42.3 at 2 rows, 55; 2048^2 253 at 2 rows, 302.
+void default_tile(const lbm_params& p, bool moments, bool solute, int* tx, int* sy) {
+  if (moments) {
+    const int strips = (p.nx + 59) / 60;
+    *tx = 64;
+    *sy = 1;
+    while (*sy < 8 && (long long)strips * ((p.ny + *sy - 1) / *sy) > 256) *sy += 1;
+    if (moment_kind((long long)p.nx * p.ny, solute, *sy) != KIND_MM_SHORT) *sy = 9;
+    return;
+  }
+  *tx = p.nx >= 1024 ? 256 : (p.nx >= 256 ? 128 : 64);
+  *sy = (long long)((p.nx + 61) / 62) * p.ny <= 3072 ? 1 : 2;
 }
 
 // Populations of the current state written over the stored moments (the
@@ -198,27 +221,16 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   a.P = s->L.P;
   a.nx = p.nx;
   a.ny = p.ny;
-  a.sy = s->sy;
-  a.nsegs = (p.ny + s->sy - 1) / s->sy;
   a.solute = s->L.solute;
   a.react = s->L.react;
-  a.omega = 1.0 / p.tau;
-  a.tau = p.tau;
-  a.G = p.G;
-  a.Gads1 = p.G_ads[0];
-  a.Gads2 = p.G_ads[1];
-  a.ax = p.accel[0];
-  a.ay = p.accel[1];
-  a.omega_g = s->L.solute ? 1.0 / p.tau_g : 0.0;
-  a.k_r = p.k_r;
-  a.threshold = p.threshold;
-  a.c_eq = p.c_eq;
-  a.c_hold = p.c_hold;
-  a.hold_x = p.hold_x;
-  a.q4 = p.solute_q == 4;
+  set_model(a, p, s->L.solute);
   for (long long t = 0; t < n; ++t) {
-    const int kind = !moments ? KIND_POP : (s->mom ? KIND_MM : KIND_PM);
-    a.tx_owned = kind == KIND_MM ? 60 : s->tx - 2;  // the moment step: 64-lane tiles
+    int tx = s->tx, sy = s->sy;
+    if (sy == 0) default_tile(p, moments && s->mom, s->L.solute, &tx, &sy);
+    const int kind = !moments ? KIND_POP : (s->mom ? moment_kind(s->L.N, s->L.solute, sy) : KIND_PM);
+    a.tx_owned = kind == KIND_POP || kind == KIND_PM ? tx - 2 : 60;  // the moment step: 64-lane tiles
+    a.sy = sy;
+    a.nsegs = (p.ny + sy - 1) / sy;
     a.nstrips = (p.nx + a.tx_owned - 1) / a.tx_owned;
     a.remap = (a.nstrips * a.nsegs) >= 8;
     a.fin = s->f(s->cur);
@@ -229,7 +241,7 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
     a.bit_p1 = pending_bit(s->step - 1);
     a.bit_p2 = pending_bit(s->step - 2);
     a.bit_cur = pending_bit(s->step);
-    hipError_t e = launch_step(a, s->tx, kind, s->nt, s->stream);
+    hipError_t e = launch_step(a, tx, kind, s->nt, s->stream);
     if (e != hipSuccess) {
       s->poisoned = true;
       return fail(LBM_EDEVICE, "step launch: %s", hipGetErrorString(e));
@@ -343,7 +355,7 @@ lbm_status lbm_init(const lbm_params* p, const uint8_t* solid, const double* rho
   s->ws = (char*)workspace;
   s->cur = 0;
   s->step = 0;
-  default_tile(*p, &s->tx, &s->sy);
+  s->tx = s->sy = 0;
   s->nt = 0;
   s->scheme = LBM_SCHEME_AUTO;
   s->mom = false;
@@ -592,8 +604,11 @@ lbm_status lbm_get_load_hint(const lbm_sim* s, int32_t* nontemporal) {
 
 lbm_status lbm_get_tile(const lbm_sim* s, int32_t* tx, int32_t* sy) {
   if (!s || !tx || !sy) return fail(LBM_EINVAL, "NULL argument");
-  *tx = use_moments(s->scheme, s->p) ? 64 : s->tx;  // moment step: 64-lane tiles
+  const bool moments = use_moments(s->scheme, s->p);
+  *tx = s->tx;
   *sy = s->sy;
+  if (s->sy == 0) default_tile(s->p, moments, s->L.solute, tx, sy);
+  if (moments) *tx = 64;  // 64-lane tiles
   return LBM_OK;
 }
 
@@ -734,14 +749,19 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
     return LBM_OK;
   };
   const int txs[] = {64, 128, 256};
-  const int sys[] = {6, 8, 9, 10, 12, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128};
+  const int sys[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128};
+  const bool moments = use_moments(s->scheme, s->p);
+  const bool short_tiles = moments && moment_kind(s->L.N, s->L.solute, SHORT_TILE) == KIND_MM_SHORT;
   std::vector<TuneCand> cands;
   for (int nt = 0; nt < 2 && st == LBM_OK; ++nt) {
     for (int tx : txs) {
-      if (use_moments(s->scheme, s->p) && tx != 64) continue;  // 64-lane tiles only
+      if (moments && tx != 64) continue;  // 64-lane tiles only
       if (tx > 2 * s->p.nx + 2 && tx != 64) continue;
       for (int sy : sys) {
         if (sy > 2 * s->p.ny && sy != 8) continue;
+        // a marching wavefront repeats four rows per tile; where short tiles
+        // run, tall ones are never faster
+        if (moments && (short_tiles ? sy > SHORT_TILE : sy < 6)) continue;
         TuneCand c{tx, sy, nt, 0.0f};
         if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
         cands.push_back(c);
@@ -797,6 +817,7 @@ struct lbm_batch {
   int tx, sy;
   int scheme;                 // LBM_SCHEME_*
   bool mom;                   // instance buffers hold moments of the last step
+  long long nodes;            // of all instances
   bool solute, react, poisoned;
   int graph_chunk;
   hipGraphExec_t graph;
@@ -901,20 +922,7 @@ StepArgs instance_args(const lbm_batch* b, int i, int parity) {
   a.remap = 0;
   a.solute = L.solute;
   a.react = L.react;
-  a.omega = 1.0 / p.tau;
-  a.tau = p.tau;
-  a.G = p.G;
-  a.Gads1 = p.G_ads[0];
-  a.Gads2 = p.G_ads[1];
-  a.ax = p.accel[0];
-  a.ay = p.accel[1];
-  a.omega_g = L.solute ? 1.0 / p.tau_g : 0.0;
-  a.k_r = p.k_r;
-  a.threshold = p.threshold;
-  a.c_eq = p.c_eq;
-  a.c_hold = p.c_hold;
-  a.hold_x = p.hold_x;
-  a.q4 = p.solute_q == 4;
+  set_model(a, p, L.solute);
   return a;
 }
 
@@ -978,8 +986,14 @@ lbm_status batch_reset(lbm_batch* b) {
   return LBM_OK;
 }
 
+long long batch_nodes(const lbm_batch* b) {
+  long long n = 0;
+  for (const Layout& L : b->L) n += L.N;
+  return n;
+}
+
 int batch_kind(const lbm_batch* b) {
-  return !batch_moments(b) ? KIND_POP : (b->mom ? KIND_MM : KIND_PM);
+  return !batch_moments(b) ? KIND_POP : (b->mom ? moment_kind(b->nodes, b->solute, b->sy) : KIND_PM);
 }
 
 // Queues nsteps batched steps on stream st (offsets 0..nsteps-1 from the
@@ -989,7 +1003,7 @@ lbm_status queue_batch(lbm_batch* b, int nsteps, hipStream_t st) {
   for (int t = 0; t < nsteps; ++t) {
     const int kind = batch_kind(b);
     hipError_t e = launch_step_batch(b->d_insts, b->d_tiles, b->ntiles, b->d_step, t, batch_tx(b),
-                                     b->solute, b->react, batch_variants(b), kind, st);
+                                     b->sy, b->solute, b->react, batch_variants(b), kind, st);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
     b->mom = kind != KIND_POP;
   }
@@ -1080,11 +1094,14 @@ lbm_status lbm_batch_init(int32_t n, const lbm_params* p, const uint8_t* const* 
   b->d_partial = (double*)(b->ws + B.partial);
   b->d_out = (double*)(b->ws + B.out);
   b->max_blocks = B.max_blocks;
-  b->tx = 128;
-  b->sy = 24;
   b->scheme = LBM_SCHEME_AUTO;
   b->mom = false;
   b->solute = solute;
+  b->nodes = batch_nodes(b);
+  // eight rows where the moment step's short tiles run (moment_kind), see
+  // default_tile
+  b->tx = 128;
+  b->sy = batch_moments(b) && moment_kind(b->nodes, solute, 8) == KIND_MM_SHORT ? 8 : 24;
   b->react = p[0].k_r > 0.0;
   b->graph = nullptr;
   b->graph_chunk = 0;

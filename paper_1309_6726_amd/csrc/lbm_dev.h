@@ -39,14 +39,38 @@ struct StepArgs {
   // model parameters in FP64 (kernel arguments stay in scalar registers)
   double omega;       // 1/tau
   double tau;
-  double G, Gads1, Gads2, ax, ay;
-  double omega_g;     // 1/tau_g
+  double mG36, mGads1, mGads2;       // -G/36, -G_ads/36 per component
+  double ax, ay;
+  double og_keep, og_w, og_wc;       // solute: 1 - 1/tau_g, w/tau_g, w c/tau_g (w: axis
+                                     // weight, c: 1 / sound speed^2)
   double k_r, threshold;
   double c_eq;        // saturation concentration of the reaction (0: plain first order)
   double c_hold;      // held concentration of the source region x < hold_x
   int hold_x;         // 0: no held source
   int q4;             // 1: D2Q4 solute lattice, 0: D2Q5
 };
+
+// The model parameters of p (solute: it has a solute lattice).
+inline void set_model(StepArgs& a, const lbm_params& p, bool solute) {
+  const bool q4 = p.solute_q == 4;
+  const double og = solute ? 1.0 / p.tau_g : 0.0, w = q4 ? 0.25 : 1.0 / 6.0;
+  a.omega = 1.0 / p.tau;
+  a.tau = p.tau;
+  a.mG36 = -p.G / 36.0;
+  a.mGads1 = -p.G_ads[0] / 36.0;
+  a.mGads2 = -p.G_ads[1] / 36.0;
+  a.ax = p.accel[0];
+  a.ay = p.accel[1];
+  a.og_keep = 1.0 - og;
+  a.og_w = og * w;
+  a.og_wc = og * w * (q4 ? 2.0 : 3.0);
+  a.k_r = p.k_r;
+  a.threshold = p.threshold;
+  a.c_eq = p.c_eq;
+  a.c_hold = p.c_hold;
+  a.hold_x = p.hold_x;
+  a.q4 = q4;
+}
 
 // Growth marks rotate over three pending bits: step n marks a node with
 // pending_bit(n); step n+1 books the populations it carried; step n+2 folds
@@ -62,7 +86,22 @@ __host__ __device__ inline unsigned pending_bit(long long n) {
 // component, so the state can be kept as six moments per node: PM collides
 // populations and stores moments, MM reads moments (rebuilding the incoming
 // populations by gathering from the neighbours) and stores moments.
-enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2 };
+enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
+
+// Which moment step runs tiles of sy rows when the lattices it advances
+// together hold `nodes` nodes.  Tiles of at most SHORT_TILE rows run with one
+// wavefront per row while the step's two buffers fit the 256 MB memory-side
+// cache, taller ones and larger lattices with one wavefront marching up the
+// tile.  Measured on square preforms, us per step (best height of each):
+// 1024^2 (92 MB) 24.8 against 33.3, 1448^2 (184 MB) 44.1 against 48.0,
+// 1600^2 (225 MB) 58.7 against 59.9, 1700^2 (254 MB) 77.0 against 71.9,
+// 2048^2 (369 MB) 114 against 99.5.  Once the reads come from HBM, the short
+// tiles' loads (one round trip per tile, two tiles per CU) are not covered.
+constexpr int SHORT_TILE = 12;
+constexpr long long SHORT_BYTES = 240ll << 20;
+inline int moment_kind(long long nodes, bool solute, int sy) {
+  return sy <= SHORT_TILE && nodes * (solute ? 88 : 48) <= SHORT_BYTES ? KIND_MM_SHORT : KIND_MM;
+}
 
 // Records a message for lbm_last_error() and returns s.
 lbm_status fail(lbm_status s, const char* fmt, ...);
@@ -73,7 +112,7 @@ hipError_t launch_step(const StepArgs& a, int tx, int kind, int nt, hipStream_t 
 // One batched step at index *stepc + j; a sequence of n such launches
 // (j = 0..n-1) is followed by launch_tick(stepc, n).
 hipError_t launch_step_batch(const StepArgs* insts, const int4* tiles, int ntiles,
-                             const long long* stepc, int j, int tx, int solute, int react,
+                             const long long* stepc, int j, int tx, int sy, int solute, int react,
                              int var, int kind, hipStream_t st);
 hipError_t launch_tick(long long* stepc, int n, hipStream_t st);
 hipError_t launch_front_batch(const StepArgs* insts, const int4* capi, const long long* stepc,

@@ -90,6 +90,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)extent, 0x00020000);
 }
 
+// One dword per lane at byte offset voff + soff, with the non-temporal hint
+// where NT and hint say so.
+template <bool NT>
+__device__ __forceinline__ unsigned load_b32(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff,
+                                             bool hint) {
+  return NT && hint ? (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, CPOL_NT)
+                    : (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0);
+}
+
 // Workgroup-wide LDS barrier that leaves outstanding global memory operations
 // in flight (only LDS traffic is ordered); a single-wave workgroup needs no
 // s_barrier at all.
@@ -97,29 +106,6 @@ __device__ __forceinline__ void lds_barrier(int TX) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   if (TX > 64) __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Shan-Chen interaction forces plus the body force at a fluid node (section
-// "LB models": cohesion between the two components and adhesion to the solid,
-// each a weight-normalised sum over the eight neighbours).  n1, n2: the
-// neighbours' densities (zero at solid nodes); sf: their solid flags (0/1);
-// index = link, 1..8 = E, N, W, S, NE, NW, SW, SE (index 0 unused).
-template <typename R>
-__device__ __forceinline__ void sc_forces(const StepArgs& a, const R* n1, const R* n2,
-                                          const float* sf, R rho1, R rho2, R& F1x, R& F1y,
-                                          R& F2x, R& F2y) {
-  const R WA = R(1) / R(9), WD = R(1) / R(36);
-  const R c2x = WA * (n2[1] - n2[3]) + WD * ((n2[5] - n2[6]) + (n2[8] - n2[7]));
-  const R c2y = WA * (n2[2] - n2[4]) + WD * ((n2[5] + n2[6]) - (n2[8] + n2[7]));
-  const R c1x = WA * (n1[1] - n1[3]) + WD * ((n1[5] - n1[6]) + (n1[8] - n1[7]));
-  const R c1y = WA * (n1[2] - n1[4]) + WD * ((n1[5] + n1[6]) - (n1[8] + n1[7]));
-  const R csx = WA * R(sf[1] - sf[3]) + WD * R((sf[5] - sf[6]) + (sf[8] - sf[7]));
-  const R csy = WA * R(sf[2] - sf[4]) + WD * R((sf[5] + sf[6]) - (sf[8] + sf[7]));
-  const R G = (R)a.G, Ga1 = (R)a.Gads1, Ga2 = (R)a.Gads2, ax = (R)a.ax, ay = (R)a.ay;
-  F1x = -G * rho1 * c2x - Ga1 * rho1 * csx + rho1 * ax;
-  F1y = -G * rho1 * c2y - Ga1 * rho1 * csy + rho1 * ay;
-  F2x = -G * rho2 * c1x - Ga2 * rho2 * csx + rho2 * ax;
-  F2y = -G * rho2 * c1y - Ga2 * rho2 * csy + rho2 * ay;
 }
 
 // 1/x from the hardware estimate refined by two Newton steps (a few ulp; the
@@ -138,21 +124,49 @@ __device__ __forceinline__ float recip(float x) {
   return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);
 }
 
+// Accelerations F_s / rho_s of the two components at a fluid node: Shan-Chen
+// cohesion and adhesion plus the body acceleration (section "LB models": each
+// a weight-normalised sum over the eight neighbours).  Both forces are
+// proportional to the node's own density, so the velocity shift tau F_s / rho_s
+// needs no division by it.  n1, n2: the neighbours' densities (zero at solid
+// nodes), index = link, 1..8 = E, N, W, S, NE, NW, SW, SE (index 0 unused);
+// (wx, wy): sum of the links to solid neighbours, axis links counted four
+// times (the weights are 4 : 1, and 1/36 is part of the constants).
+template <typename R>
+__device__ __forceinline__ void sc_accel(const StepArgs& a, const R* n1, const R* n2, R wx, R wy,
+                                         R& A1x, R& A1y, R& A2x, R& A2y) {
+  auto links = [](const R* n, R& x, R& y) {
+    const R p = n[5] - n[7], q = n[8] - n[6];
+    x = fmar(n[1] - n[3], R(4), p + q);
+    y = fmar(n[2] - n[4], R(4), p - q);
+  };
+  R c1x, c1y, c2x, c2y;
+  links(n1, c1x, c1y);
+  links(n2, c2x, c2y);
+  const R G = (R)a.mG36, Ga1 = (R)a.mGads1, Ga2 = (R)a.mGads2, ax = (R)a.ax, ay = (R)a.ay;
+  A1x = fmar(G, c2x, fmar(Ga1, wx, ax));
+  A1y = fmar(G, c2y, fmar(Ga1, wy, ay));
+  A2x = fmar(G, c1x, fmar(Ga2, wx, ax));
+  A2y = fmar(G, c1y, fmar(Ga2, wy, ay));
+}
+
 // Equilibrium velocities of the two components (common velocity shifted by
 // tau F_s / rho_s) and the physical velocity (j + F/2) / rho that advects the
-// solute.
+// solute; irt = 1 / (rho1 + rho2).
 template <typename R>
 __device__ __forceinline__ void sc_velocities(R tau, R rho1, R rho2, R j1x, R j1y, R j2x, R j2y,
-                                              R F1x, R F1y, R F2x, R F2y, R& v1x, R& v1y,
-                                              R& v2x, R& v2y, R& ux, R& uy) {
-  const R rt = rho1 + rho2;
-  const R irt = recip(rt);
-  const R upx = (j1x + j2x) * irt, upy = (j1y + j2y) * irt;
-  v1x = upx; v1y = upy; v2x = upx; v2y = upy;
-  if (rho1 > R(0)) { const R s = tau * recip(rho1); v1x += s * F1x; v1y += s * F1y; }
-  if (rho2 > R(0)) { const R s = tau * recip(rho2); v2x += s * F2x; v2y += s * F2y; }
-  ux = (j1x + j2x + R(0.5) * (F1x + F2x)) * irt;
-  uy = (j1y + j2y + R(0.5) * (F1y + F2y)) * irt;
+                                              R A1x, R A1y, R A2x, R A2y, R& v1x, R& v1y,
+                                              R& v2x, R& v2y, R& ux, R& uy, R& irt) {
+  irt = recip(rho1 + rho2);
+  const R jx = j1x + j2x, jy = j1y + j2y;
+  const R upx = jx * irt, upy = jy * irt;
+  const bool p1 = rho1 > R(0), p2 = rho2 > R(0);
+  v1x = p1 ? fmar(tau, A1x, upx) : upx;
+  v1y = p1 ? fmar(tau, A1y, upy) : upy;
+  v2x = p2 ? fmar(tau, A2x, upx) : upx;
+  v2y = p2 ? fmar(tau, A2y, upy) : upy;
+  ux = fmar(R(0.5), fmar(rho1, A1x, rho2 * A2x), jx) * irt;
+  uy = fmar(R(0.5), fmar(rho1, A1y, rho2 * A2y), jy) * irt;
 }
 
 // Solute collision (BGK on D2Q5, or on D2Q4 with weights 1/4 and no rest
@@ -161,7 +175,7 @@ __device__ __forceinline__ void sc_velocities(R tau, R rho1, R rho2, R j1x, R j1
 // saturation concentration c_eq > 0 only the excess C - c_eq precipitates),
 // the held source (post-collision solute of a node with x < hold_x set to the
 // equilibrium at c_hold), threshold test, and push of the solute populations
-// (bounce-back at solid axis neighbours).  sf: solid flags of the axis
+// (bounce-back at solid axis neighbours).  wall: solid flags of the axis
 // neighbours 1..4.
 // What solute_step leaves for memory every step: the five pushed populations
 // with their element offsets in gout, and the new precipitate of the node
@@ -182,28 +196,28 @@ __device__ __forceinline__ void store_solute(const StepArgs& a, const SoluteOut&
 }
 
 template <bool REACT, bool VAR, typename R>
-__device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R ux, R uy,
-                                            R rho1, R rho2, const float* sf, double m_cur,
-                                            unsigned P, unsigned idx, unsigned iE, unsigned iN,
-                                            unsigned iW, unsigned iS, int xc, int y, bool& ev,
-                                            int& evx, int& evy, SoluteOut& so) {
+__device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R ux, R uy, R rho1,
+                                            R irt, const bool* wall, double m_cur, unsigned P,
+                                            unsigned idx, unsigned iE, unsigned iN, unsigned iW,
+                                            unsigned iS, int xc, bool& ev, SoluteOut& so) {
   so.wm = false;
   so.m = 0.0;
   // VAR = false: the plain model (D2Q5, c_eq = 0, no held source)
   const bool q4 = VAR && a.q4 != 0;
-  const R WQ = q4 ? R(0.25) : R(1) / R(6), CQ = q4 ? R(2) : R(3);
   const R C = (((R)g[0] + (R)g[1]) + ((R)g[2] + (R)g[3])) + (R)g[4];
-  const R og = (R)a.omega_g;
+  // g* = (1 - og) g + og w C (1 + cs e.u), the constants products of the host
+  const R keep_g = (R)a.og_keep, gw = (R)a.og_w * C, gc = (R)a.og_wc * C;
+  const R gx = gc * ux, gy = gc * uy;
   R gs[5];
-  gs[1] = (R)g[1] + og * (WQ * C * (R(1) + CQ * ux) - (R)g[1]);
-  gs[2] = (R)g[2] + og * (WQ * C * (R(1) + CQ * uy) - (R)g[2]);
-  gs[3] = (R)g[3] + og * (WQ * C * (R(1) - CQ * ux) - (R)g[3]);
-  gs[4] = (R)g[4] + og * (WQ * C * (R(1) - CQ * uy) - (R)g[4]);
+  gs[1] = fmar(keep_g, (R)g[1], gw) + gx;
+  gs[2] = fmar(keep_g, (R)g[2], gw) + gy;
+  gs[3] = fmar(keep_g, (R)g[3], gw) - gx;
+  gs[4] = fmar(keep_g, (R)g[4], gw) - gy;
   gs[0] = q4 ? R(0) : C - ((gs[1] + gs[2]) + (gs[3] + gs[4]));
   if (REACT) {
-    const int ns = (int)sf[1] + (int)sf[2] + (int)sf[3] + (int)sf[4];
+    const int ns = (int)wall[1] + (int)wall[2] + (int)wall[3] + (int)wall[4];
     if (ns > 0) {
-      const double phi = (double)rho1 / ((double)rho1 + (double)rho2);
+      const double phi = (double)rho1 * (double)irt;
       const double rr = a.k_r * (double)ns * phi;
       double dm, keep;
       if (VAR && a.c_eq > 0.0) {
@@ -223,12 +237,11 @@ __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R
         a.mask[idx] = (uint8_t)a.bit_cur;
         a.sstep[idx] = (int32_t)(a.step + 1);
         ev = true;
-        evx = xc;
-        evy = y;
       }
     }
   }
   if (VAR && xc < a.hold_x) {
+    const R WQ = q4 ? R(0.25) : R(1) / R(6), CQ = q4 ? R(2) : R(3);
     const R Ch = (R)a.c_hold;
     gs[1] = WQ * Ch * (R(1) + CQ * ux);
     gs[2] = WQ * Ch * (R(1) + CQ * uy);
@@ -240,15 +253,15 @@ __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R
 #pragma unroll
   for (int q = 0; q < 5; ++q) so.g[q] = (float)gs[q];
   so.off[0] = idx;
-  so.off[1] = sf[1] != 0.0f ? 3 * P + idx : 1 * P + iE;
-  so.off[2] = sf[2] != 0.0f ? 4 * P + idx : 2 * P + iN;
-  so.off[3] = sf[3] != 0.0f ? 1 * P + idx : 3 * P + iW;
-  so.off[4] = sf[4] != 0.0f ? 2 * P + idx : 4 * P + iS;
+  so.off[1] = wall[1] ? 3 * P + idx : 1 * P + iE;
+  so.off[2] = wall[2] ? 4 * P + idx : 2 * P + iN;
+  so.off[3] = wall[3] ? 1 * P + idx : 3 * P + iW;
+  so.off[4] = wall[4] ? 2 * P + idx : 4 * P + iS;
 }
 
 // One lane per wavefront reserves event-log slots for every lane that marked
 // a node in this row, with a single atomic.
-__device__ __forceinline__ void log_events(const StepArgs& a, bool ev, int evx, int evy) {
+__device__ __forceinline__ void log_events(const StepArgs& a, bool ev, int x, int y) {
   const int lane = __lane_id();
   const unsigned long long bal = __ballot(ev);
   if (bal) {
@@ -262,8 +275,8 @@ __device__ __forceinline__ void log_events(const StepArgs& a, bool ev, int evx, 
           (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
       const unsigned long long e = base + below;
       if ((long long)e < a.ev_cap) {
-        a.ev[e].x = evx;
-        a.ev[e].y = evy;
+        a.ev[e].x = x;
+        a.ev[e].y = y;
         a.ev[e].step = a.step + 1;
       }
     }
@@ -403,9 +416,8 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, int strip, int seg,
 
     // ---- collide and push row y = r - 1 -----------------------------------
     bool ev = false;
-    int evx = 0, evy = 0;
+    const int y = ys + k - 2;
     if (k >= 2 && owner) {
-      const int y = ys + k - 2;
       const int yd = y == 0 ? ny - 1 : y - 1;
       const int yu = y == ny - 1 ? 0 : y + 1;
       const unsigned idx = (unsigned)y * (unsigned)nx + (unsigned)xc;
@@ -435,15 +447,17 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, int strip, int seg,
           n2[i] = s_r2[no[i]];
           sf[i] = s_s[no[i]];
         }
-        R F1x, F1y, F2x, F2y;
-        sc_forces<R>(a, n1, n2, sf, rho1, rho2, F1x, F1y, F2x, F2y);
+        const R wx = (R)(4.0f * (sf[1] - sf[3]) + ((sf[5] - sf[7]) + (sf[8] - sf[6])));
+        const R wy = (R)(4.0f * (sf[2] - sf[4]) + ((sf[5] - sf[7]) - (sf[8] - sf[6])));
+        R A1x, A1y, A2x, A2y;
+        sc_accel<R>(a, n1, n2, wx, wy, A1x, A1y, A2x, A2y);
         const R j1x = ((R)f[1] - (R)f[3]) + ((R)f[5] - (R)f[6]) + ((R)f[8] - (R)f[7]);
         const R j1y = ((R)f[2] - (R)f[4]) + ((R)f[5] + (R)f[6]) - ((R)f[7] + (R)f[8]);
         const R j2x = ((R)f[10] - (R)f[12]) + ((R)f[14] - (R)f[15]) + ((R)f[17] - (R)f[16]);
         const R j2y = ((R)f[11] - (R)f[13]) + ((R)f[14] + (R)f[15]) - ((R)f[16] + (R)f[17]);
-        R v1x, v1y, v2x, v2y, ux, uy;
-        sc_velocities<R>((R)a.tau, rho1, rho2, j1x, j1y, j2x, j2y, F1x, F1y, F2x, F2y, v1x, v1y,
-                         v2x, v2y, ux, uy);
+        R v1x, v1y, v2x, v2y, ux, uy, irt;
+        sc_velocities<R>((R)a.tau, rho1, rho2, j1x, j1y, j2x, j2y, A1x, A1y, A2x, A2y, v1x, v1y,
+                         v2x, v2y, ux, uy, irt);
 
         // target offsets of the four axis neighbours (and the diagonals)
         const unsigned iE = (unsigned)y * nx + xr, iW = (unsigned)y * nx + xl;
@@ -493,13 +507,14 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, int strip, int seg,
         }
         if (SOLUTE) {
           SoluteOut so;
-          solute_step<REACT, VAR, R>(a, g, ux, uy, rho1, rho2, sf, m_cur, P, idx, iE, iN, iW, iS, xc, y,
-                                ev, evx, evy, so);
+          const bool wall[5] = {false, sf[1] != 0.0f, sf[2] != 0.0f, sf[3] != 0.0f, sf[4] != 0.0f};
+          solute_step<REACT, VAR, R>(a, g, ux, uy, rho1, irt, wall, m_cur, P, idx, iE, iN, iW, iS, xc, ev,
+                                     so);
           store_solute<REACT>(a, so, idx);
         }
       }
     }
-    if (REACT) log_events(a, ev, evx, evy);
+    if (REACT) log_events(a, ev, xc, y);
     // rotate: row k becomes the row to collide next iteration
 #pragma unroll
     for (int q = 0; q < 18; ++q) f[q] = fn[q];
@@ -534,17 +549,193 @@ __device__ __forceinline__ double from_right(double v) {
   return __hiloint2double(from_right_i(__double2hiint(v)), from_right_i(__double2loint(v)));
 }
 
-// Mask bytes of a lane and of its two neighbours packed as own | left << 8 |
-// right << 16.
-__device__ __forceinline__ unsigned pack_row_mask(unsigned m) {
-  return m | ((unsigned)from_left_i((int)m) << 8) | ((unsigned)from_right_i((int)m) << 16);
+// Solid nodes of a row as lane masks: bit t is lane t.  A neighbour row's or
+// column's solidity is then a scalar shift of a mask, and a 0/1 value per lane
+// one select (on_lane).
+typedef unsigned long long lanes_t;
+__device__ __forceinline__ bool on_lane(lanes_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// The eight neighbours of every lane's node from the masks of the row below,
+// the row itself and the row above; index = link, E, N, W, S, NE, NW, SW, SE.
+struct Neighbours {
+  lanes_t n[9];
+  __device__ __forceinline__ Neighbours(lanes_t dn, lanes_t own, lanes_t up)
+      : n{0, own >> 1, up, own << 1, dn, up >> 1, up << 1, dn << 1, dn >> 1} {}
+  __device__ __forceinline__ lanes_t any() const {
+    return ((n[1] | n[2]) | (n[3] | n[4])) | ((n[5] | n[6]) | (n[7] | n[8]));
+  }
+};
+
+// Which links of every lane's node lead to a solid node, as factors 0 and 1;
+// any: some link of some fluid lane does (a node solid itself sends nothing).
+template <typename R>
+struct Bounce {
+  bool any;  // the same for all lanes
+  R s[9];
+  __device__ __forceinline__ Bounce(const Neighbours& solid, lanes_t row)
+      : any((solid.any() & ~row) != 0) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) s[i] = R(0);
+    if (any) {
+#pragma unroll
+      for (int i = 1; i < 9; ++i) s[i] = on_lane(solid.n[i]) ? R(1) : R(0);
+    }
+  }
+};
+
+// One component's outgoing equilibria of every lane's node from its stored
+// moments (zero moments: nothing goes out), handed to `to`: to.up(o2, o5, o6)
+// gets the links into the row above, to.down(o4, o7, o8) those into the row
+// below, and to.own(r, x, y) what adds to the accumulators (rho, jx, jy) of the
+// row itself: the rest and horizontal links, streamed along the row by DPP
+// wave shifts, and what bounces back.  Called with every lane active.
+// With u3 = 3 v: w rho (1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v^2)
+//              = w rho (cc + e3 (1 + e3 / 2)), e3 = e . u3, cc = 1 - u3^2 / 6.
+template <typename R, typename To>
+__device__ __forceinline__ void stream_row(float rho_s, float vx, float vy, const Bounce<R>& bounce,
+                                           To&& to) {
+  const R WA = R(1) / R(9), WD = R(1) / R(36), WR = R(4) / R(9);
+  const R rho = (R)rho_s;
+  const R ux = R(3) * (R)vx, uy = R(3) * (R)vy;
+  const R cc = fmar(ux * ux + uy * uy, R(-1) / R(6), R(1));
+  const R ra = WA * rho, rd = WD * rho;
+  auto out = [&](R r, R e3) { return r * fmar(e3, fmar(e3, R(0.5), R(1)), cc); };
+  const R o0 = WR * rho * cc;
+  const R o1 = out(ra, ux), o2 = out(ra, uy), o3 = out(ra, -ux), o4 = out(ra, -uy);
+  const R o5 = out(rd, ux + uy), o6 = out(rd, uy - ux), o7 = out(rd, -ux - uy),
+          o8 = out(rd, ux - uy);
+  to.up(o2, o5, o6);
+  to.down(o4, o7, o8);
+  // rest and horizontal links (1, 3)
+  const R a1 = from_left(o1), a3 = from_right(o3);
+  R r = (o0 + a1) + a3, x = a1 - a3, y = R(0);
+  // a value streaming into a solid node bounces back into the sender's
+  // opposite link: rho += o_i, j -= e_i o_i
+  if (bounce.any) {
+    const R* s = bounce.s;
+    r = fmar(s[1], o1, r); r = fmar(s[2], o2, r);
+    r = fmar(s[3], o3, r); r = fmar(s[4], o4, r);
+    r = fmar(s[5], o5, r); r = fmar(s[6], o6, r);
+    r = fmar(s[7], o7, r); r = fmar(s[8], o8, r);
+    x = fmar(s[3], o3, x); x = fmar(-s[1], o1, x);
+    x = fmar(-s[5], o5, x); x = fmar(s[6], o6, x);
+    x = fmar(s[7], o7, x); x = fmar(-s[8], o8, x);
+    y = s[4] * o4; y = fmar(-s[2], o2, y);
+    y = fmar(-s[5], o5, y); y = fmar(-s[6], o6, y);
+    y = fmar(s[7], o7, y); y = fmar(s[8], o8, y);
+  }
+  to.own(r, x, y);
 }
 
-// Equilibrium of a link from the stored moments of its node: wr = w rho,
-// c = 1 - 3/2 |v|^2, eu = e . v  ->  w rho (1 + 3 eu + 9/2 eu^2 - 3/2 |v|^2).
+// stream_row into the accumulators of the rows above (started by it), own and
+// below (completed by it).
 template <typename R>
-__device__ __forceinline__ R feq_m(R wr, R c, R eu) {
-  return wr * (c + eu * (R(3) + R(4.5) * eu));
+struct RowSums {
+  R *above, *row, *below;
+  __device__ __forceinline__ void up(R o2, R o5, R o6) const {
+    const R a5 = from_left(o5), a6 = from_right(o6);
+    above[0] = above[2] = (o2 + a5) + a6;
+    above[1] = a5 - a6;
+  }
+  __device__ __forceinline__ void own(R r, R x, R y) const {
+    row[0] += r;
+    row[1] += x;
+    row[2] += y;
+  }
+  __device__ __forceinline__ void down(R o4, R o7, R o8) const {
+    const R a7 = from_right(o7), a8 = from_left(o8);
+    const R v = (o4 + a7) + a8;
+    below[0] += v;
+    below[1] += a8 - a7;
+    below[2] -= v;
+  }
+};
+
+// Where a collided row goes: buffer descriptors of the outgoing moments, the
+// outgoing solute and the precipitate, and the byte stride of a plane.
+struct MomentOut {
+  __amdgpu_buffer_rsrc_t m, g, prec;
+  unsigned PB;
+};
+
+// Collision of the node (xc, y) of a complete row in the moment scheme: forces
+// from the density window (rows W0 above, W1 own, W2 below, each centre, left
+// and right of both components, zero at solids), new moments, solute,
+// reaction and growth, and all stores.  rC: the node's (rho, jx, jy) per
+// component; own: its mask byte; solid: its neighbours solid in state n; gv:
+// its solute populations; prec(): its precipitate.
+template <bool SOLUTE, bool REACT, bool VAR, typename R, typename Prec>
+__device__ __forceinline__ void collide_moments(const StepArgs& a, const MomentOut& o, const R* rC,
+                                                const R* W0, const R* W1, const R* W2,
+                                                unsigned own, const Neighbours& solid,
+                                                unsigned SCUR, const float* gv, Prec&& prec, int xc,
+                                                int xl, int xr, int y, unsigned idx, bool& ev) {
+  const int nx = a.nx, ny = a.ny;
+  const unsigned P = (unsigned)a.P;
+  // outgoing moments; zero at a node solid in state n, which no reader of
+  // the next state takes as fluid.  Every owned lane stores, so each plane
+  // is written as whole rows rather than lines with holes at solids.
+  float mo[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  if (own & SCUR) {
+    if (REACT) {
+      if (own & a.bit_p1) {
+        // turned solid at the end of the previous step: book what it carried
+        a.drop[idx] = (float)rC[0];
+        a.drop[P + idx] = (float)rC[3];
+        a.drop[2 * P + idx] =
+            SOLUTE ? (float)((((R)gv[0] + (R)gv[1]) + ((R)gv[2] + (R)gv[3])) + (R)gv[4]) : 0.0f;
+      } else if (own & a.bit_p2) {
+        a.mask[idx] = 1;  // booked one step ago: fold the mark into bit0
+      }
+    }
+  } else {
+    // neighbours x + e_i, link order 1..8 = E, N, W, S, NE, NW, SW, SE
+    const R n1[9] = {R(0), W1[4], W0[0], W1[2], W2[0], W0[4], W0[2], W2[2], W2[4]};
+    const R n2[9] = {R(0), W1[5], W0[1], W1[3], W2[1], W0[5], W0[3], W2[3], W2[5]};
+    R wx = R(0), wy = R(0);
+    if (solid.any()) {  // the same for all lanes
+      auto w = [&](int i, int v) { return on_lane(solid.n[i]) ? v : 0; };
+      const int p = w(5, 1) - w(7, 1), q = w(8, 1) - w(6, 1);
+      wx = (R)((w(1, 4) - w(3, 4)) + (p + q));
+      wy = (R)((w(2, 4) - w(4, 4)) + (p - q));
+    }
+    R A1x, A1y, A2x, A2y;
+    sc_accel<R>(a, n1, n2, wx, wy, A1x, A1y, A2x, A2y);
+    R v1x, v1y, v2x, v2y, ux, uy, irt;
+    // tau = 1 in the moment scheme
+    sc_velocities<R>(R(1), rC[0], rC[3], rC[1], rC[2], rC[4], rC[5], A1x, A1y, A2x, A2y, v1x, v1y,
+                     v2x, v2y, ux, uy, irt);
+    mo[0] = (float)rC[0];
+    mo[1] = (float)v1x;
+    mo[2] = (float)v1y;
+    mo[3] = (float)rC[3];
+    mo[4] = (float)v2x;
+    mo[5] = (float)v2y;
+    if (SOLUTE) {
+      const int yd = y == 0 ? ny - 1 : y - 1;
+      const int yu = y == ny - 1 ? 0 : y + 1;
+      const unsigned iE = (unsigned)y * nx + xr, iW = (unsigned)y * nx + xl;
+      const unsigned iN = (unsigned)yu * nx + xc, iS = (unsigned)yd * nx + xc;
+      const double mC = REACT ? prec() : 0.0;
+      SoluteOut so;
+      const bool wall[5] = {false, on_lane(solid.n[1]), on_lane(solid.n[2]), on_lane(solid.n[3]),
+                            on_lane(solid.n[4])};
+      solute_step<REACT, VAR, R>(a, gv, ux, uy, rC[0], irt, wall, mC, P, idx, iE, iN, iW, iS, xc, ev,
+                                 so);
+#pragma unroll
+      for (int q = 0; q < 5; ++q)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(so.g[q]), o.g,
+                                              (int)(4u * so.off[q]), 0, 0);
+      if (REACT && so.wm) {
+        const v2u mb = {(unsigned)__double2loint(so.m), (unsigned)__double2hiint(so.m)};
+        __builtin_amdgcn_raw_buffer_store_b64(mb, o.prec, (int)(8u * idx), 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mo[q]), o.m, (int)(4u * idx),
+                                          (int)((unsigned)q * o.PB), 0);
 }
 
 // Moment step (tau = 1), one wavefront per workgroup: lane t holds column
@@ -594,7 +785,6 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
   const int nrows = ye - ys + 4;
   const unsigned SPREV = 1u | a.bit_p2;    // solid in state n-1
   const unsigned SCUR = SPREV | a.bit_p1;  // solid in state n
-  const R WA = R(1) / R(9), WD = R(1) / R(36), WR = R(4) / R(9);
   // Buffer descriptors: one per array, plane q at scalar offset q * P * 4
   // bytes, so an access costs one 32-bit lane offset per row instead of a
   // 64-bit address per plane.  The extent covers every plane the kernel
@@ -602,11 +792,10 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
   // and a lane beyond it reads 0 and drops its store.
   const unsigned PB = P * 4u;
   const auto rMin = make_rsrc(a.fin, 6u * PB);
-  const auto rMout = make_rsrc(a.fout, 6u * PB);
   const auto rGin = make_rsrc(a.gin, SOLUTE ? 5u * PB : 0u);
-  const auto rGout = make_rsrc(a.gout, SOLUTE ? 5u * PB : 0u);
   const auto rMask = make_rsrc(a.mask, P);
   const auto rPrec = make_rsrc(a.m, REACT ? 2u * PB : 0u);
+  const MomentOut o{make_rsrc(a.fout, 6u * PB), make_rsrc(a.gout, SOLUTE ? 5u * PB : 0u), rPrec, PB};
 
   auto row_y = [&](int k) {
     int yr = ys - 2 + k;
@@ -614,7 +803,6 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
     if (yr >= ny) yr -= ny;
     return yr;
   };
-  auto sol = [](unsigned pk, int sh, unsigned bits) { return ((pk >> sh) & bits) != 0u; };
   auto mask_at = [&](int k) -> unsigned {
     return (active && k < nrows)
                ? (unsigned)__builtin_amdgcn_raw_buffer_load_b8(
@@ -641,10 +829,9 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
   // writes 0 to its slot without touching memory, and the reader needs no
   // select.
   constexpr unsigned NONE = 0xFFFFFFF0u;
-  auto prefetch = [&](int buf, int k, unsigned own_k, unsigned pkm3, unsigned pkm2,
-                      unsigned pkm1) {
+  auto prefetch = [&](int buf, int k, unsigned m_k, unsigned mm3, unsigned mm2, unsigned mm1) {
     if (k >= nrows) return;
-    const bool got_m = active && !(own_k & SPREV);
+    const bool got_m = active && !(m_k & SPREV);
     const unsigned vm = got_m ? 4u * ((unsigned)row_y(k) * (unsigned)nx + (unsigned)xc) : NONE;
     if (NT && k >= 2 && k < nrows - 2) {
 #pragma unroll
@@ -654,9 +841,8 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
       for (int q = 0; q < 6; ++q) to_lds(rMin, vm, (unsigned)q * PB, buf, q);
     }
     if (SOLUTE && k >= 4) {
-      const unsigned ownC = pkm2 & 0xFFu;
       const unsigned i = (unsigned)(ys + k - 4) * (unsigned)nx + (unsigned)xc;
-      const bool got_g = owner && !(ownC & SPREV);
+      const bool got_g = owner && !(mm2 & SPREV);
       const unsigned vg = got_g ? 4u * i : NONE;
 #pragma unroll
       for (int q = 0; q < 5; ++q) {
@@ -664,9 +850,9 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
         else to_lds(rGin, vg, (unsigned)q * PB, buf, 6 + q);
       }
       if (REACT) {
-        const bool got_p =
-            owner && !(ownC & SCUR) &&
-            (sol(pkm2, 16, SCUR) || sol(pkm1, 0, SCUR) || sol(pkm2, 8, SCUR) || sol(pkm3, 0, SCUR));
+        const lanes_t row = __ballot(mm2 & SCUR);
+        const lanes_t wall = (row >> 1) | (row << 1) | __ballot(mm1 & SCUR) | __ballot(mm3 & SCUR);
+        const bool got_p = owner && on_lane(wall & ~row);
         const unsigned vp = got_p ? 8u * i : NONE;
         to_lds(rPrec, vp, 0u, buf, 11);
         to_lds(rPrec, vp, 4u, buf, 12);
@@ -674,12 +860,11 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
     }
   };
 
-  // packed masks of rows k-3 .. k+1 (rows outside the tile read as solid)
-  const unsigned SOLID3 = 0x010101u;
-  unsigned pk_m3 = SOLID3, pk_m2 = SOLID3, pk_m1 = SOLID3;
-  unsigned pk_0 = pack_row_mask(mask_at(0));
-  unsigned m_ahead = mask_at(1);  // raw mask of row k+1 (then k+2)
-  prefetch(0, 0, pk_0 & 0xFFu, pk_m3, pk_m2, pk_m1);
+  // mask bytes of rows k-3 .. k+1 (rows outside the tile read as solid)
+  unsigned m_m3 = 1, m_m2 = 1, m_m1 = 1;
+  unsigned m_0 = mask_at(0);
+  unsigned m_ahead = mask_at(1);  // of row k+1 (then k+2)
+  prefetch(0, 0, m_0, m_m3, m_m2, m_m1);
 
   R acc0[6], acc1[6];  // (rho1, j1x, j1y, rho2, j2x, j2y) of rows k and k-1
 #pragma unroll
@@ -696,87 +881,35 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
     const int buf = k & 1;
     // everything requested during the previous iteration has arrived
     __builtin_amdgcn_s_waitcnt(VMCNT0);
-    const unsigned pk_p1 = pack_row_mask(m_ahead);
+    const unsigned m_p1 = m_ahead;
     // buffer buf holds row k's moments and row k-2's solute and precipitate
     // (0 where nothing was copied)
     auto take = [&](int slot) { return pf[buf][slot][t]; };
-    const unsigned own0 = pk_0 & 0xFFu;
     // requests for the next iteration: row k+1's moments, row k-1's solute,
     // the mask of row k+2
-    prefetch(buf ^ 1, k + 1, pk_p1 & 0xFFu, pk_m2, pk_m1, pk_0);
+    prefetch(buf ^ 1, k + 1, m_p1, m_m2, m_m1, m_0);
     m_ahead = mask_at(k + 2);
 
     const bool crow = k >= 4 && owner;
     const int yC = ys + k - 4;
     const unsigned idxC = (unsigned)(crow ? yC : 0) * (unsigned)nx + (unsigned)xc;
-    const unsigned ownC = pk_m2 & 0xFFu;
 
-    // links of this node whose target is solid in state n-1 (bit i = link i)
-    const unsigned bb =
-        (sol(pk_0, 16, SPREV) ? 0x02u : 0u) | (sol(pk_p1, 0, SPREV) ? 0x04u : 0u) |
-        (sol(pk_0, 8, SPREV) ? 0x08u : 0u) | (sol(pk_m1, 0, SPREV) ? 0x10u : 0u) |
-        (sol(pk_p1, 16, SPREV) ? 0x20u : 0u) | (sol(pk_p1, 8, SPREV) ? 0x40u : 0u) |
-        (sol(pk_m1, 8, SPREV) ? 0x80u : 0u) | (sol(pk_m1, 16, SPREV) ? 0x100u : 0u);
-    const bool bounce = bb != 0u && !(own0 & SPREV);
+    // neighbours solid in state n-1, from which values bounce back
+    const lanes_t row0 = __ballot(m_0 & SPREV);
+    const Neighbours prev(__ballot(m_m1 & SPREV), row0, __ballot(m_p1 & SPREV));
+    const Bounce<R> bounce(prev, row0);
 
     // ---- sources of row k: outgoing equilibria, streamed -----------------
     R accN[6];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      // with u3 = 3 v: w rho (1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v^2)
-      //              = w rho (cc + e3 (1 + e3 / 2)), e3 = e . u3, cc = 1 - u3^2 / 6
-      const R rho = (R)take(3 * c);
-      const R ux = R(3) * (R)take(3 * c + 1), uy = R(3) * (R)take(3 * c + 2);
-      const R cc = fmar(ux * ux + uy * uy, R(-1) / R(6), R(1));
-      const R ra = WA * rho, rd = WD * rho;
-      auto out = [&](R r, R e3) { return r * fmar(e3, fmar(e3, R(0.5), R(1)), cc); };
-      const R o0 = WR * rho * cc;
-      const R o1 = out(ra, ux), o2 = out(ra, uy), o3 = out(ra, -ux), o4 = out(ra, -uy);
-      const R o5 = out(rd, ux + uy), o6 = out(rd, uy - ux), o7 = out(rd, -ux - uy),
-              o8 = out(rd, ux - uy);
-      // up links (2, 5, 6) start the accumulator of row k+1
-      const R a5 = from_left(o5), a6 = from_right(o6);
-      const R up = (o2 + a5) + a6;
-      accN[3 * c] = up;
-      accN[3 * c + 1] = a5 - a6;
-      accN[3 * c + 2] = up;
-      // rest and horizontal links (1, 3) into row k
-      const R a1 = from_left(o1), a3 = from_right(o3);
-      acc0[3 * c] += (o0 + a1) + a3;
-      acc0[3 * c + 1] += a1 - a3;
-      // down links (4, 7, 8) complete row k-1
-      const R a7 = from_right(o7), a8 = from_left(o8);
-      const R dn = (o4 + a7) + a8;
-      acc1[3 * c] += dn;
-      acc1[3 * c + 1] += a8 - a7;
-      acc1[3 * c + 2] -= dn;
-      // values streaming into a node solid in state n-1 bounce back into the
-      // sender's opposite link: rho += o_i, j -= e_i o_i
-      if (bounce) {
-        const R s1 = (R)((bb >> 1) & 1u), s2 = (R)((bb >> 2) & 1u), s3 = (R)((bb >> 3) & 1u),
-                s4 = (R)((bb >> 4) & 1u), s5 = (R)((bb >> 5) & 1u), s6 = (R)((bb >> 6) & 1u),
-                s7 = (R)((bb >> 7) & 1u), s8 = (R)((bb >> 8) & 1u);
-        R br = s1 * o1, bx = s3 * o3, by = s4 * o4;
-        br = fmar(s2, o2, br); br = fmar(s3, o3, br);
-        br = fmar(s4, o4, br); br = fmar(s5, o5, br);
-        br = fmar(s6, o6, br); br = fmar(s7, o7, br);
-        br = fmar(s8, o8, br);
-        bx = fmar(-s1, o1, bx); bx = fmar(-s5, o5, bx);
-        bx = fmar(s6, o6, bx); bx = fmar(s7, o7, bx);
-        bx = fmar(-s8, o8, bx);
-        by = fmar(-s2, o2, by); by = fmar(-s5, o5, by);
-        by = fmar(-s6, o6, by); by = fmar(s7, o7, by);
-        by = fmar(s8, o8, by);
-        acc0[3 * c] += br;
-        acc0[3 * c + 1] += bx;
-        acc0[3 * c + 2] += by;
-      }
-    }
+    for (int c = 0; c < 2; ++c)
+      stream_row<R>(take(3 * c), take(3 * c + 1), take(3 * c + 2), bounce,
+                    RowSums<R>{accN + 3 * c, acc0 + 3 * c, acc1 + 3 * c});
 
     // ---- row k-1 complete: density window --------------------------------
     R W0[6];
     {
-      const bool s1 = sol(pk_m1, 0, SCUR);
+      const bool s1 = (m_m1 & SCUR) != 0u;
       const R d1 = s1 ? R(0) : acc1[0], d2 = s1 ? R(0) : acc1[3];
       W0[0] = d1; W0[1] = d2;
       W0[2] = from_left(d1); W0[3] = from_left(d2);
@@ -785,79 +918,18 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
 
     // ---- collide row k-2 ---------------------------------------------------
     bool ev = false;
-    int evx = 0, evy = 0;
+    const Neighbours cur(__ballot(m_m3 & SCUR), __ballot(m_m2 & SCUR), __ballot(m_m1 & SCUR));
     if (crow) {
-      const int y = yC;
-      const unsigned idx = idxC;
       float gv[5];
 #pragma unroll
       for (int q = 0; q < 5; ++q) gv[q] = take(6 + q);
-      // outgoing moments; zero at a node solid in state n, which no reader of
-      // the next state takes as fluid.  Every owned lane stores, so each plane
-      // is written as whole rows rather than lines with holes at solids.
-      float mo[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-      if (ownC & SCUR) {
-        if (REACT) {
-          if (ownC & a.bit_p1) {
-            // turned solid at the end of the previous step: book what it carried
-            a.drop[idx] = (float)rC[0];
-            a.drop[P + idx] = (float)rC[3];
-            a.drop[2 * P + idx] =
-                SOLUTE ? (float)((((R)gv[0] + (R)gv[1]) + ((R)gv[2] + (R)gv[3])) + (R)gv[4]) : 0.0f;
-          } else if (ownC & a.bit_p2) {
-            a.mask[idx] = 1;  // booked one step ago: fold the mark into bit0
-          }
-        }
-      } else {
-        // neighbours x + e_i, link order 1..8 = E, N, W, S, NE, NW, SW, SE
-        R n1[9], n2[9];
-        float sf[9];
-        n1[1] = W1[4]; n2[1] = W1[5]; sf[1] = sol(pk_m2, 16, SCUR) ? 1.0f : 0.0f;
-        n1[2] = W0[0]; n2[2] = W0[1]; sf[2] = sol(pk_m1, 0, SCUR) ? 1.0f : 0.0f;
-        n1[3] = W1[2]; n2[3] = W1[3]; sf[3] = sol(pk_m2, 8, SCUR) ? 1.0f : 0.0f;
-        n1[4] = W2[0]; n2[4] = W2[1]; sf[4] = sol(pk_m3, 0, SCUR) ? 1.0f : 0.0f;
-        n1[5] = W0[4]; n2[5] = W0[5]; sf[5] = sol(pk_m1, 16, SCUR) ? 1.0f : 0.0f;
-        n1[6] = W0[2]; n2[6] = W0[3]; sf[6] = sol(pk_m1, 8, SCUR) ? 1.0f : 0.0f;
-        n1[7] = W2[2]; n2[7] = W2[3]; sf[7] = sol(pk_m3, 8, SCUR) ? 1.0f : 0.0f;
-        n1[8] = W2[4]; n2[8] = W2[5]; sf[8] = sol(pk_m3, 16, SCUR) ? 1.0f : 0.0f;
-        R F1x, F1y, F2x, F2y;
-        sc_forces<R>(a, n1, n2, sf, rC[0], rC[3], F1x, F1y, F2x, F2y);
-        R v1x, v1y, v2x, v2y, ux, uy;
-        sc_velocities<R>((R)a.tau, rC[0], rC[3], rC[1], rC[2], rC[4], rC[5], F1x, F1y, F2x, F2y,
-                         v1x, v1y, v2x, v2y, ux, uy);
-        mo[0] = (float)rC[0];
-        mo[1] = (float)v1x;
-        mo[2] = (float)v1y;
-        mo[3] = (float)rC[3];
-        mo[4] = (float)v2x;
-        mo[5] = (float)v2y;
-        if (SOLUTE) {
-          const int yd = y == 0 ? ny - 1 : y - 1;
-          const int yu = y == ny - 1 ? 0 : y + 1;
-          const unsigned iE = (unsigned)y * nx + xr, iW = (unsigned)y * nx + xl;
-          const unsigned iN = (unsigned)yu * nx + xc, iS = (unsigned)yd * nx + xc;
-          const double mC =
-              REACT ? __hiloint2double(__float_as_int(pf[buf][12][t]), __float_as_int(pf[buf][11][t]))
-                    : 0.0;
-          SoluteOut so;
-          solute_step<REACT, VAR, R>(a, gv, ux, uy, rC[0], rC[3], sf, mC, P, idx, iE, iN, iW, iS, xc,
-                                y, ev, evx, evy, so);
-#pragma unroll
-          for (int q = 0; q < 5; ++q)
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(so.g[q]), rGout,
-                                                  (int)(4u * so.off[q]), 0, 0);
-          if (REACT && so.wm) {
-            const v2u mb = {(unsigned)__double2loint(so.m), (unsigned)__double2hiint(so.m)};
-            __builtin_amdgcn_raw_buffer_store_b64(mb, rPrec, (int)(8u * idx), 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 6; ++q)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mo[q]), rMout, (int)(4u * idx),
-                                              (int)((unsigned)q * PB), 0);
+      auto prec = [&]() {
+        return __hiloint2double(__float_as_int(pf[buf][12][t]), __float_as_int(pf[buf][11][t]));
+      };
+      collide_moments<SOLUTE, REACT, VAR, R>(a, o, rC, W0, W1, W2, m_m2, cur, SCUR, gv, prec, xc, xl, xr,
+                                             yC, idxC, ev);
     }
-    if (REACT) log_events(a, ev, evx, evy);
+    if (REACT) log_events(a, ev, xc, yC);
 
     // ---- rotate ------------------------------------------------------------
 #pragma unroll
@@ -868,13 +940,187 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
       W2[q] = W1[q];
       W1[q] = W0[q];
     }
-    pk_m3 = pk_m2;
-    pk_m2 = pk_m1;
-    pk_m1 = pk_0;
-    pk_0 = pk_p1;
+    m_m3 = m_m2;
+    m_m2 = m_m1;
+    m_m1 = m_0;
+    m_0 = m_p1;
   }
   // drain: no request may still be writing this wavefront's LDS at exit
   __builtin_amdgcn_s_waitcnt(VMCNT0);
+}
+
+// Short tiles of the moment step: one wavefront per row.  A tile of sy owned
+// rows takes sy + 4 wavefronts; wavefront k holds row ys - 2 + k.  All loads of
+// the tile are issued at once, every wavefront streams its row's equilibria
+// (vertical and diagonal links through LDS), completes its row, publishes its
+// densities in LDS and collides it.  The additions to a node happen in the
+// order of mom_wave (from below, own row, from above), so the results are
+// bit-identical to it.
+//
+// What bounds it: on a small lattice latency.  A few hundred rows of 64 nodes
+// leave most SIMDs idle, and there mom_wave's sy + 4 row iterations in series
+// (1.1-1.9 us each) are the step; here a step is one memory round trip, two
+// LDS exchanges and one row's arithmetic (256x32 without solute: 3.65 us a
+// step against 6.2 for mom_wave's best height).  On one that fills the chip
+// arithmetic: it does (sy + 4) / sy times the streaming work, 571 vector
+// instructions per owned row of 60 nodes at eight rows, as mom_wave's 533, but
+// with 24 wavefronts per CU resident (64 VGPRs, 74 KB LDS) instead of 12:
+// 1024^2 preform 24.8 us against 33.3.  Eight rows because two workgroups of
+// 12 wavefronts share a CU's LDS; nine to twelve leave one.
+constexpr int ROWS_SY = SHORT_TILE;        // most owned rows
+constexpr int ROWS_WAVES = ROWS_SY + 4;
+
+// stream_row with the vertical links into LDS rows of LROW values (lane t at
+// t + 1, so a diagonal link is read from the neighbouring column), the rest
+// kept.
+constexpr int LROW = 66;
+template <typename R>
+struct RowShares {
+  R *s_up, *s_dn;  // [3][LROW]
+  bool has_up, has_dn;
+  R r, x, y;
+  __device__ __forceinline__ void up(R o2, R o5, R o6) {
+    if (has_up) { s_up[0] = o2; s_up[LROW] = o5; s_up[2 * LROW] = o6; }
+  }
+  __device__ __forceinline__ void own(R r_, R x_, R y_) { r = r_; x = x_; y = y_; }
+  __device__ __forceinline__ void down(R o4, R o7, R o8) {
+    if (has_dn) { s_dn[0] = o4; s_dn[LROW] = o7; s_dn[2 * LROW] = o8; }
+  }
+};
+
+template <bool SOLUTE, bool REACT, bool VAR, typename R, bool NT>
+__device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, char* lds_raw) {
+  // links of both components out of rows 0 .. nrows-3 (up) and 2 .. nrows-1
+  // (down), densities of rows 1 .. nrows-2
+  const int nin = a.sy + 2;
+  R(*s_up)[2][3 * LROW] = (R(*)[2][3 * LROW])lds_raw;
+  R(*s_dn)[2][3 * LROW] = s_up + nin;
+  R(*s_rho)[2][LROW] = (R(*)[2][LROW])(s_dn + nin);
+  const int t = threadIdx.x & 63;
+  const int k = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nx = a.nx, ny = a.ny;
+  const unsigned PB = (unsigned)a.P * 4u;
+  const int x0 = strip * a.tx_owned;
+  const int nown = min(a.tx_owned, nx - x0);
+  const bool active = t <= nown + 3;
+  const bool owner = t >= 2 && t <= nown + 1;
+  int xc = x0 - 2 + t;
+  if (xc < 0) xc += nx;
+  if (xc >= nx) xc -= nx;
+  const int xl = xc == 0 ? nx - 1 : xc - 1;
+  const int xr = xc == nx - 1 ? 0 : xc + 1;
+  const int ys = seg * a.sy;
+  const int nrows = min(a.sy, ny - ys) + 4;
+  const bool live = k < nrows;                     // the last tile may be shorter
+  const bool inner = k >= 1 && k < nrows - 1;      // rows whose sums are complete
+  const bool crow = k >= 2 && k < nrows - 2;       // owned rows
+  int y = ys - 2 + k;
+  if (y < 0) y += ny;
+  if (y >= ny) y -= ny;
+  const unsigned SPREV = 1u | a.bit_p2;    // solid in state n-1
+  const unsigned SCUR = SPREV | a.bit_p1;  // solid in state n
+  constexpr unsigned NONE = 0xFFFFFFF0u;   // past every extent: reads 0
+  const auto rMin = make_rsrc(a.fin, 6u * PB);
+  const auto rGin = make_rsrc(a.gin, SOLUTE ? 5u * PB : 0u);
+  const auto rMask = make_rsrc(a.mask, (unsigned)a.P);
+  const auto rPrec = make_rsrc(a.m, REACT ? 2u * PB : 0u);
+  const MomentOut o{make_rsrc(a.fout, 6u * PB), make_rsrc(a.gout, SOLUTE ? 5u * PB : 0u), rPrec, PB};
+
+  const unsigned idx = (unsigned)y * (unsigned)nx + (unsigned)xc;
+  float mo[6], gv[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  unsigned m0 = 1, md = 1, mu = 1;
+  v2u pr = {0u, 0u};
+  RowShares<R> sh[2];
+  if (live) {
+    const unsigned yd = y == 0 ? ny - 1 : y - 1, yu = y == ny - 1 ? 0 : y + 1;
+    auto mask_of = [&](unsigned row) -> unsigned {
+      const unsigned v = (unsigned)__builtin_amdgcn_raw_buffer_load_b8(
+          rMask, (int)(active ? row * (unsigned)nx + (unsigned)xc : NONE), 0, 0);
+      return active ? v : 1u;
+    };
+    m0 = mask_of((unsigned)y);
+    md = mask_of(yd);
+    mu = mask_of(yu);
+    auto load_moments = [&](unsigned vm) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+        mo[q] = __uint_as_float(load_b32<NT>(rMin, vm, (unsigned)q * PB, crow));
+    };
+    if (!NT) load_moments(active ? 4u * idx : NONE);
+    const lanes_t row = __ballot(m0 & SPREV);
+    const Neighbours prev(__ballot(md & SPREV), row, __ballot(mu & SPREV));
+    const bool fluid = on_lane(~row);
+    if (NT) load_moments(fluid ? 4u * idx : NONE);
+    if (crow) {
+      if (SOLUTE) {
+        const unsigned vg = owner && fluid ? 4u * idx : NONE;
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+          gv[q] = __uint_as_float(load_b32<NT>(rGin, vg, (unsigned)q * PB, true));
+      }
+      if (REACT) {
+        const lanes_t here = __ballot(m0 & SCUR);
+        const lanes_t wall = (here >> 1) | (here << 1) | __ballot(md & SCUR) | __ballot(mu & SCUR);
+        pr = __builtin_amdgcn_raw_buffer_load_b64(
+            rPrec, (int)(owner && on_lane(wall & ~here) ? 8u * idx : NONE), 0, 0);
+      }
+    }
+    const Bounce<R> bounce(prev, row);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) mo[q] = fluid ? mo[q] : 0.0f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      sh[c].has_up = k < nrows - 2;
+      sh[c].has_dn = k >= 2;
+      sh[c].s_up = &s_up[k < nrows - 2 ? k : 0][c][t + 1];
+      sh[c].s_dn = &s_dn[k >= 2 ? k - 2 : 0][c][t + 1];
+      stream_row<R>(mo[3 * c], mo[3 * c + 1], mo[3 * c + 2], bounce, sh[c]);
+    }
+  }
+  lds_barrier(64 * ROWS_WAVES);
+
+  R acc[6], W1[6];
+  if (inner) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const R* su = &s_up[k - 1][c][t + 1];
+      const R* sd = &s_dn[k - 1][c][t + 1];
+      const R a5 = su[LROW - 1], a6 = su[2 * LROW + 1];
+      const R u = (su[0] + a5) + a6;
+      acc[3 * c] = u + sh[c].r;
+      acc[3 * c + 1] = (a5 - a6) + sh[c].x;
+      acc[3 * c + 2] = u + sh[c].y;
+      const R a7 = sd[LROW + 1], a8 = sd[2 * LROW - 1];
+      const R d = (sd[0] + a7) + a8;
+      acc[3 * c] += d;
+      acc[3 * c + 1] += a8 - a7;
+      acc[3 * c + 2] -= d;
+    }
+    const bool s1 = (m0 & SCUR) != 0u;
+    W1[0] = s1 ? R(0) : acc[0];
+    W1[1] = s1 ? R(0) : acc[3];
+    s_rho[k - 1][0][t + 1] = W1[0];
+    s_rho[k - 1][1][t + 1] = W1[1];
+  }
+  lds_barrier(64 * ROWS_WAVES);
+
+  if (!crow) return;
+  bool ev = false;
+  const Neighbours cur(__ballot(md & SCUR), __ballot(m0 & SCUR), __ballot(mu & SCUR));
+  if (owner) {
+    R W0[6], W2[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const int at = t + (q < 2 ? 1 : q < 4 ? 0 : 2);
+      if (q >= 2) W1[q] = s_rho[k - 1][q & 1][at];
+      W0[q] = s_rho[k][q & 1][at];
+      W2[q] = s_rho[k - 2][q & 1][at];
+    }
+    auto prec = [&]() { return __hiloint2double((int)pr.y, (int)pr.x); };
+    collide_moments<SOLUTE, REACT, VAR, R>(a, o, acc, W0, W1, W2, m0, cur, SCUR, gv, prec, xc, xl, xr, y,
+                                           idx, ev);
+  }
+  if (REACT) log_events(a, ev, xc, y);
 }
 
 // XCD-aware order: the hardware hands block b to XCD b mod 8, so XCD x
@@ -892,12 +1138,20 @@ template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT>
 __device__ __forceinline__ void run_tile(const StepArgs& a, int strip, int seg, char* lds_raw) {
   if (KIND == KIND_MM)
     mom_wave<SOLUTE, REACT, VAR, R, NT>(a, strip, seg);
+  else if (KIND == KIND_MM_SHORT)
+    mom_rows<SOLUTE, REACT, VAR, R, NT>(a, strip, seg, lds_raw);
   else
     step_tile<SOLUTE, REACT, VAR, R, KIND == KIND_PM, NT>(a, strip, seg, lds_raw);
 }
 
+// Largest workgroup and register budget (waves per SIMD) of each kind.
+template <int KIND>
+constexpr int max_threads() { return KIND == KIND_MM_SHORT ? 64 * ROWS_WAVES : 256; }
+template <int KIND>
+constexpr int min_waves() { return KIND == KIND_MM_SHORT ? 6 : 3; }
+
 template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
+__global__ void __launch_bounds__(max_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(min_waves<KIND>(), 8)))
 k_step(const StepArgs a) {
   extern __shared__ char lds_raw[];
   const int T = a.nstrips * a.nsegs;
@@ -914,7 +1168,7 @@ k_step(const StepArgs a) {
 // 0..n-1) is followed by k_tick(stepc, n), so a captured sequence replays
 // from where the last one ended.
 template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
+__global__ void __launch_bounds__(max_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(min_waves<KIND>(), 8)))
 k_step_batch(const StepArgs* __restrict__ insts, const int4* __restrict__ tiles,
              const long long* __restrict__ stepc, int j) {
   extern __shared__ char lds_raw[];
@@ -1335,8 +1589,16 @@ __global__ void k_unpack(MomSrc src, float* __restrict__ fout) {
 
 // ---- launchers ------------------------------------------------------------
 size_t step_lds_bytes(int kind, int tx) {
-  if (kind == KIND_MM) return 0;  // registers and cross-lane moves only
+  if (kind == KIND_MM) return 0;  // static
+  if (kind == KIND_MM_SHORT)      // see mom_rows
+    return (size_t)(tx / 64 - 2) * (2 * 6 + 2) * LROW * sizeof(double);
   return (size_t)4 * tx * (2 * sizeof(double) + sizeof(float));
+}
+
+// Threads per workgroup: one wavefront per tile in the moment step, one per
+// row in its short tiles.
+int step_threads(int kind, int tx, int sy) {
+  return kind == KIND_MM ? 64 : kind == KIND_MM_SHORT ? 64 * (sy + 4) : tx;
 }
 
 // Runs that use a reaction or solute-lattice variant (saturation, held
@@ -1362,9 +1624,12 @@ void launch_step_t(const StepArgs& a, int T, int tx, size_t lds, hipStream_t st)
 // steps (the one-off PM step ignores it).  The arithmetic is FP64 throughout.
 hipError_t launch_step(const StepArgs& a, int tx, int kind, int nt, hipStream_t st) {
   const int T = a.nstrips * a.nsegs;
-  if (kind == KIND_MM) tx = 64;  // the moment step runs one wavefront per tile
+  tx = step_threads(kind, tx, a.sy);
   const size_t lds = step_lds_bytes(kind, tx);
-  if (kind == KIND_MM) {
+  if (kind == KIND_MM_SHORT) {
+    if (nt) launch_step_t<double, KIND_MM_SHORT, true>(a, T, tx, lds, st);
+    else launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st);
+  } else if (kind == KIND_MM) {
     if (nt) launch_step_t<double, KIND_MM, true>(a, T, tx, lds, st);
     else launch_step_t<double, KIND_MM, false>(a, T, tx, lds, st);
   } else if (kind == KIND_PM) {
@@ -1392,11 +1657,12 @@ void launch_batch_t(const StepArgs* insts, const int4* tiles, int ntiles, const 
 }
 
 hipError_t launch_step_batch(const StepArgs* insts, const int4* tiles, int ntiles,
-                             const long long* stepc, int j, int tx, int solute, int react,
+                             const long long* stepc, int j, int tx, int sy, int solute, int react,
                              int var, int kind, hipStream_t st) {
-  if (kind == KIND_MM) tx = 64;
+  tx = step_threads(kind, tx, sy);
   const size_t lds = step_lds_bytes(kind, tx);
-  if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
+  if (kind == KIND_MM_SHORT) launch_batch_t<double, KIND_MM_SHORT>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
+  else if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
   else if (kind == KIND_PM) launch_batch_t<double, KIND_PM>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
   else launch_batch_t<double, KIND_POP>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
   return hipGetLastError();
