@@ -394,15 +394,15 @@ lbm_status lbm_observe(lbm_sim* s, lbm_obs* o) {
   hipError_t e = launch_observe(s->f(s->cur), s->g(s->cur), s->mask(), s->m(), s->drop(),
                                 s->sstep(), p.nx, p.ny, s->L.P, pending_bit(s->step - 1),
                                 pending_bit(s->step - 2), s->mom, s->L.solute, s->L.react,
-                                s->L.nblocks, s->partial(), s->out(), p.x_in, p.x_out, p.y0, p.W,
-                                s->stream);
+                                s->L.nblocks, s->partial(), s->out(), s->evc(), p.x_in, p.x_out, p.y0,
+                                p.W, s->stream);
   if (e != hipSuccess) { s->poisoned = true; return fail(LBM_EDEVICE, "observe launch: %s", hipGetErrorString(e)); }
   double h[OBS_OUT];
-  unsigned long long nev = 0;
   e = hipMemcpyAsync(h, s->out(), sizeof h, hipMemcpyDeviceToHost, s->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&nev, s->evc(), sizeof nev, hipMemcpyDeviceToHost, s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) { s->poisoned = true; return fail(LBM_EDEVICE, "observe: %s", hipGetErrorString(e)); }
+  unsigned long long nev;
+  memcpy(&nev, &h[OBS_OUT - 1], sizeof nev);
   memset(o, 0, sizeof *o);
   o->step = s->step;
   o->mass[0] = h[0];
@@ -432,20 +432,16 @@ lbm_status lbm_fields(lbm_sim* s, uint32_t mask, double* host) {
   if (mask >> 7) return fail(LBM_EINVAL, "unknown field bits");
   const lbm_params& p = s->p;
   const long long N = s->L.N;
-  // staging: the idle population buffer (72 B per node >= 7 doubles per node);
+  // staging: the idle population buffer (72 B per node, nine planes of doubles);
   // the next step overwrites every fluid slot of it before reading it
   double* stage = (double*)s->f(s->cur ^ 1);
   hipError_t e = launch_fields(s->f(s->cur), s->g(s->cur), s->mask(), s->m(), p.nx, p.ny, s->L.P,
                                pending_bit(s->step - 1), pending_bit(s->step - 2), s->mom,
                                s->L.solute, s->L.react, p.G, p.G_ads[0], p.G_ads[1],
-                               p.accel[0], p.accel[1], stage, s->stream);
-  int k = 0;
-  for (int b = 0; b < 7 && e == hipSuccess; ++b) {
-    if (!(mask & (1u << b))) continue;
-    e = hipMemcpyAsync(host + (size_t)k * N, stage + (size_t)b * N, N * sizeof(double),
+                               p.accel[0], p.accel[1], mask, stage, s->stream);
+  if (e == hipSuccess && mask)
+    e = hipMemcpyAsync(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double),
                        hipMemcpyDeviceToHost, s->stream);
-    ++k;
-  }
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) { s->poisoned = true; return fail(LBM_EDEVICE, "fields: %s", hipGetErrorString(e)); }
   return LBM_OK;
@@ -1218,14 +1214,14 @@ lbm_status lbm_batch_observe(lbm_batch* b, int32_t i, lbm_obs* o) {
   const int nblocks = (int)std::min<long long>(b->max_blocks, (L.N + 255) / 256);
   hipError_t e = launch_observe(a.fin, a.gin, a.mask, a.m, a.drop, a.sstep, p.nx, p.ny, L.P,
                                 pending_bit(b->step - 1), pending_bit(b->step - 2), b->mom,
-                                L.solute, L.react, nblocks, b->d_partial, b->d_out, p.x_in, p.x_out,
-                                p.y0, p.W, b->stream);
+                                L.solute, L.react, nblocks, b->d_partial, b->d_out, a.ev_count, p.x_in,
+                                p.x_out, p.y0, p.W, b->stream);
   double h[OBS_OUT];
-  unsigned long long nev = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(h, b->d_out, sizeof h, hipMemcpyDeviceToHost, b->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&nev, a.ev_count, sizeof nev, hipMemcpyDeviceToHost, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) { b->poisoned = true; return fail(LBM_EDEVICE, "batch observe: %s", hipGetErrorString(e)); }
+  unsigned long long nev;
+  memcpy(&nev, &h[OBS_OUT - 1], sizeof nev);
   memset(o, 0, sizeof *o);
   o->step = b->step;
   o->mass[0] = h[0];
@@ -1257,14 +1253,10 @@ lbm_status lbm_batch_fields(lbm_batch* b, int32_t i, uint32_t mask, double* host
   hipError_t e = launch_fields(a.fin, a.gin, a.mask, a.m, p.nx, p.ny, b->L[i].P,
                                pending_bit(b->step - 1), pending_bit(b->step - 2), b->mom,
                                b->L[i].solute, b->L[i].react, p.G, p.G_ads[0], p.G_ads[1],
-                               p.accel[0], p.accel[1], stage, b->stream);
-  int k = 0;
-  for (int bit = 0; bit < 7 && e == hipSuccess; ++bit) {
-    if (!(mask & (1u << bit))) continue;
-    e = hipMemcpyAsync(host + (size_t)k * N, stage + (size_t)bit * N, N * sizeof(double),
+                               p.accel[0], p.accel[1], mask, stage, b->stream);
+  if (e == hipSuccess && mask)
+    e = hipMemcpyAsync(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double),
                        hipMemcpyDeviceToHost, b->stream);
-    ++k;
-  }
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) { b->poisoned = true; return fail(LBM_EDEVICE, "batch fields: %s", hipGetErrorString(e)); }
   return LBM_OK;

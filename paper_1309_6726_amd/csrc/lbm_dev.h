@@ -10,7 +10,8 @@
 namespace lbmdev {
 
 constexpr int OBS_SLOTS = 9;   // per-block partial sums of the observe reduction
-constexpr int OBS_OUT = OBS_SLOTS + 6;  // + capillary: z, delta_e, closure, area, min width, steps
+constexpr int OBS_OUT = OBS_SLOTS + 7;  // + capillary: z, delta_e, closure, area, min width, steps;
+                                        // last: the event count (bits of an int64)
 
 struct StepArgs {
   const float* fin;
@@ -129,12 +130,13 @@ hipError_t launch_init(const double* r1, const double* r2, const double* c, cons
 // last step (mom = 1); p1, p2 are pending(n-1), pending(n-2).
 hipError_t launch_observe(const float* f, const float* g, const uint8_t* mask, const double* m,
                           const float* drop, const int32_t* sstep, int nx, int ny, long long P,
-                          unsigned p1, unsigned p2, int mom, int solute, int react, int nblocks,
-                          double* partial, double* out, int x_in, int x_out, int y0, int W,
-                          hipStream_t st);
+                          unsigned p1, unsigned p2, int mom, int solute, int react, int max_blocks,
+                          double* partial, double* out, const unsigned long long* ev_count, int x_in,
+                          int x_out, int y0, int W, hipStream_t st);
+// The selected fields (bits of sel) one after another; out holds nine planes.
 hipError_t launch_fields(const float* f, const float* g, const uint8_t* mask, const double* m,
                          int nx, int ny, long long P, unsigned p1, unsigned p2, int mom,
                          int solute, int react, double G, double Gads1, double Gads2, double ax,
-                         double ay, double* out, hipStream_t st);
+                         double ay, unsigned sel, double* out, hipStream_t st);
 
 }  // namespace lbmdev

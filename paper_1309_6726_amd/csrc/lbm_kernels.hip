@@ -1292,24 +1292,30 @@ struct MomSrc {
   }
 };
 
-// Observe, pass 1: per-block FP64 partial sums.  Slots:
-// 0 mass1, 1 mass2, 2 solute, 3 precipitate, 4 removed1, 5 removed2,
-// 6 removed solute, 7 solid count, 8 non-finite count.
+constexpr int OBS_THREADS = 512;
+
+// Sum over a wavefront, in a fixed order; the result is in lane 0.
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+  return v;
+}
+
+// One block's FP64 partial sums over its nodes.  Slots: 0 mass1, 1 mass2,
+// 2 solute, 3 precipitate, 4 removed1, 5 removed2, 6 removed solute, 7 solid
+// count, 8 non-finite count.
 template <typename Src>
-__global__ void __launch_bounds__(256) k_obs_partial(Src src, const float* __restrict__ g,
-                                                     const uint8_t* __restrict__ mask,
-                                                     const double* __restrict__ m,
-                                                     const float* __restrict__ drop, int nx,
-                                                     long long N, long long P, unsigned p1,
-                                                     unsigned p2, int solute, int react,
-                                                     double* __restrict__ partial) {
-  __shared__ double red[OBS_SLOTS][256];
+__device__ void partial_sums(const Src& src, const float* __restrict__ g,
+                             const uint8_t* __restrict__ mask, const double* __restrict__ m,
+                             const float* __restrict__ drop, int nx, long long N, long long P,
+                             unsigned p1, unsigned p2, int solute, int react, int block,
+                             int nblocks, double* __restrict__ partial) {
+  __shared__ double red[OBS_SLOTS][OBS_THREADS / 64];
   const unsigned sprev = 1u | p2, scur = sprev | p1;
   double acc[OBS_SLOTS];
 #pragma unroll
   for (int j = 0; j < OBS_SLOTS; ++j) acc[j] = 0.0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N;
-       i += (long long)gridDim.x * blockDim.x) {
+  for (long long i = block * (long long)OBS_THREADS + threadIdx.x; i < N;
+       i += (long long)nblocks * OBS_THREADS) {
     const unsigned b = mask[i];
     double s1 = 0, s2 = 0, sc = 0;
     if (!(b & sprev)) {
@@ -1340,214 +1346,267 @@ __global__ void __launch_bounds__(256) k_obs_partial(Src src, const float* __res
     }
   }
 #pragma unroll
-  for (int j = 0; j < OBS_SLOTS; ++j) red[j][threadIdx.x] = acc[j];
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-#pragma unroll
-      for (int j = 0; j < OBS_SLOTS; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + s];
-    }
-    __syncthreads();
+  for (int j = 0; j < OBS_SLOTS; ++j) {
+    const double v = wave_sum(acc[j]);
+    if ((threadIdx.x & 63) == 0) red[j][threadIdx.x >> 6] = v;
   }
-  if (threadIdx.x < OBS_SLOTS) partial[blockIdx.x * OBS_SLOTS + threadIdx.x] = red[threadIdx.x][0];
+  __syncthreads();
+  if (threadIdx.x < OBS_SLOTS) {
+    double v = 0.0;
+    for (int w = 0; w < OBS_THREADS / 64; ++w) v += red[threadIdx.x][w];
+    partial[block * OBS_SLOTS + threadIdx.x] = v;
+  }
 }
 
-// Observe, pass 2: fixed-order sum of the partials (deterministic).
-__global__ void k_obs_final(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
-  const int j = threadIdx.x;
-  if (j >= OBS_SLOTS) return;
-  double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partial[b * OBS_SLOTS + j];
-  out[j] = s;
-}
-
-// Capillary observables computed by one workgroup of 256 threads: centreline
-// front, largest grown width, first closure, and the sums behind the radii of
-// Fig. 4.  out: [0] z, [1] delta_e, [2] closure step (-1 if none), [3] open
-// area A (fluid nodes between the walls), [4] narrowest open column, [5] sum
-// over neighbouring columns of |h(x+1) - h(x)|, h the growth on the lower
-// wall.  sb: solid bits of state n.
-template <typename Src>
+// Capillary observables computed by one workgroup of OBS_THREADS threads, one
+// column per thread and pass: the centreline front and, with FULL, largest
+// grown width, first closure, and the sums behind the radii of Fig. 4.  out:
+// [0] z, [1] delta_e, [2] closure step (-1 if none), [3] open area A (fluid
+// nodes between the walls), [4] narrowest open column, [5] sum over
+// neighbouring columns of |h(x+1) - h(x)|, h the growth on the lower wall.
+// sb: solid bits of state n.
+//
+// What bounds it: round trips to memory.  Each column's wetting fraction is
+// formed once and its neighbour's taken from LDS, and a column's mask bytes
+// are read in one pass with independent loads; the front alone stops at the
+// pass that holds it.  A 1024-column capillary took 51 us with 256 threads
+// that evaluated every column twice and followed each wall by dependent loads
+// (the fronts of 34 runs 105 us), and takes 15 us with the sums beside it (9.3 us).
+template <bool FULL, typename Src>
 __device__ void capillary_obs(const Src& src, const uint8_t* __restrict__ mask,
                               const int32_t* __restrict__ sstep, int nx, unsigned sb, int x_in,
                               int x_out, int y0, int W, int react, double* __restrict__ out) {
-  __shared__ int s_min[256];
-  __shared__ double s_de[256];
-  __shared__ long long s_cl[256];
-  __shared__ int s_area[256], s_wmin[256], s_steps[256];
+  constexpr int T = OBS_THREADS;
+  __shared__ double s_phi[T];
+  __shared__ int s_blocked[T], s_db[T];
+  __shared__ int s_x[T], s_area[T], s_wmin[T], s_steps[T];
+  __shared__ double s_z[T], s_de[T];
+  __shared__ long long s_cl[T];
+  const int t = threadIdx.x;
   const int nr = (W % 2 == 0) ? 2 : 1;
   const int row0 = (W % 2 == 0) ? (y0 + W / 2 - 1) : (y0 + (W - 1) / 2);
-  int best = x_out;  // first x where the scan stops
+  int best = x_out;  // this thread's first x where the scan stops, and z there
+  double z = (double)(x_out - x_in);
   double de = 0.0;
   long long cl = -1;
   int area = 0, wmin = W, steps = 0;
-  for (int x = x_in + threadIdx.x; x < x_out; x += blockDim.x) {
-    // front predicate at x
-    bool blocked = false, nblocked = false;
-    double phi = 0, phin = 0;
-    for (int r = 0; r < nr; ++r) {
-      const long long i = (long long)(row0 + r) * nx + x;
-      if (mask[i] & sb) blocked = true;
-      else { double a, b; src.rho(i, x, row0 + r, a, b); phi += a / (a + b); }
-    }
-    phi /= nr;
-    if (x + 1 < x_out) {
-      for (int r = 0; r < nr; ++r) {
-        const long long i = (long long)(row0 + r) * nx + x + 1;
-        if (mask[i] & sb) nblocked = true;
-        else { double a, b; src.rho(i, x + 1, row0 + r, a, b); phin += a / (a + b); }
-      }
-      phin /= nr;
-    }
-    const bool stop = blocked || (x == x_in && phi < 0.5) ||
-                      (x + 1 < x_out && !nblocked && phi >= 0.5 && phin < 0.5);
-    if (stop && x < best) best = x;
-    // growth from the two walls in this column
-    int db = 0, dt = 0;
-    while (db < W && (mask[(long long)(y0 + db) * nx + x] & sb)) ++db;
-    while (dt < W && (mask[(long long)(y0 + W - 1 - dt) * nx + x] & sb)) ++dt;
-    int w = 0;
-    for (int y = y0; y < y0 + W; ++y) w += (mask[(long long)y * nx + x] & sb) ? 0 : 1;
-    area += w;
-    wmin = min(wmin, w);
-    if (x + 1 < x_out) {
-      int dn = 0;
-      while (dn < W && (mask[(long long)(y0 + dn) * nx + x + 1] & sb)) ++dn;
-      steps += abs(dn - db);
-    }
-    double col;
-    if (db >= W) {
-      col = 0.5 * W;
-      long long last = 0;
-      if (react)
-        for (int y = y0; y < y0 + W; ++y) {
-          const long long st = sstep[(long long)y * nx + x];
-          if (st > last) last = st;
-        }
-      if (cl < 0 || last < cl) cl = last;
-    } else {
-      col = (double)(db > dt ? db : dt);
-    }
-    if (col > de) de = col;
-  }
-  s_min[threadIdx.x] = best;
-  s_de[threadIdx.x] = de;
-  s_cl[threadIdx.x] = cl;
-  s_area[threadIdx.x] = area;
-  s_wmin[threadIdx.x] = wmin;
-  s_steps[threadIdx.x] = steps;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      s_area[threadIdx.x] += s_area[threadIdx.x + s];
-      s_wmin[threadIdx.x] = min(s_wmin[threadIdx.x], s_wmin[threadIdx.x + s]);
-      s_steps[threadIdx.x] += s_steps[threadIdx.x + s];
-      s_min[threadIdx.x] = min(s_min[threadIdx.x], s_min[threadIdx.x + s]);
-      s_de[threadIdx.x] = fmax(s_de[threadIdx.x], s_de[threadIdx.x + s]);
-      const long long o = s_cl[threadIdx.x + s];
-      if (o >= 0 && (s_cl[threadIdx.x] < 0 || o < s_cl[threadIdx.x])) s_cl[threadIdx.x] = o;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const int x = s_min[0];
-    double z = (double)(x_out - x_in);
+  // each pass decides T - 1 columns; the last thread's is the next one's neighbour
+  for (int xb = x_in; xb < x_out; xb += T - 1) {
+    const int x = xb + t;
+    bool blocked = false;
+    double phi = 0;
+    int db = 0, dt = 0, w = 0;
     if (x < x_out) {
-      bool blocked = false;
-      double phi = 0, phin = 0;
       for (int r = 0; r < nr; ++r) {
         const long long i = (long long)(row0 + r) * nx + x;
         if (mask[i] & sb) blocked = true;
         else { double a, b; src.rho(i, x, row0 + r, a, b); phi += a / (a + b); }
       }
       phi /= nr;
-      if (blocked) z = (double)(x - x_in);
-      else if (x == x_in && phi < 0.5) z = 0.0;
-      else {
-        for (int r = 0; r < nr; ++r) {
-          const long long i = (long long)(row0 + r) * nx + x + 1;
-          double a, b; src.rho(i, x + 1, row0 + r, a, b); phin += a / (a + b);
+      if (FULL) {  // growth from the two walls and fluid nodes of this column
+        int lo = W, hi = -1;  // lowest and highest fluid node
+#pragma unroll 8
+        for (int y = 0; y < W; ++y) {
+          const bool fluid = !(mask[(long long)(y0 + y) * nx + x] & sb);
+          w += fluid ? 1 : 0;
+          lo = fluid && lo == W ? y : lo;
+          hi = fluid ? y : hi;
         }
-        phin /= nr;
-        z = (double)x + (phi - 0.5) / (phi - phin) - x_in;
+        db = lo;
+        dt = hi < 0 ? W : W - 1 - hi;
       }
     }
-    out[0] = z;
-    out[1] = s_de[0];
-    out[2] = (double)s_cl[0];
-    out[3] = (double)s_area[0];
-    out[4] = (double)s_wmin[0];
-    out[5] = (double)s_steps[0];
+    s_phi[t] = phi;
+    s_blocked[t] = blocked;
+    if (FULL) s_db[t] = db;
+    __syncthreads();
+    const bool next = x + 1 < x_out;
+    if (x < x_out && (t < T - 1 || !next)) {
+      const double phin = next ? s_phi[t + 1] : 0.0;
+      const bool crossing = next && !s_blocked[t + 1] && phi >= 0.5 && phin < 0.5;
+      const bool dry = x == x_in && phi < 0.5;
+      if ((blocked || dry || crossing) && x < best) {
+        best = x;
+        z = blocked ? (double)(x - x_in) : dry ? 0.0 : (double)x + (phi - 0.5) / (phi - phin) - x_in;
+      }
+      if (FULL) {
+        area += w;
+        wmin = min(wmin, w);
+        if (next) steps += abs(s_db[t + 1] - db);
+        double col;
+        if (db >= W) {
+          col = 0.5 * W;
+          long long last = 0;
+          if (react)
+            for (int y = y0; y < y0 + W; ++y) {
+              const long long st = sstep[(long long)y * nx + x];
+              if (st > last) last = st;
+            }
+          if (cl < 0 || last < cl) cl = last;
+        } else {
+          col = (double)(db > dt ? db : dt);
+        }
+        if (col > de) de = col;
+      }
+    }
+    // (also orders the reads above before the next pass's writes)
+    const int found = __syncthreads_or(best < x_out);
+    if (!FULL && found) break;
+  }
+  s_x[t] = best;
+  s_z[t] = z;
+  if (FULL) {
+    s_de[t] = de;
+    s_cl[t] = cl;
+    s_area[t] = area;
+    s_wmin[t] = wmin;
+    s_steps[t] = steps;
+  }
+  __syncthreads();
+  for (int s = T / 2; s > 0; s >>= 1) {
+    if (t < s) {
+      if (s_x[t + s] < s_x[t]) {
+        s_x[t] = s_x[t + s];
+        s_z[t] = s_z[t + s];
+      }
+      if (FULL) {
+        s_area[t] += s_area[t + s];
+        s_wmin[t] = min(s_wmin[t], s_wmin[t + s]);
+        s_steps[t] += s_steps[t + s];
+        s_de[t] = fmax(s_de[t], s_de[t + s]);
+        const long long o = s_cl[t + s];
+        if (o >= 0 && (s_cl[t] < 0 || o < s_cl[t])) s_cl[t] = o;
+      }
+    }
+    __syncthreads();
+  }
+  if (t == 0) {
+    out[0] = s_z[0];
+    if (FULL) {
+      out[1] = s_de[0];
+      out[2] = (double)s_cl[0];
+      out[3] = (double)s_area[0];
+      out[4] = (double)s_wmin[0];
+      out[5] = (double)s_steps[0];
+    }
   }
 }
 
+// Observe, pass 1: block 0 the capillary (W > 0), the others partial sums.
 template <typename Src>
-__global__ void __launch_bounds__(256) k_obs_capillary(Src src, const uint8_t* __restrict__ mask,
-                                                       const int32_t* __restrict__ sstep,
-                                                       int nx, unsigned sb, int x_in, int x_out,
-                                                       int y0, int W, int react,
-                                                       double* __restrict__ out) {
-  capillary_obs(src, mask, sstep, nx, sb, x_in, x_out, y0, W, react, out);
+__global__ void __launch_bounds__(OBS_THREADS)
+k_observe(Src src, const float* __restrict__ g, const uint8_t* __restrict__ mask,
+          const double* __restrict__ m, const float* __restrict__ drop,
+          const int32_t* __restrict__ sstep, int nx, long long N, long long P, unsigned p1,
+          unsigned p2, int solute, int react, int nblocks, int x_in, int x_out, int y0, int W,
+          double* __restrict__ partial, double* __restrict__ out) {
+  const int first = W > 0 ? 1 : 0;
+  if ((int)blockIdx.x < first)
+    capillary_obs<true>(src, mask, sstep, nx, 1u | p1 | p2, x_in, x_out, y0, W, react, out + OBS_SLOTS);
+  else
+    partial_sums(src, g, mask, m, drop, nx, N, P, p1, p2, solute, react, (int)blockIdx.x - first,
+                 nblocks, partial);
+}
+
+// Observe, pass 2: fixed-order sum of the partials (deterministic; one
+// wavefront per slot, 42-164 us when one lane added a slot's 256-1024 values
+// in series) and the event count.
+__global__ void __launch_bounds__(64 * OBS_SLOTS)
+k_obs_final(const double* __restrict__ partial, int nblocks,
+            const unsigned long long* __restrict__ ev_count, double* __restrict__ out) {
+  const int j = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double s = 0.0;
+  for (int b = lane; b < nblocks; b += 64) s += partial[b * OBS_SLOTS + j];
+  s = wave_sum(s);
+  if (lane == 0) out[j] = s;
+  if (threadIdx.x == 0) out[OBS_OUT - 1] = __longlong_as_double((long long)*ev_count);
 }
 
 // Front of every instance of a batch (workgroup i -> instance i) into column
 // `slot` of the n x nslots table; queued without synchronisation.
-__global__ void __launch_bounds__(256) k_front_batch(const StepArgs* __restrict__ insts,
-                                                     const int4* __restrict__ capi,
-                                                     const long long* __restrict__ stepc,
-                                                     int slot, int nslots, int mom,
-                                                     double* __restrict__ table) {
-  __shared__ double res[6];
+__global__ void __launch_bounds__(OBS_THREADS)
+k_front_batch(const StepArgs* __restrict__ insts, const int4* __restrict__ capi,
+              const long long* __restrict__ stepc, int slot, int nslots, int mom,
+              double* __restrict__ table) {
   const long long step = *stepc;
   const int i = blockIdx.x;
   const StepArgs& a = insts[2 * i + (int)(step & 1)];
   const int4 c = capi[i];  // x_in, x_out, y0, W
+  double* z = table + (long long)i * nslots + slot;
   if (c.w <= 0) {
-    if (threadIdx.x == 0) table[(long long)i * nslots + slot] = __builtin_nan("");
+    if (threadIdx.x == 0) *z = __builtin_nan("");
     return;
   }
   const unsigned p1 = pending_bit(step - 1), p2 = pending_bit(step - 2);
   const unsigned sb = 1u | p1 | p2;
   if (mom) {
     const MomSrc src{a.fin, a.mask, a.P, a.nx, a.ny, 1u | p2};
-    capillary_obs(src, a.mask, a.sstep, a.nx, sb, c.x, c.y, c.z, c.w, a.react, res);
+    capillary_obs<false>(src, a.mask, a.sstep, a.nx, sb, c.x, c.y, c.z, c.w, a.react, z);
   } else {
     const PopSrc src{a.fin, a.P};
-    capillary_obs(src, a.mask, a.sstep, a.nx, sb, c.x, c.y, c.z, c.w, a.react, res);
+    capillary_obs<false>(src, a.mask, a.sstep, a.nx, sb, c.x, c.y, c.z, c.w, a.react, z);
   }
-  if (threadIdx.x == 0) table[(long long)i * nslots + slot] = res[0];
 }
 
-// Macroscopic fields of the current state as FP64 planes:
-// 0 rho1, 1 rho2, 2 ux, 3 uy, 4 conc, 5 precipitate, 6 solid.
+// Macroscopic fields of the current state as FP64 planes, the selected ones
+// (bits of sel: 0 rho1, 1 rho2, 2 ux, 3 uy, 4 conc, 5 precipitate, 6 solid)
+// one after another in `out`.  The velocities need the neighbours' densities:
+// with a velocity selected this pass also leaves both densities in planes 7
+// and 8 of `out`, and k_velocity fills in ux and uy from them.
 template <typename Src>
 __global__ void k_fields(Src src, const float* __restrict__ g, const uint8_t* __restrict__ mask,
-                         const double* __restrict__ m, int nx, int ny, long long P, unsigned sb,
-                         int solute, int react, double G, double Gads1, double Gads2, double ax,
-                         double ay, double* __restrict__ out) {
+                         const double* __restrict__ m, int nx, long long N, long long P, unsigned sb,
+                         int solute, int react, unsigned sel, double* __restrict__ out) {
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N;
+       i += (long long)gridDim.x * blockDim.x) {
+    const bool s = (mask[i] & sb) != 0;
+    double r1 = 0, r2 = 0, c = 0;
+    if (!s && (sel & 0xFu)) src.rho(i, (int)(i % nx), (int)(i / nx), r1, r2);
+    if (!s && solute && (sel & 16u))
+#pragma unroll
+      for (int q = 0; q < 5; ++q) c += g[q * P + i];
+    const double v[7] = {r1, r2, 0.0, 0.0, c, react && (sel & 32u) ? m[i] : 0.0, s ? 1.0 : 0.0};
+    double* o = out + i;
+#pragma unroll
+    for (int b = 0; b < 7; ++b) {
+      if (!(sel & (1u << b))) continue;
+      if (b != 2 && b != 3) *o = v[b];
+      o += N;
+    }
+    if (sel & 0xCu) {
+      out[7 * N + i] = r1;
+      out[8 * N + i] = r2;
+    }
+  }
+}
+
+template <typename Src>
+__global__ void k_velocity(Src src, const uint8_t* __restrict__ mask, int nx, int ny, unsigned sb,
+                           double G, double Gads1, double Gads2, double ax, double ay,
+                           const double* __restrict__ rho1, const double* __restrict__ rho2,
+                           double* __restrict__ out_x, double* __restrict__ out_y) {
   const long long N = (long long)nx * ny;
   const int ex[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
   const int ey[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
   const double w[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N;
        i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % nx), y = (int)(i / nx);
-    const bool s = (mask[i] & sb) != 0;
-    double r1 = 0, r2 = 0, ux = 0, uy = 0, c = 0;
-    if (!s) {
+    double ux = 0, uy = 0;
+    if (!(mask[i] & sb)) {
+      const int x = (int)(i % nx), y = (int)(i / nx);
       double o[6];
       src.full(i, x, y, o);
-      r1 = o[0];
-      r2 = o[1];
+      const double r1 = o[0], r2 = o[1];
       double c1x = 0, c1y = 0, c2x = 0, c2y = 0, sx = 0, sy = 0;
+#pragma unroll
       for (int q = 1; q < 9; ++q) {
         int xn = x + ex[q], yn = y + ey[q];
         xn = xn < 0 ? xn + nx : (xn >= nx ? xn - nx : xn);
         yn = yn < 0 ? yn + ny : (yn >= ny ? yn - ny : yn);
         const long long k = (long long)yn * nx + xn;
-        if (mask[k] & sb) { sx += w[q] * ex[q]; sy += w[q] * ey[q]; continue; }
-        double a, b;
-        src.rho(k, xn, yn, a, b);
+        const double f = (mask[k] & sb) ? 1.0 : 0.0;
+        sx += w[q] * f * ex[q]; sy += w[q] * f * ey[q];
+        const double a = rho1[k], b = rho2[k];  // zero at solids
         c1x += w[q] * a * ex[q]; c1y += w[q] * a * ey[q];
         c2x += w[q] * b * ex[q]; c2y += w[q] * b * ey[q];
       }
@@ -1557,16 +1616,9 @@ __global__ void k_fields(Src src, const float* __restrict__ g, const uint8_t* __
       const double F2y = -G * r2 * c1y - Gads2 * r2 * sy + r2 * ay;
       ux = (o[2] + o[4] + 0.5 * (F1x + F2x)) / (r1 + r2);
       uy = (o[3] + o[5] + 0.5 * (F1y + F2y)) / (r1 + r2);
-      if (solute)
-        for (int q = 0; q < 5; ++q) c += g[q * P + i];
     }
-    out[i] = r1;
-    out[N + i] = r2;
-    out[2 * N + i] = ux;
-    out[3 * N + i] = uy;
-    out[4 * N + i] = c;
-    out[5 * N + i] = react ? m[i] : 0.0;
-    out[6 * N + i] = s ? 1.0 : 0.0;
+    if (out_x) out_x[i] = ux;
+    if (out_y) out_y[i] = uy;
   }
 }
 
@@ -1675,7 +1727,7 @@ hipError_t launch_tick(long long* stepc, int n, hipStream_t st) {
 
 hipError_t launch_front_batch(const StepArgs* insts, const int4* capi, const long long* stepc,
                               int n, int slot, int nslots, int mom, double* table, hipStream_t st) {
-  hipLaunchKernelGGL(k_front_batch, dim3(n), dim3(256), 0, st, insts, capi, stepc, slot, nslots,
+  hipLaunchKernelGGL(k_front_batch, dim3(n), dim3(OBS_THREADS), 0, st, insts, capi, stepc, slot, nslots,
                      mom, table);
   return hipGetLastError();
 }
@@ -1699,47 +1751,43 @@ hipError_t launch_unpack(const float* M, const uint8_t* mask, int nx, int ny, lo
   return hipGetLastError();
 }
 
-template <typename Src>
-void observe_t(const Src& src, const float* g, const uint8_t* mask, const double* m,
-               const float* drop, const int32_t* sstep, int nx, int ny, long long P, unsigned p1,
-               unsigned p2, int solute, int react, int nblocks, double* partial, double* out,
-               int x_in, int x_out, int y0, int W, hipStream_t st) {
-  const long long N = (long long)nx * ny;
-  hipLaunchKernelGGL(k_obs_partial<Src>, dim3(nblocks), dim3(256), 0, st, src, g, mask, m, drop,
-                     nx, N, P, p1, p2, solute, react, partial);
-  hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(64), 0, st, partial, nblocks, out);
-  if (W > 0)
-    hipLaunchKernelGGL(k_obs_capillary<Src>, dim3(1), dim3(256), 0, st, src, mask, sstep, nx,
-                       1u | p1 | p2, x_in, x_out, y0, W, react, out + OBS_SLOTS);
-}
-
 hipError_t launch_observe(const float* f, const float* g, const uint8_t* mask, const double* m,
                           const float* drop, const int32_t* sstep, int nx, int ny, long long P,
-                          unsigned p1, unsigned p2, int mom, int solute, int react, int nblocks,
-                          double* partial, double* out, int x_in, int x_out, int y0, int W,
-                          hipStream_t st) {
-  if (mom)
-    observe_t(MomSrc{f, mask, P, nx, ny, 1u | p2}, g, mask, m, drop, sstep, nx, ny, P, p1, p2,
-              solute, react, nblocks, partial, out, x_in, x_out, y0, W, st);
-  else
-    observe_t(PopSrc{f, P}, g, mask, m, drop, sstep, nx, ny, P, p1, p2, solute, react, nblocks,
-              partial, out, x_in, x_out, y0, W, st);
+                          unsigned p1, unsigned p2, int mom, int solute, int react, int max_blocks,
+                          double* partial, double* out, const unsigned long long* ev_count, int x_in,
+                          int x_out, int y0, int W, hipStream_t st) {
+  const long long N = (long long)nx * ny;
+  const int nblocks = (int)((N + OBS_THREADS - 1) / OBS_THREADS < max_blocks
+                                ? (N + OBS_THREADS - 1) / OBS_THREADS : max_blocks);
+  auto go = [&](const auto& src) {
+    hipLaunchKernelGGL(k_observe, dim3(nblocks + (W > 0 ? 1 : 0)), dim3(OBS_THREADS), 0, st, src, g, mask,
+                       m, drop, sstep, nx, N, P, p1, p2, solute, react, nblocks, x_in, x_out, y0, W,
+                       partial, out);
+  };
+  if (mom) go(MomSrc{f, mask, P, nx, ny, 1u | p2});
+  else go(PopSrc{f, P});
+  hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(64 * OBS_SLOTS), 0, st, partial, nblocks, ev_count, out);
   return hipGetLastError();
 }
 
 hipError_t launch_fields(const float* f, const float* g, const uint8_t* mask, const double* m,
                          int nx, int ny, long long P, unsigned p1, unsigned p2, int mom,
                          int solute, int react, double G, double Gads1, double Gads2, double ax,
-                         double ay, double* out, hipStream_t st) {
-  const int blocks = grid_for((long long)nx * ny);
+                         double ay, unsigned sel, double* out, hipStream_t st) {
+  const long long N = (long long)nx * ny;
+  const int blocks = grid_for(N);
   const unsigned sb = 1u | p1 | p2;
-  if (mom)
-    hipLaunchKernelGGL(k_fields<MomSrc>, dim3(blocks), dim3(256), 0, st,
-                       MomSrc{f, mask, P, nx, ny, 1u | p2}, g, mask, m, nx, ny, P, sb, solute,
-                       react, G, Gads1, Gads2, ax, ay, out);
-  else
-    hipLaunchKernelGGL(k_fields<PopSrc>, dim3(blocks), dim3(256), 0, st, PopSrc{f, P}, g, mask, m,
-                       nx, ny, P, sb, solute, react, G, Gads1, Gads2, ax, ay, out);
+  double* vx = sel & 4u ? out + N * __builtin_popcount(sel & 3u) : nullptr;
+  double* vy = sel & 8u ? out + N * __builtin_popcount(sel & 7u) : nullptr;
+  auto go = [&](const auto& src) {
+    hipLaunchKernelGGL(k_fields, dim3(blocks), dim3(256), 0, st, src, g, mask, m, nx, N, P, sb, solute,
+                       react, sel, out);
+    if (vx || vy)
+      hipLaunchKernelGGL(k_velocity, dim3(blocks), dim3(256), 0, st, src, mask, nx, ny, sb, G, Gads1,
+                         Gads2, ax, ay, out + 7 * N, out + 8 * N, vx, vy);
+  };
+  if (mom) go(MomSrc{f, mask, P, nx, ny, 1u | p2});
+  else go(PopSrc{f, P});
   return hipGetLastError();
 }
 
