@@ -182,11 +182,12 @@ lbm_status lbm_events(lbm_sim* sim, int64_t first, lbm_event* buf, int64_t cap, 
 lbm_status lbm_save(lbm_sim* sim, void* blob, size_t cap, size_t* n);
 lbm_status lbm_load(lbm_sim* sim, const void* blob, size_t n);
 
-/* Launch shape of the fused step: tx threads per workgroup (64, 128 or 256)
- * covering tx-2 owned columns, sy owned rows per workgroup (1..4096).  In the
- * moment scheme tx is 64 lanes covering 60 columns, and a workgroup runs one
- * wavefront, or one per row where the library finds that faster.  Until a shape
- * is set, one is chosen from the lattice.  The shape changes no result bit. */
+/* Launch shape of the fused step: sy owned rows per workgroup (1..4096).  A
+ * workgroup covers 62 owned columns (60 in the moment scheme) with one
+ * wavefront per row, or with one wavefront per tile where the moment step finds
+ * that faster; tx (64, 128 or 256) is accepted and reported but decides nothing.
+ * Until a shape is set, one is chosen from the lattice.  The shape changes no
+ * result bit. */
 lbm_status lbm_set_tile(lbm_sim* sim, int32_t tx, int32_t sy);
 lbm_status lbm_get_tile(const lbm_sim* sim, int32_t* tx, int32_t* sy);
 

@@ -126,7 +126,7 @@ struct lbm_sim {
   char* ws;
   int cur;         // buffer holding the current state
   long long step;  // current state index
-  int tx, sy;      // launch shape; 0: not set, default_tile decides
+  int tx, sy;      // launch shape; 0: not set, default_rows decides
   int nt;          // 1: the step's loads carry the non-temporal cache hint
   int scheme;      // LBM_SCHEME_*
   bool mom;        // f[cur] holds moments of the last step, not populations
@@ -157,7 +157,11 @@ bool use_moments(int scheme, const lbm_params& p) {
   return scheme == LBM_SCHEME_MOMENTS || (scheme == LBM_SCHEME_AUTO && p.tau == 1.0);
 }
 
-// Launch shape of a handle that none was set for.
+// Columns a workgroup owns of its 64 lanes: the moment step's stencil reaches
+// two columns out, the population step's one.
+int owned_cols(bool moments) { return moments ? 60 : 62; }
+
+// Rows per workgroup of a handle that no launch shape was set for.
 //
 // Moment step: the lowest tiles (one wavefront per row) that give every CU no
 // more than one workgroup, since rows in series cost 1.5 us each and an idle
@@ -168,21 +172,14 @@ bool use_moments(int scheme, const lbm_params& p) {
 // 12 rows 11.6); 1448^2 44 at 8 rows, 61.  Beyond the cache (moment_kind) one
 // wavefront per tile, where 9 rows take 113 us at 2048^2 and 16 take 123.
 //
-// Population step: one row per workgroup while that leaves a CU at most a dozen
-// wavefronts, else two: its halo rows come from the caches and rows in series
-// cost 2 us each.  256x32 5.0 us at 1 row, 35 at 16; 1024x64 7.2, 33; 700x500
-// 16.3 at 2 rows, 38; 1023x1024 42.3 at 2 rows, 55; 2048^2 253 at 2 rows, 302.
-void default_tile(const lbm_params& p, bool moments, bool solute, int* tx, int* sy) {
-  if (moments) {
-    const int strips = (p.nx + 59) / 60;
-    *tx = 64;
-    *sy = 1;
-    while (*sy < 8 && (long long)strips * ((p.ny + *sy - 1) / *sy) > 256) *sy += 1;
-    if (moment_kind((long long)p.nx * p.ny, solute, *sy) != KIND_MM_SHORT) *sy = 9;
-    return;
-  }
-  *tx = p.nx >= 1024 ? 256 : (p.nx >= 256 ? 128 : 64);
-  *sy = (long long)((p.nx + 61) / 62) * p.ny <= 3072 ? 1 : 2;
+// Population step: the same rule up to six rows.  256x32 4.0 us at 1 row,
+// 1024x64 5.9 at 5, 700x500 14.2 at 6, 1023x1024 33.7 at 6 (2 rows 33.1, 14
+// rows 41), 2048^2 246 at 6 (1 row 247, 14 rows 256).
+int default_rows(const lbm_params& p, bool moments, bool solute) {
+  const int own = owned_cols(moments), strips = (p.nx + own - 1) / own, most = moments ? 8 : 6;
+  int sy = 1;
+  while (sy < most && (long long)strips * ((p.ny + sy - 1) / sy) > 256) sy += 1;
+  return moments && moment_kind((long long)p.nx * p.ny, solute, sy) != KIND_MM_SHORT ? 9 : sy;
 }
 
 // Populations of the current state written over the stored moments (the
@@ -225,10 +222,9 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   a.react = s->L.react;
   set_model(a, p, s->L.solute);
   for (long long t = 0; t < n; ++t) {
-    int tx = s->tx, sy = s->sy;
-    if (sy == 0) default_tile(p, moments && s->mom, s->L.solute, &tx, &sy);
+    const int sy = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
     const int kind = !moments ? KIND_POP : (s->mom ? moment_kind(s->L.N, s->L.solute, sy) : KIND_PM);
-    a.tx_owned = kind == KIND_POP || kind == KIND_PM ? tx - 2 : 60;  // the moment step: 64-lane tiles
+    a.tx_owned = owned_cols(s->mom);
     a.sy = sy;
     a.nsegs = (p.ny + sy - 1) / sy;
     a.nstrips = (p.nx + a.tx_owned - 1) / a.tx_owned;
@@ -241,14 +237,14 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
     a.bit_p1 = pending_bit(s->step - 1);
     a.bit_p2 = pending_bit(s->step - 2);
     a.bit_cur = pending_bit(s->step);
-    hipError_t e = launch_step(a, tx, kind, s->nt, s->stream);
+    hipError_t e = launch_step(a, kind, s->nt, s->stream);
     if (e != hipSuccess) {
       s->poisoned = true;
       return fail(LBM_EDEVICE, "step launch: %s", hipGetErrorString(e));
     }
     s->cur ^= 1;
     s->step += 1;
-    s->mom = kind != KIND_POP;
+    s->mom = moments;
   }
   return LBM_OK;
 }
@@ -603,8 +599,8 @@ lbm_status lbm_get_tile(const lbm_sim* s, int32_t* tx, int32_t* sy) {
   const bool moments = use_moments(s->scheme, s->p);
   *tx = s->tx;
   *sy = s->sy;
-  if (s->sy == 0) default_tile(s->p, moments, s->L.solute, tx, sy);
-  if (moments) *tx = 64;  // 64-lane tiles
+  if (s->sy == 0) *sy = default_rows(s->p, moments, s->L.solute);
+  if (s->sy == 0 || moments) *tx = 64;
   return LBM_OK;
 }
 
@@ -744,25 +740,19 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
     *ms_step = ms / nsteps;
     return LBM_OK;
   };
-  const int txs[] = {64, 128, 256};
-  const int sys[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128};
+  const int sys[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128};
   const bool moments = use_moments(s->scheme, s->p);
   const bool short_tiles = moments && moment_kind(s->L.N, s->L.solute, SHORT_TILE) == KIND_MM_SHORT;
   std::vector<TuneCand> cands;
   for (int nt = 0; nt < 2 && st == LBM_OK; ++nt) {
-    for (int tx : txs) {
-      if (moments && tx != 64) continue;  // 64-lane tiles only
-      if (tx > 2 * s->p.nx + 2 && tx != 64) continue;
-      for (int sy : sys) {
-        if (sy > 2 * s->p.ny && sy != 8) continue;
-        // a marching wavefront repeats four rows per tile; where short tiles
-        // run, tall ones are never faster
-        if (moments && (short_tiles ? sy > SHORT_TILE : sy < 6)) continue;
-        TuneCand c{tx, sy, nt, 0.0f};
-        if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
-        cands.push_back(c);
-      }
-      if (st != LBM_OK) break;
+    for (int sy : sys) {
+      if (sy > 2 * s->p.ny && sy != 8) continue;
+      // A marching wavefront repeats four rows per tile; rows in parallel are
+      // never faster in series.
+      if (moments && !short_tiles ? sy < 6 : sy > (moments ? SHORT_TILE : 14)) continue;
+      TuneCand c{64, sy, nt, 0.0f};
+      if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
+      cands.push_back(c);
     }
   }
   // a single lattice runs long after tuning: 20 ms per second-pass timing
@@ -829,14 +819,8 @@ struct BatchLayout {
   int max_tiles, max_blocks;
 };
 
-// Columns a workgroup owns.  The moment step runs one wavefront (64 lanes)
-// per tile and its stencil reaches two columns out; the population step
-// reaches one.  A batch in the moment scheme runs its first
-// (population-in) step on the same 64-lane tiling.
-int owned_cols(int tx, bool moments) { return moments ? 60 : tx - 2; }
-
-int tiles_for(const lbm_params& p, int tx, int sy) {
-  const int own = owned_cols(tx, true);
+int tiles_for(const lbm_params& p, int sy) {
+  const int own = owned_cols(true);
   return ((p.nx + own - 1) / own) * ((p.ny + sy - 1) / sy);
 }
 
@@ -862,7 +846,7 @@ lbm_status batch_layout(int n, const lbm_params* p, int nslots, BatchLayout* B) 
       return fail(LBM_EINVAL, "instance %d: tau, G and accel must be shared by the batch", i);
     if ((p[i].tau_g > 0.0) != solute || (p[i].k_r > 0.0) != react)
       return fail(LBM_EINVAL, "instance %d: solute/reaction switches must be shared", i);
-    B->max_tiles += tiles_for(p[i], 64, 8);
+    B->max_tiles += tiles_for(p[i], 8);
     B->max_blocks = std::max(B->max_blocks, (int)std::min<long long>(1024, ((long long)p[i].nx * p[i].ny + 255) / 256));
   }
   size_t off = 0;
@@ -911,7 +895,7 @@ StepArgs instance_args(const lbm_batch* b, int i, int parity) {
   a.P = L.P;
   a.nx = p.nx;
   a.ny = p.ny;
-  a.tx_owned = owned_cols(b->tx, batch_moments(b));
+  a.tx_owned = owned_cols(batch_moments(b));
   a.sy = b->sy;
   a.nstrips = (p.nx + a.tx_owned - 1) / a.tx_owned;
   a.nsegs = (p.ny + b->sy - 1) / b->sy;
@@ -938,7 +922,7 @@ lbm_status batch_configure(lbm_batch* b) {
     b->h_insts[2 * i + 1] = instance_args(b, i, 1);
   }
   std::vector<int4> order;
-  const int own = owned_cols(b->tx, batch_moments(b));
+  const int own = owned_cols(batch_moments(b));
   for (int i = 0; i < b->n; ++i) {
     const int ns = (b->p[i].nx + own - 1) / own, nq = (b->p[i].ny + b->sy - 1) / b->sy;
     // segment-major inside an instance, like the single-lattice step
@@ -998,10 +982,10 @@ int batch_kind(const lbm_batch* b) {
 lbm_status queue_batch(lbm_batch* b, int nsteps, hipStream_t st) {
   for (int t = 0; t < nsteps; ++t) {
     const int kind = batch_kind(b);
-    hipError_t e = launch_step_batch(b->d_insts, b->d_tiles, b->ntiles, b->d_step, t, batch_tx(b),
-                                     b->sy, b->solute, b->react, batch_variants(b), kind, st);
+    hipError_t e = launch_step_batch(b->d_insts, b->d_tiles, b->ntiles, b->d_step, t, b->sy,
+                                     b->solute, b->react, batch_variants(b), kind, st);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
-    b->mom = kind != KIND_POP;
+    b->mom = batch_moments(b);
   }
   if (nsteps > 0) {
     hipError_t e = launch_tick(b->d_step, nsteps, st);
@@ -1095,7 +1079,7 @@ lbm_status lbm_batch_init(int32_t n, const lbm_params* p, const uint8_t* const* 
   b->solute = solute;
   b->nodes = batch_nodes(b);
   // eight rows where the moment step's short tiles run (moment_kind), see
-  // default_tile
+  // default_rows
   b->tx = 128;
   b->sy = batch_moments(b) && moment_kind(b->nodes, solute, 8) == KIND_MM_SHORT ? 8 : 24;
   b->react = p[0].k_r > 0.0;
@@ -1304,17 +1288,14 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t steps, int32_t* tx_out, int3
     *ms_step = ms / nsteps;
     return LBM_OK;
   };
-  const int txs[] = {64, 128, 256};
   const int sys[] = {8, 9, 10, 12, 16, 20, 24, 32, 40, 48, 64, 80};
+  const bool short_tiles = !batch_moments(b) || moment_kind(b->nodes, b->solute, SHORT_TILE) == KIND_MM_SHORT;
   std::vector<TuneCand> cands;
-  for (int tx : txs) {
-    if (batch_moments(b) && tx != 64) continue;  // 64-lane tiles only
-    for (int sy : sys) {
-      TuneCand c{tx, sy, 0, 0.0f};
-      if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
-      cands.push_back(c);
-    }
-    if (st != LBM_OK) break;
+  for (int sy : sys) {
+    if (short_tiles && sy > SHORT_TILE) continue;  // as in lbm_autotune
+    TuneCand c{64, sy, 0, 0.0f};
+    if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
+    cands.push_back(c);
   }
   // a sweep's tuning is part of its cost: 5 ms per second-pass timing
   TuneCand best{b->tx, b->sy, 0, 1e30f};

@@ -28,8 +28,8 @@ struct StepArgs {
   long long P;        // plane stride in elements
   long long step;     // index n of the state being advanced (n -> n+1)
   int nx, ny;
-  int tx_owned;       // columns owned per workgroup (blockDim.x - 2, or - 4 in
-                      // the moment step, whose stencil reaches two columns out)
+  int tx_owned;       // columns owned per workgroup: 62 of 64 lanes, or 60 in the
+                      // moment step, whose stencil reaches two columns out
   int sy;             // rows owned per workgroup
   int nstrips, nsegs;
   int remap;          // XCD-aware tile order (tile count divisible by 8)
@@ -40,10 +40,8 @@ struct StepArgs {
   // model parameters in FP64 (kernel arguments stay in scalar registers)
   double omega;       // 1/tau
   double tau;
-  double mG36, mGads1, mGads2;       // -G/36, -G_ads/36 per component
-  double ax, ay;
-  double og_keep, og_w, og_wc;       // solute: 1 - 1/tau_g, w/tau_g, w c/tau_g (w: axis
-                                     // weight, c: 1 / sound speed^2)
+  double G, Gads1, Gads2, ax, ay;
+  double omega_g;     // 1/tau_g
   double k_r, threshold;
   double c_eq;        // saturation concentration of the reaction (0: plain first order)
   double c_hold;      // held concentration of the source region x < hold_x
@@ -53,24 +51,20 @@ struct StepArgs {
 
 // The model parameters of p (solute: it has a solute lattice).
 inline void set_model(StepArgs& a, const lbm_params& p, bool solute) {
-  const bool q4 = p.solute_q == 4;
-  const double og = solute ? 1.0 / p.tau_g : 0.0, w = q4 ? 0.25 : 1.0 / 6.0;
   a.omega = 1.0 / p.tau;
   a.tau = p.tau;
-  a.mG36 = -p.G / 36.0;
-  a.mGads1 = -p.G_ads[0] / 36.0;
-  a.mGads2 = -p.G_ads[1] / 36.0;
+  a.G = p.G;
+  a.Gads1 = p.G_ads[0];
+  a.Gads2 = p.G_ads[1];
   a.ax = p.accel[0];
   a.ay = p.accel[1];
-  a.og_keep = 1.0 - og;
-  a.og_w = og * w;
-  a.og_wc = og * w * (q4 ? 2.0 : 3.0);
+  a.omega_g = solute ? 1.0 / p.tau_g : 0.0;
   a.k_r = p.k_r;
   a.threshold = p.threshold;
   a.c_eq = p.c_eq;
   a.c_hold = p.c_hold;
   a.hold_x = p.hold_x;
-  a.q4 = q4;
+  a.q4 = p.solute_q == 4;
 }
 
 // Growth marks rotate over three pending bits: step n marks a node with
@@ -108,13 +102,13 @@ inline int moment_kind(long long nodes, bool solute, int sy) {
 lbm_status fail(lbm_status s, const char* fmt, ...);
 
 // nt: non-temporal load hint (moment and population steps)
-hipError_t launch_step(const StepArgs& a, int tx, int kind, int nt, hipStream_t st);
+hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st);
 // var: some instance uses a reaction or solute-lattice variant
 // One batched step at index *stepc + j; a sequence of n such launches
 // (j = 0..n-1) is followed by launch_tick(stepc, n).
 hipError_t launch_step_batch(const StepArgs* insts, const int4* tiles, int ntiles,
-                             const long long* stepc, int j, int tx, int sy, int solute, int react,
-                             int var, int kind, hipStream_t st);
+                             const long long* stepc, int j, int sy, int solute, int react, int var,
+                             int kind, hipStream_t st);
 hipError_t launch_tick(long long* stepc, int n, hipStream_t st);
 hipError_t launch_front_batch(const StepArgs* insts, const int4* capi, const long long* stepc,
                               int n, int slot, int nslots, int mom, double* table, hipStream_t st);

@@ -100,11 +100,10 @@ __device__ __forceinline__ unsigned load_b32(__amdgpu_buffer_rsrc_t r, unsigned 
 }
 
 // Workgroup-wide LDS barrier that leaves outstanding global memory operations
-// in flight (only LDS traffic is ordered); a single-wave workgroup needs no
-// s_barrier at all.
-__device__ __forceinline__ void lds_barrier(int TX) {
+// in flight (only LDS traffic is ordered).
+__device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  if (TX > 64) __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
@@ -124,30 +123,25 @@ __device__ __forceinline__ float recip(float x) {
   return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);
 }
 
-// Accelerations F_s / rho_s of the two components at a fluid node: Shan-Chen
-// cohesion and adhesion plus the body acceleration (section "LB models": each
-// a weight-normalised sum over the eight neighbours).  Both forces are
-// proportional to the node's own density, so the velocity shift tau F_s / rho_s
-// needs no division by it.  n1, n2: the neighbours' densities (zero at solid
-// nodes), index = link, 1..8 = E, N, W, S, NE, NW, SW, SE (index 0 unused);
-// (wx, wy): sum of the links to solid neighbours, axis links counted four
-// times (the weights are 4 : 1, and 1/36 is part of the constants).
+// Shan-Chen interaction forces plus the body force at a fluid node (section
+// "LB models": cohesion between the two components and adhesion to the solid,
+// each a weight-normalised sum over the eight neighbours).  n1, n2: the
+// neighbours' densities (zero at solid nodes), index = link, 1..8 = E, N, W, S,
+// NE, NW, SW, SE (index 0 unused); (csx, csy): the weighted sum of the links to
+// solid neighbours (wall_links).
 template <typename R>
-__device__ __forceinline__ void sc_accel(const StepArgs& a, const R* n1, const R* n2, R wx, R wy,
-                                         R& A1x, R& A1y, R& A2x, R& A2y) {
-  auto links = [](const R* n, R& x, R& y) {
-    const R p = n[5] - n[7], q = n[8] - n[6];
-    x = fmar(n[1] - n[3], R(4), p + q);
-    y = fmar(n[2] - n[4], R(4), p - q);
-  };
-  R c1x, c1y, c2x, c2y;
-  links(n1, c1x, c1y);
-  links(n2, c2x, c2y);
-  const R G = (R)a.mG36, Ga1 = (R)a.mGads1, Ga2 = (R)a.mGads2, ax = (R)a.ax, ay = (R)a.ay;
-  A1x = fmar(G, c2x, fmar(Ga1, wx, ax));
-  A1y = fmar(G, c2y, fmar(Ga1, wy, ay));
-  A2x = fmar(G, c1x, fmar(Ga2, wx, ax));
-  A2y = fmar(G, c1y, fmar(Ga2, wy, ay));
+__device__ __forceinline__ void sc_forces(const StepArgs& a, const R* n1, const R* n2, R csx, R csy,
+                                          R rho1, R rho2, R& F1x, R& F1y, R& F2x, R& F2y) {
+  const R WA = R(1) / R(9), WD = R(1) / R(36);
+  const R c2x = WA * (n2[1] - n2[3]) + WD * ((n2[5] - n2[6]) + (n2[8] - n2[7]));
+  const R c2y = WA * (n2[2] - n2[4]) + WD * ((n2[5] + n2[6]) - (n2[8] + n2[7]));
+  const R c1x = WA * (n1[1] - n1[3]) + WD * ((n1[5] - n1[6]) + (n1[8] - n1[7]));
+  const R c1y = WA * (n1[2] - n1[4]) + WD * ((n1[5] + n1[6]) - (n1[8] + n1[7]));
+  const R G = (R)a.G, Ga1 = (R)a.Gads1, Ga2 = (R)a.Gads2, ax = (R)a.ax, ay = (R)a.ay;
+  F1x = -G * rho1 * c2x - Ga1 * rho1 * csx + rho1 * ax;
+  F1y = -G * rho1 * c2y - Ga1 * rho1 * csy + rho1 * ay;
+  F2x = -G * rho2 * c1x - Ga2 * rho2 * csx + rho2 * ax;
+  F2y = -G * rho2 * c1y - Ga2 * rho2 * csy + rho2 * ay;
 }
 
 // Equilibrium velocities of the two components (common velocity shifted by
@@ -155,18 +149,16 @@ __device__ __forceinline__ void sc_accel(const StepArgs& a, const R* n1, const R
 // solute; irt = 1 / (rho1 + rho2).
 template <typename R>
 __device__ __forceinline__ void sc_velocities(R tau, R rho1, R rho2, R j1x, R j1y, R j2x, R j2y,
-                                              R A1x, R A1y, R A2x, R A2y, R& v1x, R& v1y,
+                                              R F1x, R F1y, R F2x, R F2y, R& v1x, R& v1y,
                                               R& v2x, R& v2y, R& ux, R& uy, R& irt) {
-  irt = recip(rho1 + rho2);
-  const R jx = j1x + j2x, jy = j1y + j2y;
-  const R upx = jx * irt, upy = jy * irt;
-  const bool p1 = rho1 > R(0), p2 = rho2 > R(0);
-  v1x = p1 ? fmar(tau, A1x, upx) : upx;
-  v1y = p1 ? fmar(tau, A1y, upy) : upy;
-  v2x = p2 ? fmar(tau, A2x, upx) : upx;
-  v2y = p2 ? fmar(tau, A2y, upy) : upy;
-  ux = fmar(R(0.5), fmar(rho1, A1x, rho2 * A2x), jx) * irt;
-  uy = fmar(R(0.5), fmar(rho1, A1y, rho2 * A2y), jy) * irt;
+  const R rt = rho1 + rho2;
+  irt = recip(rt);
+  const R upx = (j1x + j2x) * irt, upy = (j1y + j2y) * irt;
+  v1x = upx; v1y = upy; v2x = upx; v2y = upy;
+  if (rho1 > R(0)) { const R s = tau * recip(rho1); v1x += s * F1x; v1y += s * F1y; }
+  if (rho2 > R(0)) { const R s = tau * recip(rho2); v2x += s * F2x; v2y += s * F2y; }
+  ux = (j1x + j2x + R(0.5) * (F1x + F2x)) * irt;
+  uy = (j1y + j2y + R(0.5) * (F1y + F2y)) * irt;
 }
 
 // Solute collision (BGK on D2Q5, or on D2Q4 with weights 1/4 and no rest
@@ -187,17 +179,9 @@ struct SoluteOut {
   bool wm;
 };
 
-template <bool REACT>
-__device__ __forceinline__ void store_solute(const StepArgs& a, const SoluteOut& o, unsigned idx) {
-  float* __restrict__ go = a.gout;
-#pragma unroll
-  for (int q = 0; q < 5; ++q) go[o.off[q]] = o.g[q];
-  if (REACT && o.wm) a.m[idx] = o.m;
-}
-
 template <bool REACT, bool VAR, typename R>
 __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R ux, R uy, R rho1,
-                                            R irt, const bool* wall, double m_cur, unsigned P,
+                                            R rho2, R irt, const bool* wall, double m_cur, unsigned P,
                                             unsigned idx, unsigned iE, unsigned iN, unsigned iW,
                                             unsigned iS, int xc, bool& ev, SoluteOut& so) {
   so.wm = false;
@@ -205,19 +189,20 @@ __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R
   // VAR = false: the plain model (D2Q5, c_eq = 0, no held source)
   const bool q4 = VAR && a.q4 != 0;
   const R C = (((R)g[0] + (R)g[1]) + ((R)g[2] + (R)g[3])) + (R)g[4];
-  // g* = (1 - og) g + og w C (1 + cs e.u), the constants products of the host
-  const R keep_g = (R)a.og_keep, gw = (R)a.og_w * C, gc = (R)a.og_wc * C;
-  const R gx = gc * ux, gy = gc * uy;
+  const R WQ = q4 ? R(0.25) : R(1) / R(6), CQ = q4 ? R(2) : R(3);
+  const R og = (R)a.omega_g;
   R gs[5];
-  gs[1] = fmar(keep_g, (R)g[1], gw) + gx;
-  gs[2] = fmar(keep_g, (R)g[2], gw) + gy;
-  gs[3] = fmar(keep_g, (R)g[3], gw) - gx;
-  gs[4] = fmar(keep_g, (R)g[4], gw) - gy;
+  gs[1] = (R)g[1] + og * (WQ * C * (R(1) + CQ * ux) - (R)g[1]);
+  gs[2] = (R)g[2] + og * (WQ * C * (R(1) + CQ * uy) - (R)g[2]);
+  gs[3] = (R)g[3] + og * (WQ * C * (R(1) - CQ * ux) - (R)g[3]);
+  gs[4] = (R)g[4] + og * (WQ * C * (R(1) - CQ * uy) - (R)g[4]);
   gs[0] = q4 ? R(0) : C - ((gs[1] + gs[2]) + (gs[3] + gs[4]));
   if (REACT) {
     const int ns = (int)wall[1] + (int)wall[2] + (int)wall[3] + (int)wall[4];
     if (ns > 0) {
-      const double phi = (double)rho1 * (double)irt;
+      // rho1 / (rho1 + rho2) from the reciprocal, corrected by its residual
+      const double q = (double)rho1 * (double)irt;
+      const double phi = __builtin_fma(__builtin_fma(-q, (double)rho1 + (double)rho2, (double)rho1), (double)irt, q);
       const double rr = a.k_r * (double)ns * phi;
       double dm, keep;
       if (VAR && a.c_eq > 0.0) {
@@ -241,7 +226,6 @@ __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R
     }
   }
   if (VAR && xc < a.hold_x) {
-    const R WQ = q4 ? R(0.25) : R(1) / R(6), CQ = q4 ? R(2) : R(3);
     const R Ch = (R)a.c_hold;
     gs[1] = WQ * Ch * (R(1) + CQ * ux);
     gs[2] = WQ * Ch * (R(1) + CQ * uy);
@@ -257,6 +241,20 @@ __device__ __forceinline__ void solute_step(const StepArgs& a, const float* g, R
   so.off[2] = wall[2] ? 4 * P + idx : 2 * P + iN;
   so.off[3] = wall[3] ? 1 * P + idx : 3 * P + iW;
   so.off[4] = wall[4] ? 2 * P + idx : 4 * P + iS;
+}
+
+// Stores what solute_step leaves: descriptors of the outgoing solute and the
+// precipitate.
+template <bool REACT>
+__device__ __forceinline__ void store_solute(const SoluteOut& o, __amdgpu_buffer_rsrc_t rg,
+                                             __amdgpu_buffer_rsrc_t rm, unsigned idx) {
+#pragma unroll
+  for (int q = 0; q < 5; ++q)
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.g[q]), rg, (int)(4u * o.off[q]), 0, 0);
+  if (REACT && o.wm) {
+    const v2u mb = {(unsigned)__double2loint(o.m), (unsigned)__double2hiint(o.m)};
+    __builtin_amdgcn_raw_buffer_store_b64(mb, rm, (int)(8u * idx), 0, 0);
+  }
 }
 
 // One lane per wavefront reserves event-log slots for every lane that marked
@@ -325,208 +323,6 @@ __device__ __forceinline__ void moments9(const R* f, R& rho, R& jx, R& jy) {
   jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
 }
 
-// R is the arithmetic type (float or double); populations are stored as FP32.
-//
-// Population step.  Per workgroup, iteration k handles row r = ys - 1 + k: its
-// populations, precipitate (owned rows) and the mask byte of row k+1 are
-// requested together (the mask of row k arrived one iteration earlier), so
-// each iteration waits on one memory round trip.  The densities of row k go
-// to the LDS ring; after an LDS-only barrier row k-1 is collided and pushed.
-// Offsets are 32-bit (the host guarantees 23 planes fit below 2^31).  The
-// register budget is held to three waves per SIMD: a row iteration costs one
-// memory round trip plus ~1 us of VALU work per wave, so resident waves are
-// what hides the memory latency.  OUTM (tau = 1 only): store the moments
-// (rho_s, v_s) of the collided node instead of pushing populations.
-template <bool SOLUTE, bool REACT, bool VAR, typename R, bool OUTM, bool NT>
-__device__ __forceinline__ void step_tile(const StepArgs& a, int strip, int seg, char* lds_raw) {
-  const int TX = blockDim.x;
-  R* s_r1 = (R*)lds_raw;                 // [4][TX] density of component 1 (0 at solid)
-  R* s_r2 = s_r1 + 4 * TX;               // [4][TX] density of component 2
-  float* s_s = (float*)(s_r2 + 4 * TX);  // [4][TX] solid flag 0/1
-
-  const int t = threadIdx.x;
-  const int nx = a.nx, ny = a.ny;
-  const unsigned P = (unsigned)a.P;
-  const int x0 = strip * a.tx_owned;
-  const int nown = min(a.tx_owned, nx - x0);
-  const bool active = t <= nown + 1;
-  const bool owner = t >= 1 && t <= nown;
-  int xc = x0 - 1 + t;
-  if (xc < 0) xc += nx;
-  if (xc >= nx) xc -= nx;
-  const int xl = xc == 0 ? nx - 1 : xc - 1;
-  const int xr = xc == nx - 1 ? 0 : xc + 1;
-  const int ys = seg * a.sy;
-  const int ye = min(ys + a.sy, ny);
-  const int nrows = ye - ys + 2;
-  const unsigned SPREV = 1u | a.bit_p2;    // solid in state n-1
-  const unsigned SCUR = SPREV | a.bit_p1;  // solid in state n
-  const float* __restrict__ fin = a.fin;
-  const float* __restrict__ gin = a.gin;
-  const uint8_t* __restrict__ maskp = a.mask;
-
-  auto row_y = [&](int k) {
-    int yr = ys - 1 + k;
-    if (yr < 0) yr += ny;
-    if (yr >= ny) yr -= ny;
-    return yr;
-  };
-
-  float f[18], g[5], fn[18], gn[5];
-  double m_cur = 0.0, m_nxt = 0.0;
-  unsigned b_cur = 1, b_nxt = 1;
-  unsigned mask_ahead = active ? (unsigned)maskp[(unsigned)row_y(0) * (unsigned)nx + (unsigned)xc] : 1u;
-
-  for (int k = 0; k < nrows; ++k) {
-    // ---- request row k: populations (+ solute, precipitate), next mask ----
-    const unsigned idn = (unsigned)row_y(k) * (unsigned)nx + (unsigned)xc;
-    const bool owned_row = k >= 1 && k <= nrows - 2;
-    b_nxt = mask_ahead;
-    if (active) {
-      if (!(b_nxt & SPREV)) {
-        // read once per step (NT: with the non-temporal hint)
-#pragma unroll
-        for (int q = 0; q < 18; ++q)
-          fn[q] = NT ? __builtin_nontemporal_load(&fin[q * P + idn]) : fin[q * P + idn];
-        if (SOLUTE && owner && owned_row) {
-#pragma unroll
-          for (int q = 0; q < 5; ++q)
-            gn[q] = NT ? __builtin_nontemporal_load(&gin[q * P + idn]) : gin[q * P + idn];
-        }
-        if (REACT && owner && owned_row) m_nxt = a.m[idn];
-      }
-      if (k + 1 < nrows) mask_ahead = maskp[(unsigned)row_y(k + 1) * (unsigned)nx + (unsigned)xc];
-    }
-    // one wait per row, on every path: the row's loads (and the previous
-    // row's stores, issued earlier) complete here, so nothing is pending on
-    // the loop back edge
-    __builtin_amdgcn_s_waitcnt(VMCNT0);
-    R r1 = R(0), r2 = R(0);
-    float sv = 1.0f;
-    if (active && !(b_nxt & SCUR)) {
-      r1 = sum9<R>(fn);
-      r2 = sum9<R>(fn + 9);
-      sv = 0.0f;
-    }
-    const int slot = k & 3;
-    s_r1[slot * TX + t] = r1;
-    s_r2[slot * TX + t] = r2;
-    s_s[slot * TX + t] = sv;
-    lds_barrier(TX);
-
-    // ---- collide and push row y = r - 1 -----------------------------------
-    bool ev = false;
-    const int y = ys + k - 2;
-    if (k >= 2 && owner) {
-      const int yd = y == 0 ? ny - 1 : y - 1;
-      const int yu = y == ny - 1 ? 0 : y + 1;
-      const unsigned idx = (unsigned)y * (unsigned)nx + (unsigned)xc;
-      const int sb = ((k - 2) & 3) * TX, sm = ((k - 1) & 3) * TX, sa = (k & 3) * TX;
-      if (s_s[sm + t] != 0.0f) {
-        if (REACT) {
-          if (b_cur & a.bit_p1) {
-            // turned solid at the end of the previous step: book its populations
-            a.drop[idx] = (float)sum9<R>(f);
-            a.drop[P + idx] = (float)sum9<R>(f + 9);
-            a.drop[2 * P + idx] =
-                SOLUTE ? (float)((((R)g[0] + (R)g[1]) + ((R)g[2] + (R)g[3])) + (R)g[4]) : 0.0f;
-          } else if (b_cur & a.bit_p2) {
-            a.mask[idx] = 1;  // booked one step ago: fold the mark into bit0
-          }
-        }
-      } else {
-        const R rho1 = s_r1[sm + t], rho2 = s_r2[sm + t];
-        // neighbours in link order 1..8 = E, N, W, S, NE, NW, SW, SE
-        const int no[9] = {sm + t, sm + t + 1, sa + t, sm + t - 1, sb + t,
-                           sa + t + 1, sa + t - 1, sb + t - 1, sb + t + 1};
-        R n1[9], n2[9];
-        float sf[9];
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-          n1[i] = s_r1[no[i]];
-          n2[i] = s_r2[no[i]];
-          sf[i] = s_s[no[i]];
-        }
-        const R wx = (R)(4.0f * (sf[1] - sf[3]) + ((sf[5] - sf[7]) + (sf[8] - sf[6])));
-        const R wy = (R)(4.0f * (sf[2] - sf[4]) + ((sf[5] - sf[7]) - (sf[8] - sf[6])));
-        R A1x, A1y, A2x, A2y;
-        sc_accel<R>(a, n1, n2, wx, wy, A1x, A1y, A2x, A2y);
-        const R j1x = ((R)f[1] - (R)f[3]) + ((R)f[5] - (R)f[6]) + ((R)f[8] - (R)f[7]);
-        const R j1y = ((R)f[2] - (R)f[4]) + ((R)f[5] + (R)f[6]) - ((R)f[7] + (R)f[8]);
-        const R j2x = ((R)f[10] - (R)f[12]) + ((R)f[14] - (R)f[15]) + ((R)f[17] - (R)f[16]);
-        const R j2y = ((R)f[11] - (R)f[13]) + ((R)f[14] + (R)f[15]) - ((R)f[16] + (R)f[17]);
-        R v1x, v1y, v2x, v2y, ux, uy, irt;
-        sc_velocities<R>((R)a.tau, rho1, rho2, j1x, j1y, j2x, j2y, A1x, A1y, A2x, A2y, v1x, v1y,
-                         v2x, v2y, ux, uy, irt);
-
-        // target offsets of the four axis neighbours (and the diagonals)
-        const unsigned iE = (unsigned)y * nx + xr, iW = (unsigned)y * nx + xl;
-        const unsigned iN = (unsigned)yu * nx + xc, iS = (unsigned)yd * nx + xc;
-        float* __restrict__ fo = a.fout;
-        if (OUTM) {
-          fo[idx] = (float)rho1;
-          fo[P + idx] = (float)v1x;
-          fo[2 * P + idx] = (float)v1y;
-          fo[3 * P + idx] = (float)rho2;
-          fo[4 * P + idx] = (float)v2x;
-          fo[5 * P + idx] = (float)v2y;
-        } else {
-          const unsigned iNE = (unsigned)yu * nx + xr, iNW = (unsigned)yu * nx + xl;
-          const unsigned iSW = (unsigned)yd * nx + xl, iSE = (unsigned)yd * nx + xr;
-          const R om = (R)a.omega;
-          // collide one component and push each moving population as soon as
-          // it is formed (halfway bounce-back into the node's own opposite
-          // link at a solid neighbour); the rest population closes the mass
-          // balance exactly (the moving-link weights are not exact binary
-          // fractions)
-          auto collide_push = [&](const float* fc, unsigned base, R rho, R vx, R vy) {
-            const R uu = vx * vx + vy * vy;
-            R sum = R(0);
-#define CP(i, opp, w, eu, bs, tgt)                                          \
-  do {                                                                      \
-    const R fi = (R)fc[i];                                                  \
-    const R v = fi + om * (feq<R>(w, rho, eu, uu) - fi);                    \
-    sum += v;                                                               \
-    if (bs != 0.0f) fo[(base + (opp)) * P + idx] = (float)v;                \
-    else fo[(base + (i)) * P + (tgt)] = (float)v;                           \
-  } while (0)
-            const R WA = R(1) / R(9), WD = R(1) / R(36);
-            CP(1, 3, WA, vx, sf[1], iE);
-            CP(2, 4, WA, vy, sf[2], iN);
-            CP(3, 1, WA, -vx, sf[3], iW);
-            CP(4, 2, WA, -vy, sf[4], iS);
-            CP(5, 7, WD, vx + vy, sf[5], iNE);
-            CP(6, 8, WD, -vx + vy, sf[6], iNW);
-            CP(7, 5, WD, -vx - vy, sf[7], iSW);
-            CP(8, 6, WD, vx - vy, sf[8], iSE);
-#undef CP
-            fo[base * P + idx] = (float)(rho - sum);
-          };
-          collide_push(f, 0u, rho1, v1x, v1y);
-          collide_push(f + 9, 9u, rho2, v2x, v2y);
-        }
-        if (SOLUTE) {
-          SoluteOut so;
-          const bool wall[5] = {false, sf[1] != 0.0f, sf[2] != 0.0f, sf[3] != 0.0f, sf[4] != 0.0f};
-          solute_step<REACT, VAR, R>(a, g, ux, uy, rho1, irt, wall, m_cur, P, idx, iE, iN, iW, iS, xc, ev,
-                                     so);
-          store_solute<REACT>(a, so, idx);
-        }
-      }
-    }
-    if (REACT) log_events(a, ev, xc, y);
-    // rotate: row k becomes the row to collide next iteration
-#pragma unroll
-    for (int q = 0; q < 18; ++q) f[q] = fn[q];
-    if (SOLUTE) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q) g[q] = gn[q];
-    }
-    m_cur = m_nxt;
-    b_cur = b_nxt;
-  }
-}
-
 // Cross-lane moves within one wavefront (DPP wave shifts): from_left(v) in
 // lane t is v of lane t-1, from_right(v) is v of lane t+1; the end lane
 // without a source reads 0.  Called with every lane active.
@@ -566,14 +362,29 @@ struct Neighbours {
   }
 };
 
+// Weighted sum of the links to solid neighbours.
+template <typename R>
+__device__ __forceinline__ void wall_links(const Neighbours& solid, R& csx, R& csy) {
+  const R WA = R(1) / R(9), WD = R(1) / R(36);
+  csx = R(0);
+  csy = R(0);
+  if (solid.any()) {  // the same for all lanes
+    auto w = [&](int i) { return on_lane(solid.n[i]) ? 1 : 0; };
+    const int ne_sw = w(5) - w(7), se_nw = w(8) - w(6);
+    csx = WA * R(w(1) - w(3)) + WD * R(ne_sw + se_nw);
+    csy = WA * R(w(2) - w(4)) + WD * R(ne_sw - se_nw);
+  }
+}
+
 // Which links of every lane's node lead to a solid node, as factors 0 and 1;
 // any: some link of some fluid lane does (a node solid itself sends nothing).
 template <typename R>
 struct Bounce {
-  bool any;  // the same for all lanes
+  bool any;   // the same for all lanes
+  bool none;  // no lane is fluid: the row sends nothing
   R s[9];
   __device__ __forceinline__ Bounce(const Neighbours& solid, lanes_t row)
-      : any((solid.any() & ~row) != 0) {
+      : any((solid.any() & ~row) != 0), none(~row == 0) {
 #pragma unroll
     for (int i = 0; i < 9; ++i) s[i] = R(0);
     if (any) {
@@ -586,14 +397,22 @@ struct Bounce {
 // One component's outgoing equilibria of every lane's node from its stored
 // moments (zero moments: nothing goes out), handed to `to`: to.up(o2, o5, o6)
 // gets the links into the row above, to.down(o4, o7, o8) those into the row
-// below, and to.own(r, x, y) what adds to the accumulators (rho, jx, jy) of the
-// row itself: the rest and horizontal links, streamed along the row by DPP
-// wave shifts, and what bounces back.  Called with every lane active.
+// below, to.own(r, x) what adds (r, x, 0) to the accumulators (rho, jx, jy) of
+// the row itself (the rest and horizontal links, streamed along the row by DPP
+// wave shifts) and to.bounced(r, x, y) what bounces back.  Called with every
+// lane active.
 // With u3 = 3 v: w rho (1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v^2)
 //              = w rho (cc + e3 (1 + e3 / 2)), e3 = e . u3, cc = 1 - u3^2 / 6.
 template <typename R, typename To>
 __device__ __forceinline__ void stream_row(float rho_s, float vx, float vy, const Bounce<R>& bounce,
                                            To&& to) {
+  if (bounce.none) {  // inside a wall: a sixth of a sweep's rows
+    to.up(R(0), R(0), R(0));
+    to.down(R(0), R(0), R(0));
+    to.own(R(0), R(0));
+    to.bounced(R(0), R(0), R(0));
+    return;
+  }
   const R WA = R(1) / R(9), WD = R(1) / R(36), WR = R(4) / R(9);
   const R rho = (R)rho_s;
   const R ux = R(3) * (R)vx, uy = R(3) * (R)vy;
@@ -608,23 +427,26 @@ __device__ __forceinline__ void stream_row(float rho_s, float vx, float vy, cons
   to.down(o4, o7, o8);
   // rest and horizontal links (1, 3)
   const R a1 = from_left(o1), a3 = from_right(o3);
-  R r = (o0 + a1) + a3, x = a1 - a3, y = R(0);
+  to.own((o0 + a1) + a3, a1 - a3);
   // a value streaming into a solid node bounces back into the sender's
   // opposite link: rho += o_i, j -= e_i o_i
   if (bounce.any) {
     const R* s = bounce.s;
-    r = fmar(s[1], o1, r); r = fmar(s[2], o2, r);
-    r = fmar(s[3], o3, r); r = fmar(s[4], o4, r);
-    r = fmar(s[5], o5, r); r = fmar(s[6], o6, r);
-    r = fmar(s[7], o7, r); r = fmar(s[8], o8, r);
-    x = fmar(s[3], o3, x); x = fmar(-s[1], o1, x);
-    x = fmar(-s[5], o5, x); x = fmar(s[6], o6, x);
-    x = fmar(s[7], o7, x); x = fmar(-s[8], o8, x);
-    y = s[4] * o4; y = fmar(-s[2], o2, y);
-    y = fmar(-s[5], o5, y); y = fmar(-s[6], o6, y);
-    y = fmar(s[7], o7, y); y = fmar(s[8], o8, y);
+    R br = s[1] * o1, bx = s[3] * o3, by = s[4] * o4;
+    br = fmar(s[2], o2, br); br = fmar(s[3], o3, br);
+    br = fmar(s[4], o4, br); br = fmar(s[5], o5, br);
+    br = fmar(s[6], o6, br); br = fmar(s[7], o7, br);
+    br = fmar(s[8], o8, br);
+    bx = fmar(-s[1], o1, bx); bx = fmar(-s[5], o5, bx);
+    bx = fmar(s[6], o6, bx); bx = fmar(s[7], o7, bx);
+    bx = fmar(-s[8], o8, bx);
+    by = fmar(-s[2], o2, by); by = fmar(-s[5], o5, by);
+    by = fmar(-s[6], o6, by); by = fmar(s[7], o7, by);
+    by = fmar(s[8], o8, by);
+    to.bounced(br, bx, by);
+  } else {
+    to.bounced(R(0), R(0), R(0));
   }
-  to.own(r, x, y);
 }
 
 // stream_row into the accumulators of the rows above (started by it), own and
@@ -637,7 +459,11 @@ struct RowSums {
     above[0] = above[2] = (o2 + a5) + a6;
     above[1] = a5 - a6;
   }
-  __device__ __forceinline__ void own(R r, R x, R y) const {
+  __device__ __forceinline__ void own(R r, R x) const {
+    row[0] += r;
+    row[1] += x;
+  }
+  __device__ __forceinline__ void bounced(R r, R x, R y) const {
     row[0] += r;
     row[1] += x;
     row[2] += y;
@@ -692,18 +518,13 @@ __device__ __forceinline__ void collide_moments(const StepArgs& a, const MomentO
     // neighbours x + e_i, link order 1..8 = E, N, W, S, NE, NW, SW, SE
     const R n1[9] = {R(0), W1[4], W0[0], W1[2], W2[0], W0[4], W0[2], W2[2], W2[4]};
     const R n2[9] = {R(0), W1[5], W0[1], W1[3], W2[1], W0[5], W0[3], W2[3], W2[5]};
-    R wx = R(0), wy = R(0);
-    if (solid.any()) {  // the same for all lanes
-      auto w = [&](int i, int v) { return on_lane(solid.n[i]) ? v : 0; };
-      const int p = w(5, 1) - w(7, 1), q = w(8, 1) - w(6, 1);
-      wx = (R)((w(1, 4) - w(3, 4)) + (p + q));
-      wy = (R)((w(2, 4) - w(4, 4)) + (p - q));
-    }
-    R A1x, A1y, A2x, A2y;
-    sc_accel<R>(a, n1, n2, wx, wy, A1x, A1y, A2x, A2y);
+    R csx, csy;
+    wall_links<R>(solid, csx, csy);
+    R F1x, F1y, F2x, F2y;
+    sc_forces<R>(a, n1, n2, csx, csy, rC[0], rC[3], F1x, F1y, F2x, F2y);
     R v1x, v1y, v2x, v2y, ux, uy, irt;
     // tau = 1 in the moment scheme
-    sc_velocities<R>(R(1), rC[0], rC[3], rC[1], rC[2], rC[4], rC[5], A1x, A1y, A2x, A2y, v1x, v1y,
+    sc_velocities<R>(R(1), rC[0], rC[3], rC[1], rC[2], rC[4], rC[5], F1x, F1y, F2x, F2y, v1x, v1y,
                      v2x, v2y, ux, uy, irt);
     mo[0] = (float)rC[0];
     mo[1] = (float)v1x;
@@ -720,16 +541,9 @@ __device__ __forceinline__ void collide_moments(const StepArgs& a, const MomentO
       SoluteOut so;
       const bool wall[5] = {false, on_lane(solid.n[1]), on_lane(solid.n[2]), on_lane(solid.n[3]),
                             on_lane(solid.n[4])};
-      solute_step<REACT, VAR, R>(a, gv, ux, uy, rC[0], irt, wall, mC, P, idx, iE, iN, iW, iS, xc, ev,
+      solute_step<REACT, VAR, R>(a, gv, ux, uy, rC[0], rC[3], irt, wall, mC, P, idx, iE, iN, iW, iS, xc, ev,
                                  so);
-#pragma unroll
-      for (int q = 0; q < 5; ++q)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(so.g[q]), o.g,
-                                              (int)(4u * so.off[q]), 0, 0);
-      if (REACT && so.wm) {
-        const v2u mb = {(unsigned)__double2loint(so.m), (unsigned)__double2hiint(so.m)};
-        __builtin_amdgcn_raw_buffer_store_b64(mb, o.prec, (int)(8u * idx), 0, 0);
-      }
+      store_solute<REACT>(so, o.g, o.prec, idx);
     }
   }
 #pragma unroll
@@ -967,8 +781,7 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
 // with 24 wavefronts per CU resident (64 VGPRs, 74 KB LDS) instead of 12:
 // 1024^2 preform 24.8 us against 33.3.  Eight rows because two workgroups of
 // 12 wavefronts share a CU's LDS; nine to twelve leave one.
-constexpr int ROWS_SY = SHORT_TILE;        // most owned rows
-constexpr int ROWS_WAVES = ROWS_SY + 4;
+static_assert(SHORT_TILE + 4 <= 16, "one wavefront per row within a workgroup");
 
 // stream_row with the vertical links into LDS rows of LROW values (lane t at
 // t + 1, so a diagonal link is read from the neighbouring column), the rest
@@ -978,11 +791,12 @@ template <typename R>
 struct RowShares {
   R *s_up, *s_dn;  // [3][LROW]
   bool has_up, has_dn;
-  R r, x, y;
+  R r, x, b[3];
   __device__ __forceinline__ void up(R o2, R o5, R o6) {
     if (has_up) { s_up[0] = o2; s_up[LROW] = o5; s_up[2 * LROW] = o6; }
   }
-  __device__ __forceinline__ void own(R r_, R x_, R y_) { r = r_; x = x_; y = y_; }
+  __device__ __forceinline__ void own(R r_, R x_) { r = r_; x = x_; }
+  __device__ __forceinline__ void bounced(R r_, R x_, R y_) { b[0] = r_; b[1] = x_; b[2] = y_; }
   __device__ __forceinline__ void down(R o4, R o7, R o8) {
     if (has_dn) { s_dn[0] = o4; s_dn[LROW] = o7; s_dn[2 * LROW] = o8; }
   }
@@ -1046,6 +860,8 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
       for (int q = 0; q < 6; ++q)
         mo[q] = __uint_as_float(load_b32<NT>(rMin, vm, (unsigned)q * PB, crow));
     };
+    // a node solid in state n-1 holds zeros (every step that stores moments
+    // writes them there), so the loads need not wait for the mask
     if (!NT) load_moments(active ? 4u * idx : NONE);
     const lanes_t row = __ballot(m0 & SPREV);
     const Neighbours prev(__ballot(md & SPREV), row, __ballot(mu & SPREV));
@@ -1067,8 +883,6 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
     }
     const Bounce<R> bounce(prev, row);
 #pragma unroll
-    for (int q = 0; q < 6; ++q) mo[q] = fluid ? mo[q] : 0.0f;
-#pragma unroll
     for (int c = 0; c < 2; ++c) {
       sh[c].has_up = k < nrows - 2;
       sh[c].has_dn = k >= 2;
@@ -1077,7 +891,7 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
       stream_row<R>(mo[3 * c], mo[3 * c + 1], mo[3 * c + 2], bounce, sh[c]);
     }
   }
-  lds_barrier(64 * ROWS_WAVES);
+  lds_barrier();
 
   R acc[6], W1[6];
   if (inner) {
@@ -1087,9 +901,9 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
       const R* sd = &s_dn[k - 1][c][t + 1];
       const R a5 = su[LROW - 1], a6 = su[2 * LROW + 1];
       const R u = (su[0] + a5) + a6;
-      acc[3 * c] = u + sh[c].r;
-      acc[3 * c + 1] = (a5 - a6) + sh[c].x;
-      acc[3 * c + 2] = u + sh[c].y;
+      acc[3 * c] = (u + sh[c].r) + sh[c].b[0];
+      acc[3 * c + 1] = ((a5 - a6) + sh[c].x) + sh[c].b[1];
+      acc[3 * c + 2] = u + sh[c].b[2];
       const R a7 = sd[LROW + 1], a8 = sd[2 * LROW - 1];
       const R d = (sd[0] + a7) + a8;
       acc[3 * c] += d;
@@ -1102,7 +916,7 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
     s_rho[k - 1][0][t + 1] = W1[0];
     s_rho[k - 1][1][t + 1] = W1[1];
   }
-  lds_barrier(64 * ROWS_WAVES);
+  lds_barrier();
 
   if (!crow) return;
   bool ev = false;
@@ -1123,6 +937,212 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
   if (REACT) log_events(a, ev, xc, y);
 }
 
+// Keeps the FP64 values of the populations from living on beside the FP32 ones
+// (36 more registers): later uses convert again.
+__device__ __forceinline__ void forget_conversions(float* f) {
+#pragma unroll
+  for (int q = 0; q < 18; ++q) asm volatile("" : "+v"(f[q]));
+}
+
+// Population step (any tau), one wavefront per row: lane t holds column
+// x0 - 1 + t, and a workgroup owns at most the 62 columns of lanes 1..62 and at
+// most POP_ROWS rows (blockIdx.y counts them in taller tiles): wavefront k holds
+// the row below them (k = 0), one of them, or the row above.  Every wavefront loads its row's
+// populations at once, publishes the densities in LDS, and collides and pushes
+// its row (the two halo rows only publish).  The rest population is rho minus
+// the moving ones, so the collision conserves mass exactly.  OUTM (tau = 1
+// only): store the moments (rho_s, v_s) of the collided node, zero at solids,
+// instead of pushing populations.
+//
+// What bounds it: the round trips and the bandwidth of 23 planes read and
+// written.  Rows in parallel put a tile's loads in flight together and 78 VGPRs
+// keep 24 wavefronts per CU; the solute is collided first and the populations
+// are converted again where they are used, which holds the registers there.
+// us per step, against workgroups that marched up their rows (best shape):
+// 1023x1024 preform 33.7 against 42.0, 2048^2 236 against 250, 1024x64
+// capillary 5.8 against 7.2.
+constexpr int POP_ROWS = 14;
+template <bool SOLUTE, bool REACT, bool VAR, typename R, bool OUTM, bool NT>
+__device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, char* lds_raw) {
+  R(*s_rho)[2][LROW] = (R(*)[2][LROW])lds_raw;  // lane t at t + 1
+  const int t = threadIdx.x & 63;
+  const int k = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nx = a.nx, ny = a.ny;
+  const unsigned P = (unsigned)a.P;
+  const int x0 = strip * a.tx_owned;
+  const int nown = min(a.tx_owned, nx - x0);
+  const bool active = t <= nown + 1;
+  const bool owner = t >= 1 && t <= nown;
+  int xc = x0 - 1 + t;
+  if (xc < 0) xc += nx;
+  if (xc >= nx) xc -= nx;
+  const int xl = xc == 0 ? nx - 1 : xc - 1;
+  const int xr = xc == nx - 1 ? 0 : xc + 1;
+  const int ys = seg * a.sy + POP_ROWS * (int)blockIdx.y;
+  const int ye = min((seg + 1) * a.sy, ny);
+  if (ys >= ye) return;  // the whole workgroup
+  const int nrows = min(POP_ROWS, ye - ys) + 2;
+  const bool live = k < nrows;
+  const bool crow = k >= 1 && k < nrows - 1;
+  int y = ys - 1 + k;
+  if (y < 0) y += ny;
+  if (y >= ny) y -= ny;
+  const int yd = y == 0 ? ny - 1 : y - 1, yu = y == ny - 1 ? 0 : y + 1;
+  const unsigned SPREV = 1u | a.bit_p2;    // solid in state n-1
+  const unsigned SCUR = SPREV | a.bit_p1;  // solid in state n
+  const unsigned idx = (unsigned)y * (unsigned)nx + (unsigned)xc;
+  constexpr unsigned NONE = 0xFFFFFFF0u;   // past every extent: reads 0, stores nothing
+  const unsigned PB = P * 4u;
+  // one descriptor per component: nine planes stay below 2^32 bytes
+  const auto rF1 = make_rsrc(a.fin, 9u * PB), rF2 = make_rsrc(a.fin + 9ll * P, 9u * PB);
+  const auto rO1 = make_rsrc(a.fout, 9u * PB), rO2 = make_rsrc(a.fout + 9ll * P, 9u * PB);
+  const auto rGin = make_rsrc(a.gin, SOLUTE ? 5u * PB : 0u);
+  const auto rGout = make_rsrc(a.gout, SOLUTE ? 5u * PB : 0u);
+  const auto rMask = make_rsrc(a.mask, P);
+  const auto rPrec = make_rsrc(a.m, REACT ? 2u * PB : 0u);
+  auto store = [](__amdgpu_buffer_rsrc_t r, R v, unsigned voff, unsigned soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)v), r, (int)voff, (int)soff, 0);
+  };
+
+  float f[18], g[5];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) g[q] = 0.0f;
+  v2u pr = {0u, 0u};
+  unsigned m0 = 1, md = 1, mu = 1;
+  R rho1 = R(0), rho2 = R(0);
+  if (live) {
+    auto mask_of = [&](unsigned row) -> unsigned {
+      const unsigned v = (unsigned)__builtin_amdgcn_raw_buffer_load_b8(
+          rMask, (int)(active ? row * (unsigned)nx + (unsigned)xc : NONE), 0, 0);
+      return active ? v : 1u;
+    };
+    m0 = mask_of((unsigned)y);
+    if (crow) {
+      md = mask_of((unsigned)yd);
+      mu = mask_of((unsigned)yu);
+    }
+    const unsigned vf = m0 & SPREV ? NONE : 4u * idx;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) f[q] = __uint_as_float(load_b32<NT>(rF1, vf, (unsigned)q * PB, true));
+#pragma unroll
+    for (int q = 0; q < 9; ++q) f[9 + q] = __uint_as_float(load_b32<NT>(rF2, vf, (unsigned)q * PB, true));
+    if (crow) {
+      if (SOLUTE) {
+        const unsigned vg = owner ? vf : NONE;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) g[q] = __uint_as_float(load_b32<NT>(rGin, vg, (unsigned)q * PB, true));
+      }
+      if (REACT) {
+        const lanes_t here = __ballot(m0 & SCUR);
+        const lanes_t wall = (here >> 1) | (here << 1) | __ballot(md & SCUR) | __ballot(mu & SCUR);
+        pr = __builtin_amdgcn_raw_buffer_load_b64(
+            rPrec, (int)(owner && on_lane(wall & ~here) ? 8u * idx : NONE), 0, 0);
+      }
+    }
+    if (!(m0 & SCUR)) {
+      rho1 = sum9<R>(f);
+      rho2 = sum9<R>(f + 9);
+    }
+    s_rho[k][0][t + 1] = rho1;
+    s_rho[k][1][t + 1] = rho2;
+  }
+  lds_barrier();
+  if (!crow) return;
+  forget_conversions(f);
+
+  bool ev = false;
+  const Neighbours cur(__ballot(md & SCUR), __ballot(m0 & SCUR), __ballot(mu & SCUR));
+  if (owner) {
+    if (m0 & SCUR) {
+      if (REACT) {
+        if (m0 & a.bit_p1) {
+          // turned solid at the end of the previous step: book its populations
+          a.drop[idx] = (float)sum9<R>(f);
+          a.drop[P + idx] = (float)sum9<R>(f + 9);
+          a.drop[2 * P + idx] =
+              SOLUTE ? (float)((((R)g[0] + (R)g[1]) + ((R)g[2] + (R)g[3])) + (R)g[4]) : 0.0f;
+        } else if (m0 & a.bit_p2) {
+          a.mask[idx] = 1;  // booked one step ago: fold the mark into bit0
+        }
+      }
+      if (OUTM) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) store(rO1, R(0), 4u * idx, (unsigned)q * PB);
+      }
+    } else {
+      const R* up = &s_rho[k + 1][0][t + 1];
+      const R* at = &s_rho[k][0][t + 1];
+      const R* dn = &s_rho[k - 1][0][t + 1];
+      const R n1[9] = {R(0), at[1], up[0], at[-1], dn[0], up[1], up[-1], dn[-1], dn[1]};
+      const R n2[9] = {R(0), at[LROW + 1], up[LROW], at[LROW - 1], dn[LROW], up[LROW + 1],
+                       up[LROW - 1], dn[LROW - 1], dn[LROW + 1]};
+      bool wall[9];
+#pragma unroll
+      for (int i = 1; i < 9; ++i) wall[i] = on_lane(cur.n[i]);
+      R csx, csy;
+      wall_links<R>(cur, csx, csy);
+      R F1x, F1y, F2x, F2y;
+      sc_forces<R>(a, n1, n2, csx, csy, rho1, rho2, F1x, F1y, F2x, F2y);
+      const R j1x = ((R)f[1] - (R)f[3]) + ((R)f[5] - (R)f[6]) + ((R)f[8] - (R)f[7]);
+      const R j1y = ((R)f[2] - (R)f[4]) + ((R)f[5] + (R)f[6]) - ((R)f[7] + (R)f[8]);
+      const R j2x = ((R)f[10] - (R)f[12]) + ((R)f[14] - (R)f[15]) + ((R)f[17] - (R)f[16]);
+      const R j2y = ((R)f[11] - (R)f[13]) + ((R)f[14] + (R)f[15]) - ((R)f[16] + (R)f[17]);
+      R v1x, v1y, v2x, v2y, ux, uy, irt;
+      sc_velocities<R>((R)a.tau, rho1, rho2, j1x, j1y, j2x, j2y, F1x, F1y, F2x, F2y, v1x, v1y, v2x,
+                       v2y, ux, uy, irt);
+      const unsigned iE = (unsigned)y * nx + xr, iW = (unsigned)y * nx + xl;
+      const unsigned iN = (unsigned)yu * nx + xc, iS = (unsigned)yd * nx + xc;
+      if (SOLUTE) {
+        SoluteOut so;
+        solute_step<REACT, VAR, R>(a, g, ux, uy, rho1, rho2, irt, wall,
+                                   __hiloint2double((int)pr.y, (int)pr.x), P, idx, iE, iN, iW, iS, xc, ev,
+                                   so);
+        store_solute<REACT>(so, rGout, rPrec, idx);
+      }
+      if (OUTM) {
+        const R mo[6] = {rho1, v1x, v1y, rho2, v2x, v2y};
+#pragma unroll
+        for (int q = 0; q < 6; ++q) store(rO1, mo[q], 4u * idx, (unsigned)q * PB);
+      } else {
+        const unsigned iNE = (unsigned)yu * nx + xr, iNW = (unsigned)yu * nx + xl;
+        const unsigned iSW = (unsigned)yd * nx + xl, iSE = (unsigned)yd * nx + xr;
+        const R om = (R)a.omega;
+        forget_conversions(f);
+        // collide one component and push each moving population as soon as
+        // it is formed (halfway bounce-back into the node's own opposite
+        // link at a solid neighbour); the rest population closes the mass
+        // balance exactly (the moving-link weights are not exact binary
+        // fractions)
+        auto collide_push = [&](const float* fc, __amdgpu_buffer_rsrc_t r, R rho, R vx, R vy) {
+          const R uu = vx * vx + vy * vy;
+          R sum = R(0);
+#define CP(i, opp, w, eu, tgt)                                              \
+  do {                                                                      \
+    const R fi = (R)fc[i];                                                  \
+    const R v = fi + om * (feq<R>(w, rho, eu, uu) - fi);                    \
+    sum += v;                                                               \
+    store(r, v, wall[i] ? (opp) * PB + 4u * idx : (i) * PB + 4u * (tgt), 0);  \
+  } while (0)
+          const R WA = R(1) / R(9), WD = R(1) / R(36);
+          CP(1, 3, WA, vx, iE);
+          CP(2, 4, WA, vy, iN);
+          CP(3, 1, WA, -vx, iW);
+          CP(4, 2, WA, -vy, iS);
+          CP(5, 7, WD, vx + vy, iNE);
+          CP(6, 8, WD, -vx + vy, iNW);
+          CP(7, 5, WD, -vx - vy, iSW);
+          CP(8, 6, WD, vx - vy, iSE);
+#undef CP
+          store(r, rho - sum, 4u * idx, 0);
+        };
+        collide_push(f, rO1, rho1, v1x, v1y);
+        collide_push(f + 9, rO2, rho2, v2x, v2y);
+      }
+    }
+  }
+  if (REACT) log_events(a, ev, xc, y);
+}
+
 // XCD-aware order: the hardware hands block b to XCD b mod 8, so XCD x
 // receives q + (x < r) of T blocks (q = T / 8, r = T mod 8).  Give each XCD a
 // contiguous run of tiles.  Tiles are numbered segment-major, so a run is a
@@ -1136,19 +1156,19 @@ __host__ __device__ inline int xcd_tile(int b, int T) {
 
 template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT>
 __device__ __forceinline__ void run_tile(const StepArgs& a, int strip, int seg, char* lds_raw) {
-  if (KIND == KIND_MM)
+  if constexpr (KIND == KIND_MM)
     mom_wave<SOLUTE, REACT, VAR, R, NT>(a, strip, seg);
-  else if (KIND == KIND_MM_SHORT)
+  else if constexpr (KIND == KIND_MM_SHORT)
     mom_rows<SOLUTE, REACT, VAR, R, NT>(a, strip, seg, lds_raw);
   else
-    step_tile<SOLUTE, REACT, VAR, R, KIND == KIND_PM, NT>(a, strip, seg, lds_raw);
+    pop_rows<SOLUTE, REACT, VAR, R, KIND == KIND_PM, NT>(a, strip, seg, lds_raw);
 }
 
 // Largest workgroup and register budget (waves per SIMD) of each kind.
 template <int KIND>
-constexpr int max_threads() { return KIND == KIND_MM_SHORT ? 64 * ROWS_WAVES : 256; }
+constexpr int max_threads() { return KIND == KIND_MM ? 64 : 64 * 16; }
 template <int KIND>
-constexpr int min_waves() { return KIND == KIND_MM_SHORT ? 6 : 3; }
+constexpr int min_waves() { return KIND == KIND_MM ? 3 : 6; }
 
 template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT>
 __global__ void __launch_bounds__(max_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(min_waves<KIND>(), 8)))
@@ -1640,17 +1660,22 @@ __global__ void k_unpack(MomSrc src, float* __restrict__ fout) {
 }
 
 // ---- launchers ------------------------------------------------------------
-size_t step_lds_bytes(int kind, int tx) {
-  if (kind == KIND_MM) return 0;  // static
-  if (kind == KIND_MM_SHORT)      // see mom_rows
-    return (size_t)(tx / 64 - 2) * (2 * 6 + 2) * LROW * sizeof(double);
-  return (size_t)4 * tx * (2 * sizeof(double) + sizeof(float));
+// Threads per workgroup: one wavefront per tile in the moment step, one per
+// row (halo rows included) otherwise.
+static int step_threads(int kind, int sy) {
+  return kind == KIND_MM ? 64 : 64 * (kind == KIND_MM_SHORT ? sy + 4 : (sy < POP_ROWS ? sy : POP_ROWS) + 2);
 }
 
-// Threads per workgroup: one wavefront per tile in the moment step, one per
-// row in its short tiles.
-int step_threads(int kind, int tx, int sy) {
-  return kind == KIND_MM ? 64 : kind == KIND_MM_SHORT ? 64 * (sy + 4) : tx;
+// LDS beyond the static part: see mom_rows and pop_rows.
+static size_t step_lds_bytes(int kind, int threads) {
+  if (kind == KIND_MM) return 0;
+  const size_t rows = threads / 64;
+  return (kind == KIND_MM_SHORT ? (rows - 2) * (2 * 6 + 2) : rows * 2) * LROW * sizeof(double);
+}
+
+// Workgroups of T tiles: a population tile taller than POP_ROWS takes several.
+static dim3 step_grid(int kind, int sy, int T) {
+  return dim3(T, kind == KIND_POP || kind == KIND_PM ? (sy + POP_ROWS - 1) / POP_ROWS : 1);
 }
 
 // Runs that use a reaction or solute-lattice variant (saturation, held
@@ -1661,62 +1686,59 @@ inline bool uses_variants(const StepArgs& a) { return a.c_eq > 0.0 || a.hold_x >
 template <typename R, int KIND, bool NT>
 void launch_step_t(const StepArgs& a, int T, int tx, size_t lds, hipStream_t st) {
   if (a.solute && a.react && uses_variants(a))
-    hipLaunchKernelGGL((k_step<true, true, true, R, KIND, NT>), dim3(T), dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, true, true, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute && a.react)
-    hipLaunchKernelGGL((k_step<true, true, false, R, KIND, NT>), dim3(T), dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, true, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute && uses_variants(a))
-    hipLaunchKernelGGL((k_step<true, false, true, R, KIND, NT>), dim3(T), dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, false, true, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute)
-    hipLaunchKernelGGL((k_step<true, false, false, R, KIND, NT>), dim3(T), dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, false, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else
-    hipLaunchKernelGGL((k_step<false, false, false, R, KIND, NT>), dim3(T), dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<false, false, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
 }
 
 // nt: the non-temporal load hint, compiled for the moment and population
 // steps (the one-off PM step ignores it).  The arithmetic is FP64 throughout.
-hipError_t launch_step(const StepArgs& a, int tx, int kind, int nt, hipStream_t st) {
+hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st) {
   const int T = a.nstrips * a.nsegs;
-  tx = step_threads(kind, tx, a.sy);
+  const int tx = step_threads(kind, a.sy);
   const size_t lds = step_lds_bytes(kind, tx);
-  if (kind == KIND_MM_SHORT) {
-    if (nt) launch_step_t<double, KIND_MM_SHORT, true>(a, T, tx, lds, st);
-    else launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st);
-  } else if (kind == KIND_MM) {
-    if (nt) launch_step_t<double, KIND_MM, true>(a, T, tx, lds, st);
-    else launch_step_t<double, KIND_MM, false>(a, T, tx, lds, st);
-  } else if (kind == KIND_PM) {
-    launch_step_t<double, KIND_PM, false>(a, T, tx, lds, st);
-  } else {
-    if (nt) launch_step_t<double, KIND_POP, true>(a, T, tx, lds, st);
-    else launch_step_t<double, KIND_POP, false>(a, T, tx, lds, st);
+  switch (kind + (nt ? 8 : 0)) {
+    case KIND_MM: launch_step_t<double, KIND_MM, false>(a, T, tx, lds, st); break;
+    case KIND_MM + 8: launch_step_t<double, KIND_MM, true>(a, T, tx, lds, st); break;
+    case KIND_MM_SHORT: launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st); break;
+    case KIND_MM_SHORT + 8: launch_step_t<double, KIND_MM_SHORT, true>(a, T, tx, lds, st); break;
+    case KIND_POP: launch_step_t<double, KIND_POP, false>(a, T, tx, lds, st); break;
+    case KIND_POP + 8: launch_step_t<double, KIND_POP, true>(a, T, tx, lds, st); break;
+    default: launch_step_t<double, KIND_PM, false>(a, T, tx, lds, st);
   }
   return hipGetLastError();
 }
 
 template <typename R, int KIND>
 void launch_batch_t(const StepArgs* insts, const int4* tiles, int ntiles, const long long* stepc,
-                    int j, int tx, int solute, int react, int var, size_t lds, hipStream_t st) {
+                    int j, int sy, int tx, int solute, int react, int var, size_t lds, hipStream_t st) {
   if (solute && react && var)
-    hipLaunchKernelGGL((k_step_batch<true, true, true, R, KIND>), dim3(ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, true, true, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute && react)
-    hipLaunchKernelGGL((k_step_batch<true, true, false, R, KIND>), dim3(ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, true, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute && var)
-    hipLaunchKernelGGL((k_step_batch<true, false, true, R, KIND>), dim3(ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, false, true, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute)
-    hipLaunchKernelGGL((k_step_batch<true, false, false, R, KIND>), dim3(ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, false, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else
-    hipLaunchKernelGGL((k_step_batch<false, false, false, R, KIND>), dim3(ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<false, false, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
 }
 
 hipError_t launch_step_batch(const StepArgs* insts, const int4* tiles, int ntiles,
-                             const long long* stepc, int j, int tx, int sy, int solute, int react,
-                             int var, int kind, hipStream_t st) {
-  tx = step_threads(kind, tx, sy);
+                             const long long* stepc, int j, int sy, int solute, int react, int var,
+                             int kind, hipStream_t st) {
+  const int tx = step_threads(kind, sy);
   const size_t lds = step_lds_bytes(kind, tx);
-  if (kind == KIND_MM_SHORT) launch_batch_t<double, KIND_MM_SHORT>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
-  else if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
-  else if (kind == KIND_PM) launch_batch_t<double, KIND_PM>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
-  else launch_batch_t<double, KIND_POP>(insts, tiles, ntiles, stepc, j, tx, solute, react, var, lds, st);
+  if (kind == KIND_MM_SHORT) launch_batch_t<double, KIND_MM_SHORT>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else if (kind == KIND_PM) launch_batch_t<double, KIND_PM>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else launch_batch_t<double, KIND_POP>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
   return hipGetLastError();
 }
 
