@@ -937,13 +937,6 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
   if (REACT) log_events(a, ev, xc, y);
 }
 
-// Keeps the FP64 values of the populations from living on beside the FP32 ones
-// (36 more registers): later uses convert again.
-__device__ __forceinline__ void forget_conversions(float* f) {
-#pragma unroll
-  for (int q = 0; q < 18; ++q) asm volatile("" : "+v"(f[q]));
-}
-
 // Population step (any tau), one wavefront per row: lane t holds column
 // x0 - 1 + t, and a workgroup owns at most the 62 columns of lanes 1..62 and at
 // most POP_ROWS rows (blockIdx.y counts them in taller tiles): wavefront k holds
@@ -955,18 +948,26 @@ __device__ __forceinline__ void forget_conversions(float* f) {
 // instead of pushing populations.
 //
 // What bounds it: the round trips and the bandwidth of 23 planes read and
-// written.  Rows in parallel put a tile's loads in flight together and 78 VGPRs
-// keep 24 wavefronts per CU; the solute is collided first and the populations
-// are converted again where they are used, which holds the registers there.
-// us per step, against workgroups that marched up their rows (best shape):
-// 1023x1024 preform 33.7 against 42.0, 2048^2 236 against 250, 1024x64
-// capillary 5.8 against 7.2.
+// written.  Rows in parallel put a tile's loads in flight together.  The
+// densities and momenta are summed as the populations arrive, and the
+// populations then wait in LDS until the collision takes them one by one: 78
+// VGPRs and no spill keep 24 wavefronts per CU (held in registers they spilled:
+// 1023x1024 41.0 us per step against 34.2 at six rows, 700x500 16.5 against
+// 14.6, 2048^2 258 against 245).  us per step, against workgroups that marched
+// up their rows (best shape): 1023x1024 preform 34.2 against 42.0, 2048^2 237
+// against 250 (hint), 1024x64 capillary 6.2 against 7.2.
 constexpr int POP_ROWS = 14;
+// What a wavefront of pop_rows keeps in LDS: its row's densities, lane t at
+// t + 1, for the neighbouring rows, and its own lanes' populations.
+struct PopRow {
+  double rho[2][LROW];
+  float f[18][64];
+};
 template <bool SOLUTE, bool REACT, bool VAR, typename R, bool OUTM, bool NT>
 __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, char* lds_raw) {
-  R(*s_rho)[2][LROW] = (R(*)[2][LROW])lds_raw;  // lane t at t + 1
   const int t = threadIdx.x & 63;
   const int k = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  PopRow* const row = (PopRow*)lds_raw + k;
   const int nx = a.nx, ny = a.ny;
   const unsigned P = (unsigned)a.P;
   const int x0 = strip * a.tx_owned;
@@ -1004,16 +1005,17 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)v), r, (int)voff, (int)soff, 0);
   };
 
-  float f[18], g[5];
+  float g[5];
 #pragma unroll
   for (int q = 0; q < 5; ++q) g[q] = 0.0f;
   v2u pr = {0u, 0u};
   unsigned m0 = 1, md = 1, mu = 1;
-  R rho1 = R(0), rho2 = R(0);
+  R rho1 = R(0), rho2 = R(0), j1x = R(0), j1y = R(0), j2x = R(0), j2y = R(0);
   if (live) {
-    auto mask_of = [&](unsigned row) -> unsigned {
+    float f[18];
+    auto mask_of = [&](unsigned yr) -> unsigned {
       const unsigned v = (unsigned)__builtin_amdgcn_raw_buffer_load_b8(
-          rMask, (int)(active ? row * (unsigned)nx + (unsigned)xc : NONE), 0, 0);
+          rMask, (int)(active ? yr * (unsigned)nx + (unsigned)xc : NONE), 0, 0);
       return active ? v : 1u;
     };
     m0 = mask_of((unsigned)y);
@@ -1043,12 +1045,20 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
       rho1 = sum9<R>(f);
       rho2 = sum9<R>(f + 9);
     }
-    s_rho[k][0][t + 1] = rho1;
-    s_rho[k][1][t + 1] = rho2;
+    row->rho[0][t + 1] = rho1;
+    row->rho[1][t + 1] = rho2;
+    if (crow) {
+      j1x = ((R)f[1] - (R)f[3]) + ((R)f[5] - (R)f[6]) + ((R)f[8] - (R)f[7]);
+      j1y = ((R)f[2] - (R)f[4]) + ((R)f[5] + (R)f[6]) - ((R)f[7] + (R)f[8]);
+      j2x = ((R)f[10] - (R)f[12]) + ((R)f[14] - (R)f[15]) + ((R)f[17] - (R)f[16]);
+      j2y = ((R)f[11] - (R)f[13]) + ((R)f[14] + (R)f[15]) - ((R)f[16] + (R)f[17]);
+#pragma unroll
+      for (int q = 0; q < 18; ++q) row->f[q][t] = f[q];
+    }
   }
   lds_barrier();
   if (!crow) return;
-  forget_conversions(f);
+  auto pop = [&](int q) { return (R)row->f[q][t]; };
 
   bool ev = false;
   const Neighbours cur(__ballot(md & SCUR), __ballot(m0 & SCUR), __ballot(mu & SCUR));
@@ -1057,6 +1067,9 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
       if (REACT) {
         if (m0 & a.bit_p1) {
           // turned solid at the end of the previous step: book its populations
+          float f[18];
+#pragma unroll
+          for (int q = 0; q < 18; ++q) f[q] = row->f[q][t];
           a.drop[idx] = (float)sum9<R>(f);
           a.drop[P + idx] = (float)sum9<R>(f + 9);
           a.drop[2 * P + idx] =
@@ -1070,9 +1083,9 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
         for (int q = 0; q < 6; ++q) store(rO1, R(0), 4u * idx, (unsigned)q * PB);
       }
     } else {
-      const R* up = &s_rho[k + 1][0][t + 1];
-      const R* at = &s_rho[k][0][t + 1];
-      const R* dn = &s_rho[k - 1][0][t + 1];
+      const R* up = &row[1].rho[0][t + 1];
+      const R* at = &row[0].rho[0][t + 1];
+      const R* dn = &row[-1].rho[0][t + 1];
       const R n1[9] = {R(0), at[1], up[0], at[-1], dn[0], up[1], up[-1], dn[-1], dn[1]};
       const R n2[9] = {R(0), at[LROW + 1], up[LROW], at[LROW - 1], dn[LROW], up[LROW + 1],
                        up[LROW - 1], dn[LROW - 1], dn[LROW + 1]};
@@ -1083,10 +1096,6 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
       wall_links<R>(cur, csx, csy);
       R F1x, F1y, F2x, F2y;
       sc_forces<R>(a, n1, n2, csx, csy, rho1, rho2, F1x, F1y, F2x, F2y);
-      const R j1x = ((R)f[1] - (R)f[3]) + ((R)f[5] - (R)f[6]) + ((R)f[8] - (R)f[7]);
-      const R j1y = ((R)f[2] - (R)f[4]) + ((R)f[5] + (R)f[6]) - ((R)f[7] + (R)f[8]);
-      const R j2x = ((R)f[10] - (R)f[12]) + ((R)f[14] - (R)f[15]) + ((R)f[17] - (R)f[16]);
-      const R j2y = ((R)f[11] - (R)f[13]) + ((R)f[14] + (R)f[15]) - ((R)f[16] + (R)f[17]);
       R v1x, v1y, v2x, v2y, ux, uy, irt;
       sc_velocities<R>((R)a.tau, rho1, rho2, j1x, j1y, j2x, j2y, F1x, F1y, F2x, F2y, v1x, v1y, v2x,
                        v2y, ux, uy, irt);
@@ -1107,18 +1116,17 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
         const unsigned iNE = (unsigned)yu * nx + xr, iNW = (unsigned)yu * nx + xl;
         const unsigned iSW = (unsigned)yd * nx + xl, iSE = (unsigned)yd * nx + xr;
         const R om = (R)a.omega;
-        forget_conversions(f);
         // collide one component and push each moving population as soon as
         // it is formed (halfway bounce-back into the node's own opposite
         // link at a solid neighbour); the rest population closes the mass
         // balance exactly (the moving-link weights are not exact binary
         // fractions)
-        auto collide_push = [&](const float* fc, __amdgpu_buffer_rsrc_t r, R rho, R vx, R vy) {
+        auto collide_push = [&](int q0, __amdgpu_buffer_rsrc_t r, R rho, R vx, R vy) {
           const R uu = vx * vx + vy * vy;
           R sum = R(0);
 #define CP(i, opp, w, eu, tgt)                                              \
   do {                                                                      \
-    const R fi = (R)fc[i];                                                  \
+    const R fi = pop(q0 + i);                                                \
     const R v = fi + om * (feq<R>(w, rho, eu, uu) - fi);                    \
     sum += v;                                                               \
     store(r, v, wall[i] ? (opp) * PB + 4u * idx : (i) * PB + 4u * (tgt), 0);  \
@@ -1135,8 +1143,8 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
 #undef CP
           store(r, rho - sum, 4u * idx, 0);
         };
-        collide_push(f, rO1, rho1, v1x, v1y);
-        collide_push(f + 9, rO2, rho2, v2x, v2y);
+        collide_push(0, rO1, rho1, v1x, v1y);
+        collide_push(9, rO2, rho2, v2x, v2y);
       }
     }
   }
@@ -1670,7 +1678,7 @@ static int step_threads(int kind, int sy) {
 static size_t step_lds_bytes(int kind, int threads) {
   if (kind == KIND_MM) return 0;
   const size_t rows = threads / 64;
-  return (kind == KIND_MM_SHORT ? (rows - 2) * (2 * 6 + 2) : rows * 2) * LROW * sizeof(double);
+  return kind == KIND_MM_SHORT ? (rows - 2) * (2 * 6 + 2) * LROW * sizeof(double) : rows * sizeof(PopRow);
 }
 
 // Workgroups of T tiles: a population tile taller than POP_ROWS takes several.
