@@ -9,9 +9,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
+#include "host_copy.h"
 #include "lbm.h"
 #include "lbm_dev.h"
 
@@ -131,6 +133,7 @@ struct lbm_sim {
   int scheme;      // LBM_SCHEME_*
   bool mom;        // f[cur] holds moments of the last step, not populations
   bool poisoned;
+  HostCopy copy;   // of fields
   float* f(int i) const { return (float*)(ws + L.f[i]); }
   float* g(int i) const { return L.solute ? (float*)(ws + L.g[i]) : nullptr; }
   uint8_t* mask() const { return (uint8_t*)(ws + L.mask); }
@@ -343,7 +346,7 @@ lbm_status lbm_init(const lbm_params* p, const uint8_t* solid, const double* rho
     if (solute && (!(conc[i] >= 0.0) || !std::isfinite(conc[i])))
       return fail(LBM_EINVAL, "concentration at node %lld must be finite and >= 0", i);
   }
-  lbm_sim* s = (lbm_sim*)calloc(1, sizeof(lbm_sim));
+  lbm_sim* s = new (std::nothrow) lbm_sim();
   if (!s) return fail(LBM_ENOMEM, "handle allocation");
   s->p = *p;
   s->L = L;
@@ -358,7 +361,7 @@ lbm_status lbm_init(const lbm_params* p, const uint8_t* solid, const double* rho
   // stage the FP64 inputs in the second population buffer (72 B per node)
   char* stage = (char*)s->f(1);
   hipStream_t hs = s->stream;
-  auto bail = [&](lbm_status e) { free(s); return e; };
+  auto bail = [&](lbm_status e) { delete s; return e; };
 #define CK(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) { fail(LBM_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); return bail(LBM_EDEVICE); } } while (0)
   CK(hipMemcpyAsync(stage, rho1, N * sizeof(double), hipMemcpyHostToDevice, hs));
   CK(hipMemcpyAsync(stage + N * sizeof(double), rho2, N * sizeof(double), hipMemcpyHostToDevice, hs));
@@ -435,10 +438,9 @@ lbm_status lbm_fields(lbm_sim* s, uint32_t mask, double* host) {
                                pending_bit(s->step - 1), pending_bit(s->step - 2), s->mom,
                                s->L.solute, s->L.react, p.G, p.G_ads[0], p.G_ads[1],
                                p.accel[0], p.accel[1], mask, stage, s->stream);
-  if (e == hipSuccess && mask)
-    e = hipMemcpyAsync(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double),
-                       hipMemcpyDeviceToHost, s->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  if (e == hipSuccess)
+    e = mask ? s->copy.to_host(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double), s->stream)
+             : hipStreamSynchronize(s->stream);
   if (e != hipSuccess) { s->poisoned = true; return fail(LBM_EDEVICE, "fields: %s", hipGetErrorString(e)); }
   return LBM_OK;
 }
@@ -772,7 +774,7 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
   return LBM_OK;
 }
 
-void lbm_destroy(lbm_sim* s) { free(s); }
+void lbm_destroy(lbm_sim* s) { delete s; }
 
 }  // extern "C"
 
@@ -808,6 +810,7 @@ struct lbm_batch {
   int graph_chunk;
   hipGraphExec_t graph;
   hipStream_t cap_stream;     // library-owned stream used only to capture the graph
+  HostCopy copy;              // of fields
 };
 
 namespace {
@@ -1238,10 +1241,9 @@ lbm_status lbm_batch_fields(lbm_batch* b, int32_t i, uint32_t mask, double* host
                                pending_bit(b->step - 1), pending_bit(b->step - 2), b->mom,
                                b->L[i].solute, b->L[i].react, p.G, p.G_ads[0], p.G_ads[1],
                                p.accel[0], p.accel[1], mask, stage, b->stream);
-  if (e == hipSuccess && mask)
-    e = hipMemcpyAsync(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double),
-                       hipMemcpyDeviceToHost, b->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+  if (e == hipSuccess)
+    e = mask ? b->copy.to_host(host, stage, (size_t)__builtin_popcount(mask) * N * sizeof(double), b->stream)
+             : hipStreamSynchronize(b->stream);
   if (e != hipSuccess) { b->poisoned = true; return fail(LBM_EDEVICE, "batch fields: %s", hipGetErrorString(e)); }
   return LBM_OK;
 }
