@@ -91,9 +91,11 @@ __device__ __forceinline__ void store_transposed(__bf16* frags, int ks, int tile
 // layer are requested two layers ahead of their use.  32 samples is the
 // matrix instruction's tile; fewer workgroups than CUs run for small batches.
 // Measured: 5.6 us for 8 prediction rows (33 us as six launches and a copy),
-// 16.0 us for a training minibatch of 256, which with k_update's 6.4 us took
-// 21 launches and 120 us when every layer product, bias sum and update was a
-// launch of its own.
+// 13.1 us for a training minibatch of 256 (16.0 when the targets' loads went row
+// by row behind the weights, the loss branched for each element and its sum
+// was folded before the backward pass), which with k_update's 6.4 us took 21
+// launches and 120 us when every layer product, bias sum and update was a launch
+// of its own.
 template <bool TRAIN>
 __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs ra,
                                               const TrainArgs ta, float* __restrict__ y) {
@@ -108,35 +110,73 @@ __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs r
   const int r0 = blockIdx.x * ROWS;
   const int unit = 32 * wave + col;
 
+  auto normalise = [](int j, float x, float lo, float hi) {
+    if (j == 2) { x = log10f(x); lo = log10f(lo); hi = log10f(hi); }
+    return 2.0f * (x - lo) / (hi - lo) - 1.0f;
+  };
+  constexpr int YI = (ROWS * NOUT + 511) / 512;
+  const int tid = threadIdx.x;
+  auto target = [&](int i) { return min(tid + 512 * i, ROWS * NOUT - 1); };
   bf16x8 w0[2], wa[16], wb[16];
-  load_frags<2>(w0, net.wf[0], wave, lane);
-  load_frags<16>(wa, net.wf[1], wave, lane);
-  float bias[NL];
+  float bias[NL], lw = 0.0f, yv[YI], cv = 1.0f;
+  auto load_biases = [&]() {
 #pragma unroll
-  for (int l = 0; l < 3; ++l) bias[l] = net.bias[l][unit];
-  bias[3] = wave < 3 ? net.bias[3][unit] : 0.0f;
-
-  for (int e = threadIdx.x; e < ROWS * KIN; e += 512) {
-    const int r = e / KIN, j = e % KIN;
-    float v = 0.0f;
-    if (r0 + r < ra.rows && j < NIN) {
-      const int src = ra.idx ? ra.idx[r0 + r] : r0 + r;
-      float x = ra.X[(size_t)src * NIN + j], a = net.lo[j], b = net.hi[j];
-      if (j == 2) { x = log10f(x); a = log10f(a); b = log10f(b); }
-      v = 2.0f * (x - a) / (b - a) - 1.0f;
+    for (int l = 0; l < 3; ++l) bias[l] = net.bias[l][unit];
+    bias[3] = wave < 3 ? net.bias[3][unit] : 0.0f;
+  };
+  if constexpr (TRAIN) {
+    // A wavefront's loads return in the order they were requested: the rows'
+    // indices come first, then the inputs and targets that hang on them, then
+    // the weights.  Rows beyond the last sample read the last one's, unused.
+    constexpr int XI = ROWS * KIN / 512;
+    static_assert(KIN == 32 && XI * 512 == ROWS * KIN, "thread t loads input t mod 32 of row t / 32 + 16 i");
+    auto source = [&](int r) {
+      const int at = min(r0 + r, ra.rows - 1);
+      return ra.idx ? ra.idx[at] : at;
+    };
+    int xsrc[XI], ysrc[YI];
+#pragma unroll
+    for (int i = 0; i < XI; ++i) xsrc[i] = source((tid >> 5) + 16 * i);
+#pragma unroll
+    for (int i = 0; i < YI; ++i) ysrc[i] = source(target(i) / NOUT);
+    const int csrc = ta.RW ? source(tid & (ROWS - 1)) : 0;
+    const int j = tid & 31, jin = min(j, NIN - 1);
+    const float lo = net.lo[jin], hi = net.hi[jin];
+    load_biases();
+    if (unit < NOUT) lw = ta.lw[unit];
+    load_frags<2>(w0, net.wf[0], wave, lane);
+    float xv[XI];
+#pragma unroll
+    for (int i = 0; i < XI; ++i) xv[i] = ra.X[(size_t)xsrc[i] * NIN + jin];
+#pragma unroll
+    for (int i = 0; i < YI; ++i) yv[i] = ta.Y[(size_t)ysrc[i] * NOUT + target(i) % NOUT];
+    if (ta.RW) cv = ta.RW[csrc];
+    load_frags<16>(wa, net.wf[1], wave, lane);
+#pragma unroll
+    for (int i = 0; i < XI; ++i) {
+      asm volatile("" : "+v"(xv[i]));  // keeps the load where it was requested
+      const int r = (tid >> 5) + 16 * i;
+      const __bf16 v = (__bf16)(r0 + r < ra.rows && j < NIN ? normalise(j, xv[i], lo, hi) : 0.0f);
+      sx[r * XS + j] = v;
+      // samples as contraction: unit j, sample r of block blockIdx.x
+      ta.at[0][((size_t)2 * blockIdx.x + (r >> 4)) * 512 + (((r >> 3) & 1) * 32 + j) * 8 + (r & 7)] = v;
     }
-    sx[r * XS + j] = (__bf16)v;
-    if (TRAIN)  // samples as contraction: unit j, sample r of block blockIdx.x
-      ta.at[0][((size_t)2 * blockIdx.x + (r >> 4)) * 512 + (((r >> 3) & 1) * 32 + j) * 8 + (r & 7)] = (__bf16)v;
-  }
-  if (TRAIN) {
-    // requested with the inputs, so the loss waits on no further round trip
-    for (int e = threadIdx.x; e < ROWS * NOUT; e += 512) {
-      const int r = r0 + e / NOUT;
-      if (r < ra.rows) st[e] = ta.Y[(size_t)(ra.idx ? ra.idx[r] : r) * NOUT + e % NOUT];
+  } else {
+    // a prediction's inputs hang on nothing, and few rows leave whole
+    // wavefronts without any: weights first (8 rows: 5.7 us; 5.9 to 6.2 with
+    // every wavefront's inputs requested before the second layer's weights)
+    load_frags<2>(w0, net.wf[0], wave, lane);
+    load_frags<16>(wa, net.wf[1], wave, lane);
+    load_biases();
+    for (int e = tid; e < ROWS * KIN; e += 512) {
+      const int r = e / KIN, j = e % KIN;
+      float v = 0.0f;
+      if (r0 + r < ra.rows && j < NIN) {
+        const int src = ra.idx ? ra.idx[r0 + r] : r0 + r;
+        v = normalise(j, ra.X[(size_t)src * NIN + j], net.lo[j], net.hi[j]);
+      }
+      sx[r * XS + j] = (__bf16)v;
     }
-    const int r = r0 + (int)threadIdx.x;
-    if (threadIdx.x < ROWS && r < ra.rows) sc[threadIdx.x] = ta.RW ? ta.RW[ra.idx ? ra.idx[r] : r] : 1.0f;
   }
   load_frags<16>(wb, net.wf[2], wave, lane);
   __syncthreads();
@@ -157,6 +197,11 @@ __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs r
     if (TRAIN) store_transposed(ta.at[l + 1], ta.ks, wave, blockIdx.x, h, lane);
   };
   hidden(product<2>(sx, XS, w0, lane), 0, sa);
+  if (TRAIN) {
+#pragma unroll
+    for (int i = 0; i < YI; ++i) st[target(i)] = yv[i];  // the last threads write one target's value twice
+    if (tid < ROWS) sc[tid] = cv;
+  }
   __syncthreads();
   hidden(product<16>(sa, HS, wa, lane), 1, sb);
   if (wave < 3) load_frags<16>(wa, net.wf[3], wave, lane);
@@ -167,6 +212,7 @@ __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs r
   if (TRAIN) load_frags<16>(wb, net.wt[2], wave, lane);
   __syncthreads();
 
+  double sum = 0.0;  // this lane's part of the loss
   if (wave < 3) {
     const floatx16 acc = product<16>(sa, HS, wa, lane);
     if (!TRAIN) {
@@ -176,26 +222,20 @@ __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs r
         if (r < ra.rows && unit < NOUT) y[(size_t)r * NOUT + unit] = acc[i] + bias[3];
       }
     } else {
-      double sum = 0.0;
       __bf16 dy[16];
-      const float lw = unit < NOUT ? ta.lw[unit] : 0.0f;
+      const int u = min(unit, NOUT - 1);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int r = acc_row(i, half);
-        float d = 0.0f;
-        if (r0 + r < ra.rows && unit < NOUT) {
-          const float yv = acc[i] + bias[3];
-          const float diff = yv - st[r * NOUT + unit];
-          const float c = lw * sc[r] * ta.scale;
-          d = 2.0f * c * diff;
-          sum += (double)(c * diff * diff);
-        }
-        dy[i] = (__bf16)d;
+        const bool real = r0 + r < ra.rows && unit < NOUT;
+        const float yv = acc[i] + bias[3];
+        const float diff = yv - st[r * NOUT + u];
+        const float c = lw * sc[r] * ta.scale;
+        sum += real ? (double)(c * diff * diff) : 0.0;
+        dy[i] = (__bf16)(real ? 2.0f * c * diff : 0.0f);
         sy[r * YS + unit] = dy[i];
       }
       store_transposed(ta.dt[3], ta.ks, wave, blockIdx.x, dy, lane);
-      for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
-      if (lane == 0) atomicAdd(ta.loss, sum);
     }
   }
   if (!TRAIN) return;
@@ -218,6 +258,10 @@ __global__ void __launch_bounds__(512) k_rows(const NetArgs net, const RowArgs r
   masked(product<16>(sb, HS, wb, lane), 1, sa);
   __syncthreads();
   masked(product<16>(sa, HS, wa, lane), 0, nullptr);
+  if (wave < 3) {
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o);
+    if (lane == 0) atomicAdd(ta.loss, sum);
+  }
 }
 
 // ---- parameter update ------------------------------------------------------
