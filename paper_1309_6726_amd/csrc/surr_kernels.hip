@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "surr_dev.h"
 
 namespace surrdev {
@@ -91,9 +93,9 @@ __device__ __forceinline__ void store_transposed(__bf16* frags, int ks, int tile
 // layer are requested two layers ahead of their use.  32 samples is the
 // matrix instruction's tile; fewer workgroups than CUs run for small batches.
 // Measured: 5.6 us for 8 prediction rows (33 us as six launches and a copy),
-// 13.1 us for a training minibatch of 256 (16.0 when the targets' loads went row
+// 14.3 us for a training minibatch of 256 (16.0 when the targets' loads went row
 // by row behind the weights, the loss branched for each element and its sum
-// was folded before the backward pass), which with k_update's 6.4 us took 21
+// was folded before the backward pass), which with k_update's 4.8 us took 21
 // launches and 120 us when every layer product, bias sum and update was a launch
 // of its own.
 template <bool TRAIN>
@@ -293,7 +295,9 @@ __device__ __forceinline__ float adam(const UpdateArgs& u, float g, float p, flo
 // four wavefronts forms the whole product (16 matrix instructions for 256
 // samples, operands shared in L1) and updates four of its sixteen rows per
 // lane: the divisions and square roots of Adam are what this launch waits on
-// otherwise (7.8 us a minibatch with one wavefront per tile).
+// otherwise.  What is left is one round trip of loads, the products, Adam and
+// the stores.  us a minibatch: 7.8 with one wavefront per tile, 6.4 with eight
+// steps of operands in flight and a bias's moments behind its sum, 4.8 now.
 template <int L>
 __device__ __forceinline__ void update_weights(const UpdateArgs& u, int tile, __bf16* lds) {
   constexpr int N = LN[L], K = LK[L], TK = K / 32;
@@ -314,16 +318,21 @@ __device__ __forceinline__ void update_weights(const UpdateArgs& u, int tile, __
     }
   }
   floatx16 acc = zero16();
-  // eight steps of operands in flight; u.steps is even
+  // sixteen steps of operands in flight, so 256 samples cost one round trip
   int s = 0;
-  for (; s + 8 <= u.steps; s += 8) {
-    bf16x8 av[8], bv[8];
+  auto steps = [&](auto count) {
+    constexpr int n = decltype(count)::value;
+    bf16x8 av[n], bv[n];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) { av[q] = a[(s + q) * 64]; bv[q] = b[(s + q) * 64]; }
+    for (int q = 0; q < n; ++q) { av[q] = a[(s + q) * 64]; bv[q] = b[(s + q) * 64]; }
+    __builtin_amdgcn_sched_barrier(0);  // all of them requested before the first product
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int q = 0; q < n; ++q)
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[q], bv[q], acc, 0, 0, 0);
-  }
+    s += n;
+  };
+  while (s + 16 <= u.steps) steps(std::integral_constant<int, 16>{});
+  if (s + 8 <= u.steps) steps(std::integral_constant<int, 8>{});
   for (; s < u.steps; ++s)
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s * 64], b[s * 64], acc, 0, 0, 0);
   float g[4];
@@ -361,6 +370,13 @@ template <int L>
 __device__ __forceinline__ void update_biases(const UpdateArgs& u, int n0) {
   const int lane = threadIdx.x & 63;
   const __bf16* d = u.dt[L] + (size_t)(n0 >> 5) * u.ks * 512 + (n0 & 31) * 8;
+  const int n = n0 + lane, e = LN[L] * LK[L] + n;
+  float p = 0.0f, m1 = 0.0f, m2 = 0.0f;  // requested with the gradients
+  if (lane < BIAS_GROUP && !u.packed) {
+    p = u.p[L][e];
+    m1 = u.m1[L][e];
+    m2 = u.m2[L][e];
+  }
   float s[BIAS_GROUP];
 #pragma unroll
   for (int j = 0; j < BIAS_GROUP; ++j) s[j] = 0.0f;
@@ -377,13 +393,13 @@ __device__ __forceinline__ void update_biases(const UpdateArgs& u, int n0) {
     if (lane == j) g = t;
   }
   if (lane >= BIAS_GROUP) return;
-  const int n = n0 + lane;
   if (u.packed) {
     if (n < RN[L]) u.packed[packed_weights(L) + RN[L] * RK[L] + n] = g;
     return;
   }
-  const int e = LN[L] * LK[L] + n;
-  u.p[L][e] = adam(u, g, u.p[L][e], u.m1[L][e], u.m2[L][e]);
+  u.p[L][e] = adam(u, g, p, m1, m2);
+  u.m1[L][e] = m1;
+  u.m2[L][e] = m2;
 }
 
 // One workgroup per weight tile, one wavefront per bias group: 187
