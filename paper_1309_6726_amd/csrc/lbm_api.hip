@@ -169,15 +169,17 @@ int owned_cols(bool moments) { return moments ? 60 : 62; }
 // Moment step: the lowest tiles (one wavefront per row) that give every CU no
 // more than one workgroup, since rows in series cost 1.5 us each and an idle
 // CU nothing; where eight rows per tile do not get there, eight (12 wavefronts,
-// two workgroups per CU).  us per step, against 16 rows per tile before: 256x32
-// without solute 3.65 at 1 row, 23.3; 1024x64 5.1 at 5 rows, 29.6; 509x40 with
-// the variants 4.4 at 2 rows, 37; 700x500 10.9 at 8 rows, 34 (4 rows 11.8,
-// 12 rows 11.6); 1448^2 44 at 8 rows, 61.  Beyond the cache (moment_kind) one
-// wavefront per tile, where 9 rows take 113 us at 2048^2 and 16 take 123.
+// two workgroups per CU).  us per step, against 16 rows marched before: 256x32
+// without solute 3.65 at 1 row, 24.3; 1024x64 5.2 at 5 rows (4 rows 6.1, 8 rows
+// 5.4), 31; 509x40 with the variants 4.5 at 2 rows, 35; 700x500 11.1 at 8 rows
+// (4 rows 13.0, 12 rows 11.7), 36; 1448^2 46.7 at 8 rows (12 rows 59.5), 59.5.
+// Beyond the cache (moment_kind) one wavefront per tile, where 9 rows take 113
+// us at 2048^2 and 16 take 123.
 //
-// Population step: the same rule up to six rows.  256x32 4.0 us at 1 row,
-// 1024x64 5.9 at 5, 700x500 14.2 at 6, 1023x1024 33.7 at 6 (2 rows 33.1, 14
-// rows 41), 2048^2 246 at 6 (1 row 247, 14 rows 256).
+// Population step: the same rule up to six rows.  256x32 4.3 us at 1 row (6
+// rows 7.3), 1024x64 6.0 at 3 to 8, 700x500 14.6 at 6 (2 rows 15.3, 14 rows
+// 18.8), 1023x1024 34.2 at 6 (14 rows 46), 2048^2 247 at 6 (1 row 249, 14 rows
+// 262).
 int default_rows(const lbm_params& p, bool moments, bool solute) {
   const int own = owned_cols(moments), strips = (p.nx + own - 1) / own, most = moments ? 8 : 6;
   int sy = 1;

@@ -88,9 +88,9 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 // wavefront per row while the step's two buffers fit the 256 MB memory-side
 // cache, taller ones and larger lattices with one wavefront marching up the
 // tile.  Measured on square preforms, us per step (best height of each):
-// 1024^2 (92 MB) 24.8 against 33.3, 1448^2 (184 MB) 44.1 against 48.0,
-// 1600^2 (225 MB) 58.7 against 59.9, 1700^2 (254 MB) 77.0 against 71.9,
-// 2048^2 (369 MB) 114 against 99.5.  Once the reads come from HBM, the short
+// 1024^2 (92 MB) 26.7 against 35.2, 1448^2 (184 MB) 46.7 against 48.4,
+// 1600^2 (225 MB) 55.6 against 60.6, 1700^2 (254 MB) 76.8 against 77.7,
+// 2048^2 (369 MB) 117 against 104.  Once the reads come from HBM, the short
 // tiles' loads (one round trip per tile, two tiles per CU) are not covered.
 constexpr int SHORT_TILE = 12;
 constexpr long long SHORT_BYTES = 240ll << 20;

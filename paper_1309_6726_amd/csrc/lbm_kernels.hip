@@ -19,26 +19,27 @@
 // f and g are double-buffered (A/B); a step reads one buffer and writes the
 // other.
 //
-// Population step (any tau), one kernel per time step.  A workgroup of TX
-// threads owns TX-2 consecutive columns (one column per thread, plus one halo
-// column on each side) and SY consecutive rows, and marches up its rows.  For
-// every row it loads the node populations (coalesced along x), forms the
-// densities, puts rho1, rho2 and the solid flag of the row into a 4-row LDS
-// ring, and then collides the row below with the cohesion/adhesion stencil
-// read from LDS, applies the reaction, and pushes the post-collision
-// populations to the neighbours (or back into the node's own opposite link at
-// a solid neighbour).
+// Population step (any tau), one kernel per time step (pop_rows).  A workgroup
+// owns 62 consecutive columns (one lane each, plus one halo column on each
+// side) and up to POP_ROWS rows, one wavefront per row and one more below and
+// above.  A wavefront loads its row's populations (coalesced along x), forms the
+// densities and momenta, publishes the densities in LDS, and collides its row
+// with the cohesion/adhesion stencil read from there, applies the reaction, and
+// pushes the post-collision populations to the neighbours (or back into the
+// node's own opposite link at a solid neighbour).
 //
 // Moment step (tau = 1).  With full relaxation the post-collision populations
 // of a component are its equilibria at (rho_s, v_s), so a node stores those
 // three numbers per component (24 bytes instead of 72) and the next step
 // rebuilds the populations that arrive at x by evaluating the equilibrium of
 // each upstream neighbour (halfway bounce-back: the node's own moments with
-// the velocity reversed when the upstream node is solid).  A workgroup then
-// owns TX-4 columns: the gathered densities feed the force stencil, which
-// reaches two columns and two rows out.  Per-node arithmetic is independent
-// of the launch shape in both steps, so every tile shape gives bit-identical
-// results.
+// the velocity reversed when the upstream node is solid).  A tile then owns 60
+// columns: the gathered densities feed the force stencil, which reaches two
+// columns and two rows out.  Two kernels run it (moment_kind chooses): mom_rows,
+// one wavefront per row of the tile with the links exchanged through LDS, and
+// mom_wave, one wavefront that marches up its tile.  Per-node arithmetic is
+// independent of the kernel and of the launch shape in both steps, so every tile
+// shape gives bit-identical results.
 //
 // Growth timing.  In the step n -> n+1 a node whose precipitate exceeds the
 // threshold still streams as fluid (the step uses the solid set of state n);
@@ -775,11 +776,12 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
 // leave most SIMDs idle, and there mom_wave's sy + 4 row iterations in series
 // (1.1-1.9 us each) are the step; here a step is one memory round trip, two
 // LDS exchanges and one row's arithmetic (256x32 without solute: 3.65 us a
-// step against 6.2 for mom_wave's best height).  On one that fills the chip
-// arithmetic: it does (sy + 4) / sy times the streaming work, 571 vector
-// instructions per owned row of 60 nodes at eight rows, as mom_wave's 533, but
-// with 24 wavefronts per CU resident (64 VGPRs, 74 KB LDS) instead of 12:
-// 1024^2 preform 24.8 us against 33.3.  Eight rows because two workgroups of
+// step against 6.6 for mom_wave's best height).  On one that fills the chip
+// arithmetic: it does (sy + 4) / sy times the streaming work, 577 vector
+// instructions per owned row of 60 nodes at eight rows (counted; they keep the
+// SIMDs busy for 70% of a step at 1448^2), but with 24 wavefronts per CU
+// resident (72 VGPRs, 74 KB LDS) instead of mom_wave's 12: 1024^2 preform 26.7
+// us against 35.2, 700x500 11.1 against 16.1.  Eight rows because two workgroups of
 // 12 wavefronts share a CU's LDS; nine to twelve leave one.
 static_assert(SHORT_TILE + 4 <= 16, "one wavefront per row within a workgroup");
 
