@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 
 GUARD = 4096  # doubles after the end
 
-# (nx, ny, field bits), 8 nx ny bytes a field: less than one slot, one slot of
-# 512 KB exactly and a row more, an odd number of slots, the last size of one
+# (nx, ny, field bits), 8 nx ny bytes a field: less than one slot (and small
+# enough that the first copy makes no slots), one slot of 512 KB exactly and a
+# row more, an odd number of slots, the last size of one
 # thread and the first of four, a last chunk of one row, a ragged many
 CASES = [(32, 8, 0x10), (256, 256, 0x01), (256, 257, 0x02), (301, 211, 0x4d), (1023, 1025, 0x02),
          (1023, 1025, 0x03), (1024, 1024, 0x03), (1024, 1025, 0x08 | 0x10), (700, 501, 0x7f)]
