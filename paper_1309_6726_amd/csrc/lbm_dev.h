@@ -92,10 +92,17 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 // 1600^2 (225 MB) 55.6 against 60.6, 1700^2 (254 MB) 76.8 against 77.7,
 // 2048^2 (369 MB) 117 against 104.  Once the reads come from HBM, the short
 // tiles' loads (one round trip per tile, two tiles per CU) are not covered.
-constexpr int SHORT_TILE = 12;
+//
+// Above SHORT_PAIR rows a CU holds one workgroup instead of two, which pays only
+// on lattices of half that size.  At 12 rows: 700x500 (31 MB) 11.7 against 29,
+// 1024^2 34.7 against 38.0, 34 capillaries (177 MB) 62.7 against 48.9, 1448^2
+// 59.5 against 48.4.
+constexpr int SHORT_TILE = 12, SHORT_PAIR = 8;
 constexpr long long SHORT_BYTES = 240ll << 20;
 inline int moment_kind(long long nodes, bool solute, int sy) {
-  return sy <= SHORT_TILE && nodes * (solute ? 88 : 48) <= SHORT_BYTES ? KIND_MM_SHORT : KIND_MM;
+  const long long bytes = nodes * (solute ? 88 : 48);
+  return sy <= SHORT_TILE && bytes <= (sy <= SHORT_PAIR ? SHORT_BYTES : SHORT_BYTES / 2) ? KIND_MM_SHORT
+                                                                                        : KIND_MM;
 }
 
 // Records a message for lbm_last_error() and returns s.

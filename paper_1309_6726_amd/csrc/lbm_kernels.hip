@@ -400,8 +400,8 @@ struct Bounce {
 // gets the links into the row above, to.down(o4, o7, o8) those into the row
 // below, to.own(r, x) what adds (r, x, 0) to the accumulators (rho, jx, jy) of
 // the row itself (the rest and horizontal links, streamed along the row by DPP
-// wave shifts) and to.bounced(r, x, y) what bounces back.  Called with every
-// lane active.
+// wave shifts) and to.bounced(r, x, y) what bounces back (to.unbounced() where
+// nothing does on any lane).  Called with every lane active.
 // With u3 = 3 v: w rho (1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v^2)
 //              = w rho (cc + e3 (1 + e3 / 2)), e3 = e . u3, cc = 1 - u3^2 / 6.
 template <typename R, typename To>
@@ -411,7 +411,7 @@ __device__ __forceinline__ void stream_row(float rho_s, float vx, float vy, cons
     to.up(R(0), R(0), R(0));
     to.down(R(0), R(0), R(0));
     to.own(R(0), R(0));
-    to.bounced(R(0), R(0), R(0));
+    to.unbounced();
     return;
   }
   const R WA = R(1) / R(9), WD = R(1) / R(36), WR = R(4) / R(9);
@@ -446,7 +446,7 @@ __device__ __forceinline__ void stream_row(float rho_s, float vx, float vy, cons
     by = fmar(s[8], o8, by);
     to.bounced(br, bx, by);
   } else {
-    to.bounced(R(0), R(0), R(0));
+    to.unbounced();
   }
 }
 
@@ -469,6 +469,7 @@ struct RowSums {
     row[1] += x;
     row[2] += y;
   }
+  __device__ __forceinline__ void unbounced() const {}
   __device__ __forceinline__ void down(R o4, R o7, R o8) const {
     const R a7 = from_right(o7), a8 = from_left(o8);
     const R v = (o4 + a7) + a8;
@@ -579,7 +580,12 @@ __device__ __forceinline__ void collide_moments(const StepArgs& a, const MomentO
 // and rewritten by the same wavefront an iteration later) keep the normal
 // policy.  Whether the hint pays depends on how the step's footprint meets
 // the caches, so the single-lattice step takes it as an autotuned choice.
-template <bool SOLUTE, bool REACT, bool VAR, typename R, bool NT>
+//
+// BATCH: rows that are nothing but wall (a sixth of a capillary sweep's) are
+// skipped.  A single lattice that this kernel gets is too large to have any,
+// and the branch alone costs it 2% (2048^2, 12 rows: 104.0 us with it, 102.0
+// without).
+template <bool SOLUTE, bool REACT, bool VAR, typename R, bool NT, bool BATCH>
 __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) {
   // prefetch slots per buffer: 0..5 moments, 6..10 solute, 11..12 precipitate
   __shared__ float pf[2][13][64];
@@ -712,7 +718,8 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
     // neighbours solid in state n-1, from which values bounce back
     const lanes_t row0 = __ballot(m_0 & SPREV);
     const Neighbours prev(__ballot(m_m1 & SPREV), row0, __ballot(m_p1 & SPREV));
-    const Bounce<R> bounce(prev, row0);
+    Bounce<R> bounce(prev, row0);
+    if (!BATCH) bounce.none = false;
 
     // ---- sources of row k: outgoing equilibria, streamed -----------------
     R accN[6];
@@ -799,6 +806,7 @@ struct RowShares {
   }
   __device__ __forceinline__ void own(R r_, R x_) { r = r_; x = x_; }
   __device__ __forceinline__ void bounced(R r_, R x_, R y_) { b[0] = r_; b[1] = x_; b[2] = y_; }
+  __device__ __forceinline__ void unbounced() { bounced(R(0), R(0), R(0)); }
   __device__ __forceinline__ void down(R o4, R o7, R o8) {
     if (has_dn) { s_dn[0] = o4; s_dn[LROW] = o7; s_dn[2 * LROW] = o8; }
   }
@@ -1164,10 +1172,10 @@ __host__ __device__ inline int xcd_tile(int b, int T) {
   return (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
 }
 
-template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT>
+template <bool SOLUTE, bool REACT, bool VAR, typename R, int KIND, bool NT, bool BATCH>
 __device__ __forceinline__ void run_tile(const StepArgs& a, int strip, int seg, char* lds_raw) {
   if constexpr (KIND == KIND_MM)
-    mom_wave<SOLUTE, REACT, VAR, R, NT>(a, strip, seg);
+    mom_wave<SOLUTE, REACT, VAR, R, NT, BATCH>(a, strip, seg);
   else if constexpr (KIND == KIND_MM_SHORT)
     mom_rows<SOLUTE, REACT, VAR, R, NT>(a, strip, seg, lds_raw);
   else
@@ -1187,7 +1195,7 @@ k_step(const StepArgs a) {
   const int T = a.nstrips * a.nsegs;
   const int tile = a.remap ? xcd_tile(blockIdx.x, T) : (int)blockIdx.x;
   const int seg = tile / a.nstrips;
-  run_tile<SOLUTE, REACT, VAR, R, KIND, NT>(a, tile - seg * a.nstrips, seg, lds_raw);
+  run_tile<SOLUTE, REACT, VAR, R, KIND, NT, false>(a, tile - seg * a.nstrips, seg, lds_raw);
 }
 
 // Batched step: one launch advances every instance of a batch by one step.
@@ -1209,7 +1217,7 @@ k_step_batch(const StepArgs* __restrict__ insts, const int4* __restrict__ tiles,
   a.bit_p1 = pending_bit(step - 1);
   a.bit_p2 = pending_bit(step - 2);
   a.bit_cur = pending_bit(step);
-  run_tile<SOLUTE, REACT, VAR, R, KIND, false>(a, e.y, e.z, lds_raw);
+  run_tile<SOLUTE, REACT, VAR, R, KIND, false, true>(a, e.y, e.z, lds_raw);
 }
 
 // Advances the device step counter by n (one lane).
