@@ -46,7 +46,7 @@ class HostCopy {
     const int nslots = threaded ? MAX_SLOTS : 2;
     const bool once = bytes < SMALL && !called_;
     called_ = true;
-    if (once || known_to_hip(dst) || !reserve(slot * nslots, nslots)) {
+    if (once || known_to_hip(dst) || !reserve(slot * nslots, nslots, st)) {
       hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
       const hipError_t w = hipStreamSynchronize(st);
       return e == hipSuccess ? w : e;
@@ -82,9 +82,21 @@ class HostCopy {
     return false;
   }
 
-  bool reserve(size_t bytes, int events) {
-    for (; nev_ < events; ++nev_)
-      if (hipEventCreateWithFlags(&ev_[nev_], hipEventDisableTiming) != hipSuccess) return give_up();
+  // Slots of together `bytes`, and events on st's device, whichever is current.
+  bool reserve(size_t bytes, int events, hipStream_t st) {
+    if (nev_ < events) {
+      int was = 0;
+      hipDevice_t own = 0;
+      if (hipGetDevice(&was) != hipSuccess || hipStreamGetDevice(st, &own) != hipSuccess) return give_up();
+      if (own != was && hipSetDevice(own) != hipSuccess) return give_up();
+      hipError_t e = hipSuccess;
+      while (nev_ < events && e == hipSuccess) {
+        e = hipEventCreateWithFlags(&ev_[nev_], hipEventDisableTiming);
+        if (e == hipSuccess) ++nev_;
+      }
+      if (own != was) (void)hipSetDevice(was);
+      if (e != hipSuccess) return give_up();
+    }
     if (bytes <= size_) return true;
     if (pinned_) (void)hipHostFree(pinned_);
     pinned_ = nullptr;
