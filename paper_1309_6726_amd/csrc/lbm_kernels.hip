@@ -1428,7 +1428,8 @@ __device__ void capillary_obs(const Src& src, const uint8_t* __restrict__ mask,
   double de = 0.0;
   long long cl = -1;
   int area = 0, wmin = W, steps = 0;
-  // each pass decides T - 1 columns; the last thread's is the next one's neighbour
+  // each pass decides the columns of T - 1 threads; the last one's only serves
+  // as a neighbour, and is the next pass's first
   for (int xb = x_in; xb < x_out; xb += T - 1) {
     const int x = xb + t;
     bool blocked = false;
@@ -1459,7 +1460,7 @@ __device__ void capillary_obs(const Src& src, const uint8_t* __restrict__ mask,
     if (FULL) s_db[t] = db;
     __syncthreads();
     const bool next = x + 1 < x_out;
-    if (x < x_out && (t < T - 1 || !next)) {
+    if (x < x_out && t < T - 1) {
       const double phin = next ? s_phi[t + 1] : 0.0;
       const bool crossing = next && !s_blocked[t + 1] && phi >= 0.5 && phin < 0.5;
       const bool dry = x == x_in && phi < 0.5;
