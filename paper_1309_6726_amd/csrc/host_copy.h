@@ -25,6 +25,8 @@
 #include <thread>
 #include <vector>
 
+#include "pinned.h"
+
 namespace lbmdev {
 
 class HostCopy {
@@ -34,7 +36,6 @@ class HostCopy {
   HostCopy& operator=(const HostCopy&) = delete;
   ~HostCopy() {
     for (int i = 0; i < nev_; ++i) (void)hipEventDestroy(ev_[i]);
-    if (pinned_) (void)hipHostFree(pinned_);
   }
 
   // Copies bytes bytes from device memory, after the work queued on st, and
@@ -46,28 +47,33 @@ class HostCopy {
     const int nslots = threaded ? MAX_SLOTS : 2;
     const bool once = bytes < SMALL && !called_;
     called_ = true;
-    if (once || known_to_hip(dst) || !reserve(slot * nslots, nslots, st)) {
+    Pinned block;
+    char* const pinned = known_to_hip(dst) ? nullptr : (char*)block.take(slot * nslots, !once);
+    if (!pinned || !events(nslots, st)) {
       hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
       const hipError_t w = hipStreamSynchronize(st);
       return e == hipSuccess ? w : e;
     }
-    Job j{(char*)dst, (const char*)src, bytes, slot, nslots, (long)((bytes + slot - 1) / slot), st};
+    Job j{(char*)dst, (const char*)src, pinned, bytes, slot, nslots, (long)((bytes + slot - 1) / slot), st};
+    block.in_use();
     const hipError_t e = threaded ? run_threaded(j) : run(j);
     // an error can leave copies into the slots on the stream
-    return e == hipSuccess ? e : (void(hipStreamSynchronize(st)), e);
+    if (e == hipSuccess || hipStreamSynchronize(st) == hipSuccess) block.done();
+    return e;
   }
 
  private:
   static constexpr size_t THREADED = size_t(16) << 20;
-  // The slots cost 84 to 97 us to allocate and up to 70 to give back, so an
-  // object's first copy makes none for what a plain copy does in 120 us (200 KB;
-  // 306 us at 512 KB).
+  // New slots cost 84 to 97 us, so an object's first copy makes none, if the
+  // library keeps none, for what a plain copy does in 120 us (200 KB; 306 us at
+  // 512 KB).
   static constexpr size_t SMALL = size_t(256) << 10;
   static constexpr int THREADS = 4, MAX_SLOTS = 2 * THREADS;
 
   struct Job {
     char* dst;
     const char* src;
+    char* pinned;
     size_t bytes, slot;
     int nslots;
     long chunks;
@@ -82,31 +88,20 @@ class HostCopy {
     return false;
   }
 
-  // Slots of together `bytes`, and events on st's device, whichever is current.
-  bool reserve(size_t bytes, int events, hipStream_t st) {
-    if (nev_ < events) {
-      int was = 0;
-      hipDevice_t own = 0;
-      if (hipGetDevice(&was) != hipSuccess || hipStreamGetDevice(st, &own) != hipSuccess) return give_up();
-      if (own != was && hipSetDevice(own) != hipSuccess) return give_up();
-      hipError_t e = hipSuccess;
-      while (nev_ < events && e == hipSuccess) {
-        e = hipEventCreateWithFlags(&ev_[nev_], hipEventDisableTiming);
-        if (e == hipSuccess) ++nev_;
-      }
-      if (own != was) (void)hipSetDevice(was);
-      if (e != hipSuccess) return give_up();
+  // As many events on st's device, whichever is current.
+  bool events(int count, hipStream_t st) {
+    if (nev_ >= count) return true;
+    int was = 0;
+    hipDevice_t own = 0;
+    if (hipGetDevice(&was) != hipSuccess || hipStreamGetDevice(st, &own) != hipSuccess) return give_up();
+    if (own != was && hipSetDevice(own) != hipSuccess) return give_up();
+    hipError_t e = hipSuccess;
+    while (nev_ < count && e == hipSuccess) {
+      e = hipEventCreateWithFlags(&ev_[nev_], hipEventDisableTiming);
+      if (e == hipSuccess) ++nev_;
     }
-    if (bytes <= size_) return true;
-    if (pinned_) (void)hipHostFree(pinned_);
-    pinned_ = nullptr;
-    size_ = 0;
-    if (hipHostMalloc((void**)&pinned_, bytes, hipHostMallocPortable) != hipSuccess) {
-      pinned_ = nullptr;
-      return give_up();
-    }
-    size_ = bytes;
-    return true;
+    if (own != was) (void)hipSetDevice(was);
+    return e == hipSuccess || give_up();
   }
   static bool give_up() {
     (void)hipGetLastError();
@@ -118,7 +113,7 @@ class HostCopy {
   // Only the calling thread queues work: st may name a per-thread stream.
   hipError_t issue(const Job& j, long c) {
     const int k = (int)(c % j.nslots);
-    hipError_t e = hipMemcpyAsync(pinned_ + k * j.slot, j.src + (size_t)c * j.slot, length(j, c),
+    hipError_t e = hipMemcpyAsync(j.pinned + k * j.slot, j.src + (size_t)c * j.slot, length(j, c),
                                   hipMemcpyDeviceToHost, j.st);
     return e == hipSuccess ? hipEventRecord(ev_[k], j.st) : e;
   }
@@ -126,7 +121,7 @@ class HostCopy {
   hipError_t take(const Job& j, long c) {
     const int k = (int)(c % j.nslots);
     const hipError_t e = hipEventSynchronize(ev_[k]);
-    if (e == hipSuccess) std::memcpy(j.dst + (size_t)c * j.slot, pinned_ + k * j.slot, length(j, c));
+    if (e == hipSuccess) std::memcpy(j.dst + (size_t)c * j.slot, j.pinned + k * j.slot, length(j, c));
     return e;
   }
 
@@ -213,8 +208,6 @@ class HostCopy {
 
   std::mutex call_;
   bool called_ = false;
-  char* pinned_ = nullptr;
-  size_t size_ = 0;
   hipEvent_t ev_[MAX_SLOTS];
   int nev_ = 0;
 };

@@ -10,6 +10,7 @@
 
 #include "lbm.h"
 #include "lbm_dev.h"
+#include "pinned.h"
 #include "surr_dev.h"
 
 using lbmdev::fail;
@@ -58,11 +59,11 @@ SLayout slayout(int max_batch, int max_data) {
 
 constexpr int NOALLOC_ROWS = 1024;  // most query rows of one surr_predict_noalloc
 
-// Pinned host memory of a handle (0.9 MB).  Queries, answers, gradients, the
-// loss and the packed parameters pass through it: the kernels read and write
-// it themselves, so a call is its launches and one wait.  Copies to and from
-// pageable memory cost 10-20 us each, and the copy of the answers' columns out
-// of their padded rows went row by row (1.8 ms for 256 rows).
+// Pinned host memory that a call takes (0.9 MB).  Queries, answers, gradients, the
+// loss and the packed parameters pass through it: the kernels read and write it
+// themselves, so a call is its launches and one wait.  Copies to and from pageable
+// memory cost 10-20 us each, and the copy of the answers' columns out of their
+// padded rows went row by row (1.8 ms for 256 rows).
 constexpr int HOST_ROWS = 1024;  // rows per launch that reads its samples here
 struct HostBuffer {
   double loss;
@@ -81,7 +82,6 @@ struct surr_net {
   long long adam_t;
   float wsum;    // sum of the loss weights, added in order in FP32
   bool loss_dirty;     // the loss accumulator may hold a failed call's part
-  HostBuffer* host;    // pinned
   template <typename T> T* at(size_t off) const { return (T*)(ws + off); }
 };
 
@@ -92,6 +92,29 @@ namespace {
     hipError_t e_ = (expr);                                                                 \
     if (e_ != hipSuccess) return fail(LBM_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
+
+// The pinned buffer of one call, whose kernels may use it until wait() or done():
+// where a call fails before, HIP gets the buffer back and waits for them.
+class CallBuffer {
+ public:
+  lbm_status take() {
+    if (!(host_ = (HostBuffer*)block_.take(sizeof(HostBuffer), true)))
+      return fail(LBM_ENOMEM, "no pinned memory");
+    block_.in_use();
+    return LBM_OK;
+  }
+  lbm_status wait(hipStream_t st) {
+    HC(hipStreamSynchronize(st));
+    done();
+    return LBM_OK;
+  }
+  void done() { block_.done(); }
+  HostBuffer* operator->() const { return host_; }
+
+ private:
+  lbmdev::Pinned block_;
+  HostBuffer* host_ = nullptr;
+};
 
 NetArgs net_args(const surr_net* s) {
   NetArgs n{};
@@ -133,11 +156,11 @@ lbm_status begin_loss(surr_net* s) {
   return LBM_OK;
 }
 
-// Waits for a call's last update, after which s->host holds its loss.
-lbm_status end_loss(surr_net* s) {
-  HC(hipStreamSynchronize(s->stream));
-  s->loss_dirty = false;
-  return LBM_OK;
+// Waits for a call's last update, after which its buffer holds the loss.
+lbm_status end_loss(surr_net* s, CallBuffer& host) {
+  const lbm_status st = host.wait(s->stream);
+  if (st == LBM_OK) s->loss_dirty = false;
+  return st;
 }
 
 // Gradients of the last sample_pass: packed, or applied by Adam.
@@ -159,9 +182,10 @@ UpdateArgs update_args(surr_net* s, int rows) {
   return u;
 }
 
-lbm_status adam_step(surr_net* s, int rows, float lr, bool last) {
+// loss_out: where the loss goes with a call's last update, else null.
+lbm_status adam_step(surr_net* s, int rows, float lr, double* loss_out) {
   UpdateArgs u = update_args(s, rows);
-  if (last) u.loss_out = &s->host->loss;
+  u.loss_out = loss_out;
   s->adam_t += 1;
   u.lr = lr;
   u.b1 = 0.9f;
@@ -173,9 +197,9 @@ lbm_status adam_step(surr_net* s, int rows, float lr, bool last) {
   return LBM_OK;
 }
 
-PackArgs pack_args(surr_net* s) {
+PackArgs pack_args(surr_net* s, float* packed) {
   PackArgs a{};
-  a.packed = s->host->packed;
+  a.packed = packed;
   for (int l = 0; l < NL; ++l) {
     a.p[l] = s->at<float>(s->S.p[l]);
     a.m1[l] = s->at<float>(s->S.m1[l]);
@@ -221,35 +245,36 @@ lbm_status surr_init(const double* lo, const double* hi, int32_t max_batch, int3
   float lof[NIN], hif[NIN], lw[NOUT];
   for (int j = 0; j < NIN; ++j) { lof[j] = (float)lo[j]; hif[j] = (float)hi[j]; }
   for (int j = 0; j < NOUT; ++j) lw[j] = 1.0f;
-  hipError_t e = hipHostMalloc((void**)&s->host, sizeof(HostBuffer), hipHostMallocMapped | hipHostMallocPortable);
-  if (e != hipSuccess) { delete s; return fail(LBM_ENOMEM, "pinned buffer: %s", hipGetErrorString(e)); }
-  e = hipMemsetAsync(s->ws, 0, s->S.total, s->stream);
+  hipError_t e = hipMemsetAsync(s->ws, 0, s->S.total, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.lo, lof, sizeof lof, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.hi, hif, sizeof hif, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s->ws + s->S.lw, lw, sizeof lw, hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-  if (e != hipSuccess) {
-    surr_destroy(s);
-    return fail(LBM_EDEVICE, "surrogate init: %s", hipGetErrorString(e));
-  }
+  if (e != hipSuccess) { delete s; return fail(LBM_EDEVICE, "surrogate init: %s", hipGetErrorString(e)); }
   *out = s;
   return LBM_OK;
 }
 
 lbm_status surr_set_params(surr_net* s, const float* packed) {
   if (!s || !packed) return fail(LBM_EINVAL, "NULL argument");
-  memcpy(s->host->packed, packed, sizeof s->host->packed);
-  HC(unpack_params(pack_args(s), s->stream));
-  HC(hipStreamSynchronize(s->stream));
+  CallBuffer host;
+  lbm_status st = host.take();
+  if (st != LBM_OK) return st;
+  memcpy(host->packed, packed, sizeof host->packed);
+  HC(unpack_params(pack_args(s, host->packed), s->stream));
+  if ((st = host.wait(s->stream)) != LBM_OK) return st;
   s->adam_t = 0;
   return LBM_OK;
 }
 
 lbm_status surr_get_params(surr_net* s, float* packed) {
   if (!s || !packed) return fail(LBM_EINVAL, "NULL argument");
-  HC(pack_params(pack_args(s), s->stream));
-  HC(hipStreamSynchronize(s->stream));
-  memcpy(packed, s->host->packed, sizeof s->host->packed);
+  CallBuffer host;
+  lbm_status st = host.take();
+  if (st != LBM_OK) return st;
+  HC(pack_params(pack_args(s, host->packed), s->stream));
+  if ((st = host.wait(s->stream)) != LBM_OK) return st;
+  memcpy(packed, host->packed, sizeof host->packed);
   return LBM_OK;
 }
 
@@ -288,9 +313,11 @@ lbm_status surr_train_epoch(surr_net* s, const int32_t* perm, int32_t batch, flo
   if (!(lr > 0.0f) || !std::isfinite(lr)) return fail(LBM_EINVAL, "bad learning rate");
   for (int i = 0; i < s->n_data; ++i)
     if (perm[i] < 0 || perm[i] >= s->n_data) return fail(LBM_EINVAL, "perm[%d] out of range", i);
-  HC(hipMemcpyAsync(s->ws + s->S.perm, perm, (size_t)s->n_data * 4, hipMemcpyHostToDevice, s->stream));
-  lbm_status st = begin_loss(s);
+  CallBuffer host;
+  lbm_status st = host.take();
   if (st != LBM_OK) return st;
+  HC(hipMemcpyAsync(s->ws + s->S.perm, perm, (size_t)s->n_data * 4, hipMemcpyHostToDevice, s->stream));
+  if ((st = begin_loss(s)) != LBM_OK) return st;
   const float* X = s->at<float>(s->S.X);
   const float* Y = s->at<float>(s->S.Y);
   int nb = 0;
@@ -298,48 +325,55 @@ lbm_status surr_train_epoch(surr_net* s, const int32_t* perm, int32_t batch, flo
     const int rows = std::min(batch, s->n_data - off);
     if ((st = sample_pass(s, X, Y, s->at<float>(s->S.RW), s->at<int32_t>(s->S.perm) + off, rows)) != LBM_OK)
       return st;
-    if ((st = adam_step(s, rows, lr, off + rows >= s->n_data)) != LBM_OK) return st;
+    if ((st = adam_step(s, rows, lr, off + rows >= s->n_data ? &host->loss : nullptr)) != LBM_OK) return st;
   }
-  if ((st = end_loss(s)) != LBM_OK) return st;
-  if (mean_loss) *mean_loss = s->host->loss / nb;
+  if ((st = end_loss(s, host)) != LBM_OK) return st;
+  if (mean_loss) *mean_loss = host->loss / nb;
   return LBM_OK;
 }
 
 lbm_status surr_gradients(surr_net* s, const float* x, const float* y, int32_t n, float* grad,
                           double* loss_out) {
   if (!s || !x || !y || !grad || n < 1 || n > s->S.Bp) return fail(LBM_EINVAL, "bad arguments");
-  const float *X = s->host->x, *Y = s->host->y;
+  CallBuffer host;
+  lbm_status st = host.take();
+  if (st != LBM_OK) return st;
+  const float *X = host->x, *Y = host->y;
   if (n <= HOST_ROWS) {
-    memcpy(s->host->x, x, (size_t)n * NIN * 4);
-    memcpy(s->host->y, y, (size_t)n * NOUT * 4);
+    memcpy(host->x, x, (size_t)n * NIN * 4);
+    memcpy(host->y, y, (size_t)n * NOUT * 4);
   } else {
     X = s->at<float>(s->S.qx);
     Y = s->at<float>(s->S.qy);
     HC(hipMemcpyAsync(s->ws + s->S.qx, x, (size_t)n * NIN * 4, hipMemcpyHostToDevice, s->stream));
     HC(hipMemcpyAsync(s->ws + s->S.qy, y, (size_t)n * NOUT * 4, hipMemcpyHostToDevice, s->stream));
   }
-  lbm_status st = begin_loss(s);
-  if (st != LBM_OK) return st;
+  if ((st = begin_loss(s)) != LBM_OK) return st;
   if ((st = sample_pass(s, X, Y, nullptr, nullptr, n)) != LBM_OK) return st;
   UpdateArgs u = update_args(s, n);
-  u.packed = s->host->packed;
-  u.loss_out = &s->host->loss;
+  u.packed = host->packed;
+  u.loss_out = &host->loss;
   HC(update(u, s->stream));
-  if ((st = end_loss(s)) != LBM_OK) return st;
-  memcpy(grad, s->host->packed, sizeof s->host->packed);
-  if (loss_out) *loss_out = s->host->loss;
+  if ((st = end_loss(s, host)) != LBM_OK) return st;
+  memcpy(grad, host->packed, sizeof host->packed);
+  if (loss_out) *loss_out = host->loss;
   return LBM_OK;
 }
 
 lbm_status surr_predict(surr_net* s, const float* x, int32_t n, float* y) {
   if (!s || !x || !y || n < 0) return fail(LBM_EINVAL, "bad arguments");
+  if (n == 0) return LBM_OK;
+  CallBuffer host;
+  lbm_status st = host.take();
+  if (st != LBM_OK) return st;
   for (int off = 0; off < n; off += HOST_ROWS) {
     const int rows = std::min(HOST_ROWS, n - off);
-    memcpy(s->host->x, x + (size_t)off * NIN, (size_t)rows * NIN * 4);
-    HC(predict(net_args(s), RowArgs{s->host->x, nullptr, rows}, s->host->y, s->stream));
+    memcpy(host->x, x + (size_t)off * NIN, (size_t)rows * NIN * 4);
+    HC(predict(net_args(s), RowArgs{host->x, nullptr, rows}, host->y, s->stream));
     HC(hipStreamSynchronize(s->stream));
-    memcpy(y + (size_t)off * NOUT, s->host->y, (size_t)rows * NOUT * 4);
+    memcpy(y + (size_t)off * NOUT, host->y, (size_t)rows * NOUT * 4);
   }
+  host.done();
   return LBM_OK;
 }
 
@@ -358,10 +392,6 @@ lbm_status surr_predict_noalloc(const surr_net* s, const float* x, int32_t n, fl
   return LBM_OK;
 }
 
-void surr_destroy(surr_net* s) {
-  if (!s) return;
-  if (s->host) (void)hipHostFree(s->host);
-  delete s;
-}
+void surr_destroy(surr_net* s) { delete s; }
 
 }  // extern "C"
