@@ -227,8 +227,9 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   a.react = s->L.react;
   set_model(a, p, s->L.solute);
   for (long long t = 0; t < n; ++t) {
-    const int sy = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
-    const int kind = !moments ? KIND_POP : (s->mom ? moment_kind(s->L.N, s->L.solute, sy) : KIND_PM);
+    const int set = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
+    const int kind = !moments ? KIND_POP : (s->mom ? moment_kind(s->L.N, s->L.solute, set) : KIND_PM);
+    const int sy = launch_rows(kind, set);
     a.tx_owned = owned_cols(s->mom);
     a.sy = sy;
     a.nsegs = (p.ny + sy - 1) / sy;
@@ -805,6 +806,7 @@ struct lbm_batch {
   int max_blocks;
   long long step;
   int tx, sy;
+  int rows;                   // of the tiles launched (launch_rows)
   int scheme;                 // LBM_SCHEME_*
   bool mom;                   // instance buffers hold moments of the last step
   long long nodes;            // of all instances
@@ -901,9 +903,9 @@ StepArgs instance_args(const lbm_batch* b, int i, int parity) {
   a.nx = p.nx;
   a.ny = p.ny;
   a.tx_owned = owned_cols(batch_moments(b));
-  a.sy = b->sy;
+  a.sy = b->rows;
   a.nstrips = (p.nx + a.tx_owned - 1) / a.tx_owned;
-  a.nsegs = (p.ny + b->sy - 1) / b->sy;
+  a.nsegs = (p.ny + b->rows - 1) / b->rows;
   a.remap = 0;
   a.solute = L.solute;
   a.react = L.react;
@@ -921,6 +923,7 @@ void drop_graph(lbm_batch* b) {
 // Rebuild the per-instance arguments and the tile list for the launch shape.
 lbm_status batch_configure(lbm_batch* b) {
   drop_graph(b);
+  b->rows = batch_moments(b) ? b->sy : launch_rows(KIND_POP, b->sy);
   b->h_insts.resize(2 * b->n);
   for (int i = 0; i < b->n; ++i) {
     b->h_insts[2 * i] = instance_args(b, i, 0);
@@ -929,7 +932,7 @@ lbm_status batch_configure(lbm_batch* b) {
   std::vector<int4> order;
   const int own = owned_cols(batch_moments(b));
   for (int i = 0; i < b->n; ++i) {
-    const int ns = (b->p[i].nx + own - 1) / own, nq = (b->p[i].ny + b->sy - 1) / b->sy;
+    const int ns = (b->p[i].nx + own - 1) / own, nq = (b->p[i].ny + b->rows - 1) / b->rows;
     // segment-major inside an instance, like the single-lattice step
     for (int q = 0; q < nq; ++q)
       for (int s = 0; s < ns; ++s) order.push_back(make_int4(i, s, q, 0));
@@ -987,7 +990,7 @@ int batch_kind(const lbm_batch* b) {
 lbm_status queue_batch(lbm_batch* b, int nsteps, hipStream_t st) {
   for (int t = 0; t < nsteps; ++t) {
     const int kind = batch_kind(b);
-    hipError_t e = launch_step_batch(b->d_insts, b->d_tiles, b->ntiles, b->d_step, t, b->sy,
+    hipError_t e = launch_step_batch(b->d_insts, b->d_tiles, b->ntiles, b->d_step, t, b->rows,
                                      b->solute, b->react, batch_variants(b), kind, st);
     if (e != hipSuccess) return fail(LBM_EDEVICE, "batch step launch: %s", hipGetErrorString(e));
     b->mom = batch_moments(b);

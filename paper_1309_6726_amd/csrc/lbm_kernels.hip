@@ -949,13 +949,13 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
 
 // Population step (any tau), one wavefront per row: lane t holds column
 // x0 - 1 + t, and a workgroup owns at most the 62 columns of lanes 1..62 and at
-// most POP_ROWS rows (blockIdx.y counts the workgroups of a taller tile, which
-// share its rows): wavefront k holds the row below them (k = 0), one of them, or
-// the row above.  Every wavefront loads its row's populations at once, publishes
-// the densities in LDS, and collides and pushes its row (the two halo rows only
-// publish).  The rest population is rho minus the moving ones, so the collision
-// conserves mass exactly.  OUTM (tau = 1 only): store the moments (rho_s, v_s) of
-// the collided node, zero at solids, instead of pushing populations.
+// most POP_ROWS rows (blockIdx.y counts them in taller tiles, see launch_rows):
+// wavefront k holds the row below them (k = 0), one of them, or the row above.
+// Every wavefront loads its row's populations at once, publishes the densities in
+// LDS, and collides and pushes its row (the two halo rows only publish).  The rest
+// population is rho minus the moving ones, so the collision conserves mass exactly.
+// OUTM (tau = 1 only): store the moments (rho_s, v_s) of the collided node, zero at
+// solids, instead of pushing populations.
 //
 // What bounds it: the round trips and the bandwidth of 23 planes read and
 // written.  Rows in parallel put a tile's loads in flight together.  The
@@ -966,7 +966,7 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
 // 14.6, 2048^2 258 against 245).  us per step, against workgroups that marched
 // up their rows (best shape): 1023x1024 preform 34.2 against 42.0, 2048^2 237
 // against 250 (hint), 1024x64 capillary 6.2 against 7.2.
-constexpr int POP_ROWS = 14;
+
 // What a wavefront of pop_rows keeps in LDS: its row's densities, lane t at
 // t + 1, for the neighbouring rows, and its own lanes' populations.
 struct PopRow {
@@ -989,11 +989,10 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
   if (xc >= nx) xc -= nx;
   const int xl = xc == 0 ? nx - 1 : xc - 1;
   const int xr = xc == nx - 1 ? 0 : xc + 1;
-  const int rows = ((int)blockDim.x >> 6) - 2;
-  const int ys = seg * a.sy + rows * (int)blockIdx.y;
+  const int ys = seg * a.sy + POP_ROWS * (int)blockIdx.y;
   const int ye = min((seg + 1) * a.sy, ny);
   if (ys >= ye) return;  // the whole workgroup
-  const int nrows = min(rows, ye - ys) + 2;
+  const int nrows = min(POP_ROWS, ye - ys) + 2;
   const bool live = k < nrows;
   const bool crow = k >= 1 && k < nrows - 1;
   int y = ys - 1 + k;
@@ -1680,17 +1679,10 @@ __global__ void k_unpack(MomSrc src, float* __restrict__ fout) {
 }
 
 // ---- launchers ------------------------------------------------------------
-// Workgroups that share a population tile of sy rows: as few as may be, with rows
-// as even as may be.  16 rows as 8 and 8 against 14 and 2, us per step: 1024^2
-// 38.6, 54.1; 2048x1100 with the hint 113, 130; 2500^2 397, 425.
-static int tile_parts(int kind, int sy) {
-  return kind == KIND_POP || kind == KIND_PM ? (sy + POP_ROWS - 1) / POP_ROWS : 1;
-}
-
-// Threads per workgroup, `parts` of which share a tile: one wavefront per tile in
-// the marching moment step, one per row (halo rows included) otherwise.
-static int step_threads(int kind, int sy, int parts) {
-  return kind == KIND_MM ? 64 : 64 * ((sy + parts - 1) / parts + (kind == KIND_MM_SHORT ? 4 : 2));
+// Threads per workgroup: one wavefront per tile in the moment step, one per
+// row (halo rows included) otherwise.
+static int step_threads(int kind, int sy) {
+  return kind == KIND_MM ? 64 : 64 * (kind == KIND_MM_SHORT ? sy + 4 : (sy < POP_ROWS ? sy : POP_ROWS) + 2);
 }
 
 // LDS beyond the static part: see mom_rows and pop_rows.
@@ -1700,70 +1692,72 @@ static size_t step_lds_bytes(int kind, int threads) {
   return kind == KIND_MM_SHORT ? (rows - 2) * (2 * 6 + 2) * LROW * sizeof(double) : rows * sizeof(PopRow);
 }
 
+// Workgroups of T tiles: a population tile taller than POP_ROWS takes several.
+static dim3 step_grid(int kind, int sy, int T) {
+  return dim3(T, kind == KIND_POP || kind == KIND_PM ? (sy + POP_ROWS - 1) / POP_ROWS : 1);
+}
+
 // Runs that use a reaction or solute-lattice variant (saturation, held
 // source, D2Q4) take their own instantiation, so the plain model keeps its
 // instruction stream.
 inline bool uses_variants(const StepArgs& a) { return a.c_eq > 0.0 || a.hold_x > 0 || a.q4; }
 
 template <typename R, int KIND, bool NT>
-void launch_step_t(const StepArgs& a, dim3 grid, int tx, size_t lds, hipStream_t st) {
+void launch_step_t(const StepArgs& a, int T, int tx, size_t lds, hipStream_t st) {
   if (a.solute && a.react && uses_variants(a))
-    hipLaunchKernelGGL((k_step<true, true, true, R, KIND, NT>), grid, dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, true, true, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute && a.react)
-    hipLaunchKernelGGL((k_step<true, true, false, R, KIND, NT>), grid, dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, true, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute && uses_variants(a))
-    hipLaunchKernelGGL((k_step<true, false, true, R, KIND, NT>), grid, dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, false, true, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else if (a.solute)
-    hipLaunchKernelGGL((k_step<true, false, false, R, KIND, NT>), grid, dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<true, false, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
   else
-    hipLaunchKernelGGL((k_step<false, false, false, R, KIND, NT>), grid, dim3(tx), lds, st, a);
+    hipLaunchKernelGGL((k_step<false, false, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
 }
 
 // nt: the non-temporal load hint, compiled for the moment and population
 // steps (the one-off PM step ignores it).  The arithmetic is FP64 throughout.
 hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st) {
-  const int parts = tile_parts(kind, a.sy);
-  const dim3 grid(a.nstrips * a.nsegs, parts);
-  const int tx = step_threads(kind, a.sy, parts);
+  const int T = a.nstrips * a.nsegs;
+  const int tx = step_threads(kind, a.sy);
   const size_t lds = step_lds_bytes(kind, tx);
   switch (kind + (nt ? 8 : 0)) {
-    case KIND_MM: launch_step_t<double, KIND_MM, false>(a, grid, tx, lds, st); break;
-    case KIND_MM + 8: launch_step_t<double, KIND_MM, true>(a, grid, tx, lds, st); break;
-    case KIND_MM_SHORT: launch_step_t<double, KIND_MM_SHORT, false>(a, grid, tx, lds, st); break;
-    case KIND_MM_SHORT + 8: launch_step_t<double, KIND_MM_SHORT, true>(a, grid, tx, lds, st); break;
-    case KIND_POP: launch_step_t<double, KIND_POP, false>(a, grid, tx, lds, st); break;
-    case KIND_POP + 8: launch_step_t<double, KIND_POP, true>(a, grid, tx, lds, st); break;
-    default: launch_step_t<double, KIND_PM, false>(a, grid, tx, lds, st);
+    case KIND_MM: launch_step_t<double, KIND_MM, false>(a, T, tx, lds, st); break;
+    case KIND_MM + 8: launch_step_t<double, KIND_MM, true>(a, T, tx, lds, st); break;
+    case KIND_MM_SHORT: launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st); break;
+    case KIND_MM_SHORT + 8: launch_step_t<double, KIND_MM_SHORT, true>(a, T, tx, lds, st); break;
+    case KIND_POP: launch_step_t<double, KIND_POP, false>(a, T, tx, lds, st); break;
+    case KIND_POP + 8: launch_step_t<double, KIND_POP, true>(a, T, tx, lds, st); break;
+    default: launch_step_t<double, KIND_PM, false>(a, T, tx, lds, st);
   }
   return hipGetLastError();
 }
 
 template <typename R, int KIND>
-void launch_batch_t(const StepArgs* insts, const int4* tiles, const long long* stepc, int j, dim3 grid,
-                    int tx, int solute, int react, int var, size_t lds, hipStream_t st) {
+void launch_batch_t(const StepArgs* insts, const int4* tiles, int ntiles, const long long* stepc,
+                    int j, int sy, int tx, int solute, int react, int var, size_t lds, hipStream_t st) {
   if (solute && react && var)
-    hipLaunchKernelGGL((k_step_batch<true, true, true, R, KIND>), grid, dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, true, true, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute && react)
-    hipLaunchKernelGGL((k_step_batch<true, true, false, R, KIND>), grid, dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, true, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute && var)
-    hipLaunchKernelGGL((k_step_batch<true, false, true, R, KIND>), grid, dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, false, true, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else if (solute)
-    hipLaunchKernelGGL((k_step_batch<true, false, false, R, KIND>), grid, dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<true, false, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
   else
-    hipLaunchKernelGGL((k_step_batch<false, false, false, R, KIND>), grid, dim3(tx), lds, st, insts, tiles, stepc, j);
+    hipLaunchKernelGGL((k_step_batch<false, false, false, R, KIND>), step_grid(KIND, sy, ntiles), dim3(tx), lds, st, insts, tiles, stepc, j);
 }
 
 hipError_t launch_step_batch(const StepArgs* insts, const int4* tiles, int ntiles,
                              const long long* stepc, int j, int sy, int solute, int react, int var,
                              int kind, hipStream_t st) {
-  const int parts = tile_parts(kind, sy);
-  const dim3 grid(ntiles, parts);
-  const int tx = step_threads(kind, sy, parts);
+  const int tx = step_threads(kind, sy);
   const size_t lds = step_lds_bytes(kind, tx);
-  if (kind == KIND_MM_SHORT) launch_batch_t<double, KIND_MM_SHORT>(insts, tiles, stepc, j, grid, tx, solute, react, var, lds, st);
-  else if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, stepc, j, grid, tx, solute, react, var, lds, st);
-  else if (kind == KIND_PM) launch_batch_t<double, KIND_PM>(insts, tiles, stepc, j, grid, tx, solute, react, var, lds, st);
-  else launch_batch_t<double, KIND_POP>(insts, tiles, stepc, j, grid, tx, solute, react, var, lds, st);
+  if (kind == KIND_MM_SHORT) launch_batch_t<double, KIND_MM_SHORT>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else if (kind == KIND_MM) launch_batch_t<double, KIND_MM>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else if (kind == KIND_PM) launch_batch_t<double, KIND_PM>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
+  else launch_batch_t<double, KIND_POP>(insts, tiles, ntiles, stepc, j, sy, tx, solute, react, var, lds, st);
   return hipGetLastError();
 }
 

@@ -50,3 +50,37 @@ def _all_heights(lbm, nx, ny, kind, scheme):  # noqa: F811
 def test_population_heights_bitwise(lbm, nx, ny, kind):  # noqa: F811
     _all_heights(lbm, nx, ny, kind, "populations")
 
+
+@pytest.mark.parametrize("kind", ["plain", "all", "flow"])
+@pytest.mark.parametrize("nx,ny", SIZES)
+def test_moment_heights_bitwise(lbm, nx, ny, kind):  # noqa: F811
+    _all_heights(lbm, nx, ny, kind, "moments")
+
+
+def _large(nx, ny, k_r):
+    """A lattice that gives a marching wavefront to every SIMD up to some height,
+    with growth in its first steps."""
+    rng = np.random.default_rng(nx)
+    solid = (rng.uniform(size=(ny, nx)) < 0.2).astype(np.uint8)
+    rho = np.where(solid, 0.0, rng.uniform(0.2, 1.0, size=(ny, nx)))
+    p = inputs.Params(nx=nx, ny=ny, tau_g=0.65 if k_r else 0.0, k_r=k_r, threshold=0.02)
+    return inputs.Problem(p, solid, rho, rho[::-1, ::-1] * (solid == 0) + (solid == 0), rho if k_r else None)
+
+
+# up to 74 and up to 70 rows marching, more shared; the second beyond the size
+# for which nine rows and more are shared
+@pytest.mark.parametrize("nx,ny,k_r", [(901, 1203, 0.02), (1741, 1163, 0.0)])
+def test_large_moment_heights_bitwise(lbm, nx, ny, k_r):  # noqa: F811
+    prob = _large(nx, ny, k_r)
+    want = None
+    for sy, nt in ((4, 0), (1, 1), (2, 1), (5, 0), (6, 1), (8, 1), (9, 0), (10, 1), (12, 0), (12, 1), (14, 0),
+                   (16, 1), (24, 0), (40, 1), (70, 0), (200, 0)):
+        PT.say(f"[tuned shapes] moments {nx}x{ny} height {sy} hint {nt}")
+        sim = lbm.Sim.from_problem(prob, scheme="moments", tile=(64, sy))
+        sim.set_load_hint(nt)
+        sim.step(5)
+        got, ev = sim.fields(), sorted(PT.event_set(sim.events()))
+        sim.close()
+        want = want or (got, ev)
+        assert ev == want[1] and all(np.array_equal(got[k], want[0][k]) for k in got), (sy, nt)
+    assert len(want[1]) > 0 or not k_r
