@@ -164,6 +164,17 @@ bool use_moments(int scheme, const lbm_params& p) {
 // two columns out, the population step's one.
 int owned_cols(bool moments) { return moments ? 60 : 62; }
 
+// Tiles of sy rows of a lattice in the moment step.
+long long moment_tiles(const lbm_params& p, int sy) {
+  const int own = owned_cols(true);
+  return (long long)((p.nx + own - 1) / own) * ((p.ny + sy - 1) / sy);
+}
+
+// The moment step that a single lattice takes with tiles of sy rows.
+int single_kind(const lbm_params& p, bool solute, int sy) {
+  return moment_kind((long long)p.nx * p.ny, solute, sy, moment_tiles(p, sy));
+}
+
 // Rows per workgroup of a handle that no launch shape was set for.
 //
 // Moment step: the lowest tiles (one wavefront per row) that give every CU no
@@ -184,7 +195,7 @@ int default_rows(const lbm_params& p, bool moments, bool solute) {
   const int own = owned_cols(moments), strips = (p.nx + own - 1) / own, most = moments ? 8 : 6;
   int sy = 1;
   while (sy < most && (long long)strips * ((p.ny + sy - 1) / sy) > 256) sy += 1;
-  return moments && moment_kind((long long)p.nx * p.ny, solute, sy) != KIND_MM_SHORT ? 9 : sy;
+  return moments && single_kind(p, solute, sy) != KIND_MM_SHORT ? 9 : sy;
 }
 
 // Populations of the current state written over the stored moments (the
@@ -228,7 +239,7 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   set_model(a, p, s->L.solute);
   for (long long t = 0; t < n; ++t) {
     const int set = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
-    const int kind = !moments ? KIND_POP : (s->mom ? moment_kind(s->L.N, s->L.solute, set) : KIND_PM);
+    const int kind = !moments ? KIND_POP : (s->mom ? single_kind(p, s->L.solute, set) : KIND_PM);
     const int sy = launch_rows(kind, set);
     a.tx_owned = owned_cols(s->mom);
     a.sy = sy;
@@ -747,14 +758,14 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
   };
   const int sys[] = {1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64, 96, 128};
   const bool moments = use_moments(s->scheme, s->p);
-  const bool short_tiles = moments && moment_kind(s->L.N, s->L.solute, SHORT_TILE) == KIND_MM_SHORT;
   std::vector<TuneCand> cands;
   for (int nt = 0; nt < 2 && st == LBM_OK; ++nt) {
     for (int sy : sys) {
       if (sy > 2 * s->p.ny && sy != 8) continue;
-      // A marching wavefront repeats four rows per tile; rows in parallel are
-      // never faster in series.
-      if (moments && !short_tiles ? sy < 6 : sy > (moments ? SHORT_TILE : 14)) continue;
+      // A marching wavefront repeats four rows per tile; a tile that several
+      // workgroups share repeats a lower one.
+      const int kind = moments ? single_kind(s->p, s->L.solute, sy) : KIND_POP;
+      if (kind == KIND_MM ? sy < 6 : launch_rows(kind, sy) < sy) continue;
       TuneCand c{64, sy, nt, 0.0f};
       if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
       cands.push_back(c);
@@ -806,6 +817,7 @@ struct lbm_batch {
   int max_blocks;
   long long step;
   int tx, sy;
+  int kind;                   // of the steps after the first
   int rows;                   // of the tiles launched (launch_rows)
   int scheme;                 // LBM_SCHEME_*
   bool mom;                   // instance buffers hold moments of the last step
@@ -819,6 +831,10 @@ struct lbm_batch {
 
 namespace {
 
+// A batch's tiles have at least eight rows, and shared ones at least five (nine
+// rows as five and four).
+constexpr int LOWEST_BATCH_ROWS = 5;
+
 struct BatchLayout {
   size_t insts, tiles, capi, stepc, table, partial, out, common, total;
   std::vector<Layout> L;
@@ -826,16 +842,17 @@ struct BatchLayout {
   int max_tiles, max_blocks;
 };
 
-int tiles_for(const lbm_params& p, int sy) {
-  const int own = owned_cols(true);
-  return ((p.nx + own - 1) / own) * ((p.ny + sy - 1) / sy);
-}
-
 bool batch_moments(const lbm_batch* b) { return use_moments(b->scheme, b->p[0]); }
 bool batch_variants(const lbm_batch* b) {
   for (const lbm_params& p : b->p)
     if (p.c_eq > 0.0 || p.hold_x > 0 || p.solute_q == 4) return true;
   return false;
+}
+// The moment step that the batch takes with tiles of sy rows.
+int tiled_kind(const lbm_batch* b, int sy) {
+  long long tiles = 0;
+  for (const lbm_params& p : b->p) tiles += moment_tiles(p, sy);
+  return moment_kind(b->nodes, b->solute, sy, tiles);
 }
 int batch_tx(const lbm_batch* b) { return batch_moments(b) ? 64 : b->tx; }
 
@@ -853,7 +870,7 @@ lbm_status batch_layout(int n, const lbm_params* p, int nslots, BatchLayout* B) 
       return fail(LBM_EINVAL, "instance %d: tau, G and accel must be shared by the batch", i);
     if ((p[i].tau_g > 0.0) != solute || (p[i].k_r > 0.0) != react)
       return fail(LBM_EINVAL, "instance %d: solute/reaction switches must be shared", i);
-    B->max_tiles += tiles_for(p[i], 8);
+    B->max_tiles += moment_tiles(p[i], LOWEST_BATCH_ROWS);
     B->max_blocks = std::max(B->max_blocks, (int)std::min<long long>(1024, ((long long)p[i].nx * p[i].ny + 255) / 256));
   }
   size_t off = 0;
@@ -923,7 +940,8 @@ void drop_graph(lbm_batch* b) {
 // Rebuild the per-instance arguments and the tile list for the launch shape.
 lbm_status batch_configure(lbm_batch* b) {
   drop_graph(b);
-  b->rows = batch_moments(b) ? b->sy : launch_rows(KIND_POP, b->sy);
+  b->kind = batch_moments(b) ? tiled_kind(b, b->sy) : KIND_POP;
+  b->rows = launch_rows(b->kind, b->sy);
   b->h_insts.resize(2 * b->n);
   for (int i = 0; i < b->n; ++i) {
     b->h_insts[2 * i] = instance_args(b, i, 0);
@@ -980,9 +998,7 @@ long long batch_nodes(const lbm_batch* b) {
   return n;
 }
 
-int batch_kind(const lbm_batch* b) {
-  return !batch_moments(b) ? KIND_POP : (b->mom ? moment_kind(b->nodes, b->solute, b->sy) : KIND_PM);
-}
+int batch_kind(const lbm_batch* b) { return b->kind == KIND_POP || b->mom ? b->kind : KIND_PM; }
 
 // Queues nsteps batched steps on stream st (offsets 0..nsteps-1 from the
 // device step counter) and the counter's advance; the host-side step and
@@ -1089,7 +1105,7 @@ lbm_status lbm_batch_init(int32_t n, const lbm_params* p, const uint8_t* const* 
   // eight rows where the moment step's short tiles run (moment_kind), see
   // default_rows
   b->tx = 128;
-  b->sy = batch_moments(b) && moment_kind(b->nodes, solute, 8) == KIND_MM_SHORT ? 8 : 24;
+  b->sy = batch_moments(b) && tiled_kind(b, 8) == KIND_MM_SHORT ? 8 : 24;
   b->react = p[0].k_r > 0.0;
   b->graph = nullptr;
   b->graph_chunk = 0;
@@ -1296,10 +1312,10 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t steps, int32_t* tx_out, int3
     return LBM_OK;
   };
   const int sys[] = {8, 9, 10, 12, 16, 20, 24, 32, 40, 48, 64, 80};
-  const bool short_tiles = !batch_moments(b) || moment_kind(b->nodes, b->solute, SHORT_TILE) == KIND_MM_SHORT;
   std::vector<TuneCand> cands;
   for (int sy : sys) {
-    if (short_tiles && sy > SHORT_TILE) continue;  // as in lbm_autotune
+    const int kind = batch_moments(b) ? tiled_kind(b, sy) : KIND_POP;
+    if (launch_rows(kind, sy) < sy) continue;  // as in lbm_autotune
     TuneCand c{64, sy, 0, 0.0f};
     if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
     cands.push_back(c);

@@ -97,22 +97,32 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 // on lattices of half that size.  At 12 rows: 700x500 (31 MB) 11.7 against 29,
 // 1024^2 34.7 against 38.0, 34 capillaries (177 MB) 62.7 against 48.9, 1448^2
 // 59.5 against 48.4.
-constexpr int SHORT_TILE = 12, SHORT_PAIR = 8;
+//
+// Marching needs a wavefront for every SIMD: with fewer tiles than that the step
+// is one wavefront's chain of rows, and a tile is shared by workgroups of at most
+// SHORT_PAIR rows instead (launch_rows), on a lattice of any size.  us per step,
+// marching against shared: 256x32 at 16 rows 32 against 5.7, 1024^2 at 24 rows
+// 50.5 against 26, 1448^2 at 64 rows 122 against 45, 2500^2 at 128 rows 260 against
+// 177.
+constexpr int SHORT_TILE = 12, SHORT_PAIR = 8, SIMDS = 1024;
 constexpr long long SHORT_BYTES = 240ll << 20;
-inline int moment_kind(long long nodes, bool solute, int sy) {
+inline int moment_kind(long long nodes, bool solute, int sy, long long tiles) {
+  if (tiles < SIMDS) return KIND_MM_SHORT;
   const long long bytes = nodes * (solute ? 88 : 48);
   return sy <= SHORT_TILE && bytes <= (sy <= SHORT_PAIR ? SHORT_BYTES : SHORT_BYTES / 2) ? KIND_MM_SHORT
                                                                                         : KIND_MM;
 }
 
 // Rows of the tiles that a step of this kind is launched with where tiles of sy
-// rows are set.  A population workgroup owns at most POP_ROWS rows, and a taller
-// tile's workgroups share its rows as evenly as may be (which is launched as
-// lower tiles).  16 rows as 8 and 8 against 14 and 2, us per step: 1024^2 38.6,
-// 54.1; 2048x1100 with the hint 113, 130; 2500^2 397, 425.
+// rows are set.  The workgroups that share a tall tile get rows as even as may be
+// (which is launched as lower tiles).  Population tiles, at most POP_ROWS rows a
+// workgroup: 16 rows as 8 and 8 against 14 and 2, us per step: 1024^2 38.6, 54.1;
+// 2048x1100 with the hint 113, 130; 2500^2 397, 425.
 constexpr int POP_ROWS = 14;
 inline int launch_rows(int kind, int sy) {
-  const int most = kind == KIND_POP || kind == KIND_PM ? POP_ROWS : sy;
+  const int most = kind == KIND_MM || (kind == KIND_MM_SHORT && sy <= SHORT_TILE) ? sy
+                   : kind == KIND_MM_SHORT                                        ? SHORT_PAIR
+                                                                                  : POP_ROWS;
   const int parts = (sy + most - 1) / most;
   return (sy + parts - 1) / parts;
 }
