@@ -240,7 +240,7 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   for (long long t = 0; t < n; ++t) {
     const int set = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
     const int kind = !moments ? KIND_POP : (s->mom ? single_kind(p, s->L.solute, set) : KIND_PM);
-    const int sy = launch_rows(kind, set);
+    const int sy = launch_rows(kind, set, moment_tiles(p, set));
     a.tx_owned = owned_cols(s->mom);
     a.sy = sy;
     a.nsegs = (p.ny + sy - 1) / sy;
@@ -765,7 +765,7 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
       // A marching wavefront repeats four rows per tile; a tile that several
       // workgroups share repeats a lower one.
       const int kind = moments ? single_kind(s->p, s->L.solute, sy) : KIND_POP;
-      if (kind == KIND_MM ? sy < 6 : launch_rows(kind, sy) < sy) continue;
+      if (kind == KIND_MM ? sy < 6 : launch_rows(kind, sy, moment_tiles(s->p, sy)) < sy) continue;
       TuneCand c{64, sy, nt, 0.0f};
       if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
       cands.push_back(c);
@@ -848,12 +848,17 @@ bool batch_variants(const lbm_batch* b) {
     if (p.c_eq > 0.0 || p.hold_x > 0 || p.solute_q == 4) return true;
   return false;
 }
-// The moment step that the batch takes with tiles of sy rows.
-int tiled_kind(const lbm_batch* b, int sy) {
-  long long tiles = 0;
-  for (const lbm_params& p : b->p) tiles += moment_tiles(p, sy);
-  return moment_kind(b->nodes, b->solute, sy, tiles);
-}
+// The step that the batch takes after its first one with tiles of sy rows, and the
+// rows of the tiles it is launched with.
+struct BatchStep {
+  int kind = KIND_POP, rows;
+  BatchStep(const lbm_batch* b, int sy) {
+    long long tiles = 0;
+    for (const lbm_params& p : b->p) tiles += moment_tiles(p, sy);
+    if (batch_moments(b)) kind = moment_kind(b->nodes, b->solute, sy, tiles);
+    rows = launch_rows(kind, sy, tiles);
+  }
+};
 int batch_tx(const lbm_batch* b) { return batch_moments(b) ? 64 : b->tx; }
 
 lbm_status batch_layout(int n, const lbm_params* p, int nslots, BatchLayout* B) {
@@ -940,8 +945,9 @@ void drop_graph(lbm_batch* b) {
 // Rebuild the per-instance arguments and the tile list for the launch shape.
 lbm_status batch_configure(lbm_batch* b) {
   drop_graph(b);
-  b->kind = batch_moments(b) ? tiled_kind(b, b->sy) : KIND_POP;
-  b->rows = launch_rows(b->kind, b->sy);
+  const BatchStep step(b, b->sy);
+  b->kind = step.kind;
+  b->rows = step.rows;
   b->h_insts.resize(2 * b->n);
   for (int i = 0; i < b->n; ++i) {
     b->h_insts[2 * i] = instance_args(b, i, 0);
@@ -1105,7 +1111,7 @@ lbm_status lbm_batch_init(int32_t n, const lbm_params* p, const uint8_t* const* 
   // eight rows where the moment step's short tiles run (moment_kind), see
   // default_rows
   b->tx = 128;
-  b->sy = batch_moments(b) && tiled_kind(b, 8) == KIND_MM_SHORT ? 8 : 24;
+  b->sy = BatchStep(b, 8).kind == KIND_MM_SHORT ? 8 : 24;
   b->react = p[0].k_r > 0.0;
   b->graph = nullptr;
   b->graph_chunk = 0;
@@ -1314,8 +1320,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t steps, int32_t* tx_out, int3
   const int sys[] = {8, 9, 10, 12, 16, 20, 24, 32, 40, 48, 64, 80};
   std::vector<TuneCand> cands;
   for (int sy : sys) {
-    const int kind = batch_moments(b) ? tiled_kind(b, sy) : KIND_POP;
-    if (launch_rows(kind, sy) < sy) continue;  // as in lbm_autotune
+    if (BatchStep(b, sy).rows < sy) continue;  // as in lbm_autotune
     TuneCand c{64, sy, 0, 0.0f};
     if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
     cands.push_back(c);

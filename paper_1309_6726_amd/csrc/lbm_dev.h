@@ -83,46 +83,60 @@ __host__ __device__ inline unsigned pending_bit(long long n) {
 // populations by gathering from the neighbours) and stores moments.
 enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 
-// Which moment step runs tiles of sy rows when the lattices it advances
-// together hold `nodes` nodes.  Tiles of at most SHORT_TILE rows run with one
-// wavefront per row while the step's two buffers fit the 256 MB memory-side
-// cache, taller ones and larger lattices with one wavefront marching up the
-// tile.  Measured on square preforms, us per step (best height of each):
-// 1024^2 (92 MB) 26.7 against 35.2, 1448^2 (184 MB) 46.7 against 48.4,
-// 1600^2 (225 MB) 55.6 against 60.6, 1700^2 (254 MB) 76.8 against 77.7,
-// 2048^2 (369 MB) 117 against 104.  Once the reads come from HBM, the short
-// tiles' loads (one round trip per tile, two tiles per CU) are not covered.
+// Which moment step runs `tiles` tiles of sy rows when the lattices it advances
+// together hold `nodes` nodes: one wavefront per row (short tiles) or one marching
+// up each tile.
 //
-// Above SHORT_PAIR rows a CU holds one workgroup instead of two, which pays only
-// on lattices of half that size.  At 12 rows: 700x500 (31 MB) 11.7 against 29,
-// 1024^2 34.7 against 38.0, 34 capillaries (177 MB) 62.7 against 48.9, 1448^2
-// 59.5 against 48.4.
+// Short tiles while the step's two buffers fit the 256 MB memory-side cache.
+// Measured on square preforms, us per step (best height of each): 1024^2 (92 MB)
+// 26.7 against 35.2, 1448^2 (184 MB) 46.7 against 48.4, 1600^2 (225 MB) 55.6
+// against 60.6, 1700^2 (254 MB) 76.8 against 77.7, 2048^2 (369 MB) 117 against 104.
+// Once the reads come from HBM, the short tiles' loads (one round trip per
+// workgroup, two workgroups per CU) are not covered.
+//
+// That is the best height's line; a set height has its own.  Eight rows and up to
+// four fill a CU with two and three workgroups (24 wavefronts), five and six leave
+// places empty (20 and 18) and repeat half as much again.  us per step, short
+// against marching, without solute in brackets: five rows 1150^2 39.9, 40.9,
+// 1600^2 71.2, 67.5 (52.3, 52.1), 2100^2 (86.5, 82.5); six rows 1250^2 44.5, 45.6
+// (33.3, 35.6), 1448^2 59.2, 53.9 (43.8, 41.4), 2100^2 (84.7, 76.4).  Workgroups of
+// five to eight share a tile of ten rows and more (launch_rows): ten rows 1024^2
+// 33.0, 33.4, 1150^2 39.9, 42.5, 1250^2 45.0, 43.2 (33.3, 33.7), 1448^2 (46, 41.7);
+// twelve rows 1024^2 32.5, 38.3, 1150^2 39.5, 38.3, 1600^2 (52, 47.7).
 //
 // Marching needs a wavefront for every SIMD: with fewer tiles than that the step
-// is one wavefront's chain of rows, and a tile is shared by workgroups of at most
-// SHORT_PAIR rows instead (launch_rows), on a lattice of any size.  us per step,
-// marching against shared: 256x32 at 16 rows 32 against 5.7, 1024^2 at 24 rows
-// 50.5 against 26, 1448^2 at 64 rows 122 against 45, 2500^2 at 128 rows 260 against
-// 177.
-constexpr int SHORT_TILE = 12, SHORT_PAIR = 8, SIMDS = 1024;
-constexpr long long SHORT_BYTES = 240ll << 20;
+// is one wavefront's chain of rows, and tiles are short on a lattice of any size.
+// us per step, marching against shared: 256x32 at 16 rows 32 against 5.7, 1024^2 at
+// 24 rows 50.5 against 26, 1448^2 at 64 rows 122 against 45, 2500^2 at 128 rows 260
+// against 177.
+constexpr int SHORT_TILE = 12, SHORT_ROWS = 8, SIMDS = 1024;
 inline int moment_kind(long long nodes, bool solute, int sy, long long tiles) {
+  constexpr long long SHORT_BYTES = 240ll << 20, SHARED_NODES = 1400000, LOOSE_NODES = 2000000;
   if (tiles < SIMDS) return KIND_MM_SHORT;
-  const long long bytes = nodes * (solute ? 88 : 48);
-  return sy <= SHORT_TILE && bytes <= (sy <= SHORT_PAIR ? SHORT_BYTES : SHORT_BYTES / 2) ? KIND_MM_SHORT
-                                                                                        : KIND_MM;
+  if (nodes * (solute ? 88 : 48) > SHORT_BYTES) return KIND_MM;
+  if (sy > SHORT_ROWS) return nodes <= SHARED_NODES ? KIND_MM_SHORT : KIND_MM;
+  return (sy == 5 || sy == 6) && nodes > LOOSE_NODES ? KIND_MM : KIND_MM_SHORT;
 }
 
-// Rows of the tiles that a step of this kind is launched with where tiles of sy
-// rows are set.  The workgroups that share a tall tile get rows as even as may be
-// (which is launched as lower tiles).  Population tiles, at most POP_ROWS rows a
-// workgroup: 16 rows as 8 and 8 against 14 and 2, us per step: 1024^2 38.6, 54.1;
-// 2048x1100 with the hint 113, 130; 2500^2 397, 425.
+// Rows of the tiles that a step of this kind is launched with where `tiles` tiles of
+// sy rows are set.  The workgroups that share a tall tile get rows as even as may
+// be (which is launched as lower tiles).
+//
+// Population tiles, at most POP_ROWS rows a workgroup: 16 rows as 8 and 8 against
+// 14 and 2, us per step: 1024^2 38.6, 54.1; 2048x1100 with the hint 113, 130; 2500^2
+// 397, 425.
+//
+// Short moment tiles: ten rows and more leave a CU one workgroup with no more rows
+// than two of five to eight have, which pays while there are hardly two for each
+// CU.  Whole against shared, us per step, without solute in brackets: 2048x76 at
+// 12 rows (245 tiles) 6.9, 7.1, 512^2 at 10 rows (468 tiles) 11.2, 11.8, 800^2 at 10
+// rows (1120 tiles) 25.0, 21.9, 1024^2 at 10 rows 38.0, 33.0 and at 9 rows 33.3, 33.0
+// (23.9, 24.7).
 constexpr int POP_ROWS = 14;
-inline int launch_rows(int kind, int sy) {
-  const int most = kind == KIND_MM || (kind == KIND_MM_SHORT && sy <= SHORT_TILE) ? sy
-                   : kind == KIND_MM_SHORT                                        ? SHORT_PAIR
-                                                                                  : POP_ROWS;
+inline int launch_rows(int kind, int sy, long long tiles) {
+  int most = POP_ROWS;
+  if (kind == KIND_MM || (kind == KIND_MM_SHORT && sy <= (tiles <= 512 ? SHORT_TILE : 9))) most = sy;
+  else if (kind == KIND_MM_SHORT) most = SHORT_ROWS;
   const int parts = (sy + most - 1) / most;
   return (sy + parts - 1) / parts;
 }

@@ -789,7 +789,7 @@ __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) 
 // SIMDs busy for 70% of a step at 1448^2), but with 24 wavefronts per CU
 // resident (72 VGPRs, 74 KB LDS) instead of mom_wave's 12: 1024^2 preform 26.7
 // us against 35.2, 700x500 11.1 against 16.1.  Eight rows because two workgroups of
-// 12 wavefronts share a CU's LDS; nine to twelve leave one.
+// 12 wavefronts share a CU's LDS; nine to twelve leave one (launch_rows).
 static_assert(SHORT_TILE + 4 <= 16, "one wavefront per row within a workgroup");
 
 // stream_row with the vertical links into LDS rows of LROW values (lane t at
