@@ -193,9 +193,10 @@ lbm_status lbm_get_tile(const lbm_sim* sim, int32_t* tx, int32_t* sy);
 
 /* Cache hint on the step's loads: 0 (default) the normal policy, 1 the
  * non-temporal hint on the streamed state (population step: the populations;
- * moment step: the moments of a workgroup's own rows and the solute
- * populations, while the halo rows, which the neighbouring workgroup reads
- * too, and the precipitate keep the normal policy).  Which is faster
+ * moment step with one wavefront per tile: the moments of a workgroup's own rows
+ * and the solute populations, while the halo rows, which the neighbouring
+ * workgroup reads too, and the precipitate keep the normal policy; with one
+ * wavefront per row: none, as it only costs there).  Which is faster
  * depends on how the lattice's footprint meets the GPU's caches, so
  * lbm_autotune chooses it along with the launch shape.  It applies to the
  * single-lattice steps (not the batched step) and changes no result bit. */

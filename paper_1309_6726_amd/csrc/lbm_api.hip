@@ -171,8 +171,8 @@ long long moment_tiles(const lbm_params& p, int sy) {
 }
 
 // The moment step that a single lattice takes with tiles of sy rows.
-int single_kind(const lbm_params& p, bool solute, int sy) {
-  return moment_kind((long long)p.nx * p.ny, solute, sy, moment_tiles(p, sy));
+int single_kind(const lbm_params& p, bool solute, int sy, int nt) {
+  return moment_kind((long long)p.nx * p.ny, solute, sy, moment_tiles(p, sy), nt);
 }
 
 // Rows per workgroup of a handle that no launch shape was set for.
@@ -195,7 +195,7 @@ int default_rows(const lbm_params& p, bool moments, bool solute) {
   const int own = owned_cols(moments), strips = (p.nx + own - 1) / own, most = moments ? 8 : 6;
   int sy = 1;
   while (sy < most && (long long)strips * ((p.ny + sy - 1) / sy) > 256) sy += 1;
-  return moments && single_kind(p, solute, sy) != KIND_MM_SHORT ? 9 : sy;
+  return moments && single_kind(p, solute, sy, 0) != KIND_MM_SHORT ? 9 : sy;
 }
 
 // Populations of the current state written over the stored moments (the
@@ -239,7 +239,7 @@ lbm_status queue_steps(lbm_sim* s, long long n) {
   set_model(a, p, s->L.solute);
   for (long long t = 0; t < n; ++t) {
     const int set = s->sy ? s->sy : default_rows(p, moments && s->mom, s->L.solute);
-    const int kind = !moments ? KIND_POP : (s->mom ? single_kind(p, s->L.solute, set) : KIND_PM);
+    const int kind = !moments ? KIND_POP : (s->mom ? single_kind(p, s->L.solute, set, s->nt) : KIND_PM);
     const int sy = launch_rows(kind, set, moment_tiles(p, set));
     a.tx_owned = owned_cols(s->mom);
     a.sy = sy;
@@ -762,10 +762,11 @@ lbm_status lbm_autotune(lbm_sim* s, int32_t steps, int32_t* tx_out, int32_t* sy_
   for (int nt = 0; nt < 2 && st == LBM_OK; ++nt) {
     for (int sy : sys) {
       if (sy > 2 * s->p.ny && sy != 8) continue;
-      // A marching wavefront repeats four rows per tile; a tile that several
-      // workgroups share repeats a lower one.
-      const int kind = moments ? single_kind(s->p, s->L.solute, sy) : KIND_POP;
+      // A marching wavefront repeats four rows per tile.  A tile that several
+      // workgroups share repeats a lower one, a short one runs without the hint.
+      const int kind = moments ? single_kind(s->p, s->L.solute, sy, nt) : KIND_POP;
       if (kind == KIND_MM ? sy < 6 : launch_rows(kind, sy, moment_tiles(s->p, sy)) < sy) continue;
+      if (kind == KIND_MM_SHORT && nt) continue;
       TuneCand c{64, sy, nt, 0.0f};
       if ((st = time_shape(c, steps, &c.ms)) != LBM_OK) break;
       cands.push_back(c);
@@ -855,7 +856,7 @@ struct BatchStep {
   BatchStep(const lbm_batch* b, int sy) {
     long long tiles = 0;
     for (const lbm_params& p : b->p) tiles += moment_tiles(p, sy);
-    if (batch_moments(b)) kind = moment_kind(b->nodes, b->solute, sy, tiles);
+    if (batch_moments(b)) kind = moment_kind(b->nodes, b->solute, sy, tiles, 0);
     rows = launch_rows(kind, sy, tiles);
   }
 };

@@ -109,11 +109,19 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 // us per step, marching against shared: 256x32 at 16 rows 32 against 5.7, 1024^2 at
 // 24 rows 50.5 against 26, 1448^2 at 64 rows 122 against 45, 2500^2 at 128 rows 260
 // against 177.
+//
+// nt: the non-temporal load hint is set.  Short tiles, whose neighbours read their
+// halo rows at the same time, are slower with it and run without; where there are
+// many of them (low ones on large lattices) a marching wavefront with it is faster
+// still.  us per step with the hint set, marching against short without it: 800^2 at
+// one row (11200 tiles) 33.8, 37.3, 1024^2 at two rows (9216) 38.2, 39.7, 2100^2
+// without solute at four rows (18375) 79.5, 83.7; 1024^2 at three rows (6156) 36.7,
+// 34.1, at eight 37.1, 25.6, 1600^2 at eight (5400) 67.6, 55.0 (72.2 with the hint).
 constexpr int SHORT_TILE = 12, SHORT_ROWS = 8, SIMDS = 1024;
-inline int moment_kind(long long nodes, bool solute, int sy, long long tiles) {
-  constexpr long long SHORT_BYTES = 240ll << 20, SHARED_NODES = 1400000, LOOSE_NODES = 2000000;
+inline int moment_kind(long long nodes, bool solute, int sy, long long tiles, int nt) {
+  constexpr long long SHORT_BYTES = 240ll << 20, SHARED_NODES = 1400000, LOOSE_NODES = 2000000, HINTED_TILES = 9000;
   if (tiles < SIMDS) return KIND_MM_SHORT;
-  if (nodes * (solute ? 88 : 48) > SHORT_BYTES) return KIND_MM;
+  if (nodes * (solute ? 88 : 48) > SHORT_BYTES || (nt && tiles > HINTED_TILES)) return KIND_MM;
   if (sy > SHORT_ROWS) return nodes <= SHARED_NODES ? KIND_MM_SHORT : KIND_MM;
   return (sy == 5 || sy == 6) && nodes > LOOSE_NODES ? KIND_MM : KIND_MM_SHORT;
 }
@@ -144,7 +152,7 @@ inline int launch_rows(int kind, int sy, long long tiles) {
 // Records a message for lbm_last_error() and returns s.
 lbm_status fail(lbm_status s, const char* fmt, ...);
 
-// nt: non-temporal load hint (moment and population steps)
+// nt: non-temporal load hint
 hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st);
 // var: some instance uses a reaction or solute-lattice variant
 // One batched step at index *stepc + j; a sequence of n such launches

@@ -91,13 +91,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)extent, 0x00020000);
 }
 
-// One dword per lane at byte offset voff + soff, with the non-temporal hint
-// where NT and hint say so.
+// One dword per lane at byte offset voff + soff, with the non-temporal hint if NT.
 template <bool NT>
-__device__ __forceinline__ unsigned load_b32(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff,
-                                             bool hint) {
-  return NT && hint ? (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, CPOL_NT)
-                    : (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0);
+__device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+  return __uint_as_float(
+      (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, NT ? CPOL_NT : 0));
 }
 
 // Workgroup-wide LDS barrier that leaves outstanding global memory operations
@@ -812,7 +810,7 @@ struct RowShares {
   }
 };
 
-template <bool SOLUTE, bool REACT, bool VAR, typename R, bool NT>
+template <bool SOLUTE, bool REACT, bool VAR, typename R>
 __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, char* lds_raw) {
   // links of both components out of rows 0 .. nrows-3 (up) and 2 .. nrows-1
   // (down), densities of rows 1 .. nrows-2
@@ -867,22 +865,22 @@ __device__ __forceinline__ void mom_rows(const StepArgs& a, int strip, int seg, 
     mu = mask_of(yu);
     auto load_moments = [&](unsigned vm) {
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
-        mo[q] = __uint_as_float(load_b32<NT>(rMin, vm, (unsigned)q * PB, crow));
+      for (int q = 0; q < 6; ++q) mo[q] = load_f32<false>(rMin, vm, (unsigned)q * PB);
     };
     // a node solid in state n-1 holds zeros (every step that stores moments
-    // writes them there), so the loads need not wait for the mask
-    if (!NT) load_moments(active ? 4u * idx : NONE);
+    // writes them there), so the loads need not wait for the mask (written in
+    // place instead of called, they are scheduled otherwise: 1024^2 at five rows
+    // 36.2 us instead of 33.0)
+    load_moments(active ? 4u * idx : NONE);
     const lanes_t row = __ballot(m0 & SPREV);
     const Neighbours prev(__ballot(md & SPREV), row, __ballot(mu & SPREV));
     const bool fluid = on_lane(~row);
-    if (NT) load_moments(fluid ? 4u * idx : NONE);
     if (crow) {
       if (SOLUTE) {
         const unsigned vg = owner && fluid ? 4u * idx : NONE;
 #pragma unroll
         for (int q = 0; q < 5; ++q)
-          gv[q] = __uint_as_float(load_b32<NT>(rGin, vg, (unsigned)q * PB, true));
+          gv[q] = load_f32<false>(rGin, vg, (unsigned)q * PB);
       }
       if (REACT) {
         const lanes_t here = __ballot(m0 & SCUR);
@@ -1035,14 +1033,14 @@ __device__ __forceinline__ void pop_rows(const StepArgs& a, int strip, int seg, 
     }
     const unsigned vf = m0 & SPREV ? NONE : 4u * idx;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) f[q] = __uint_as_float(load_b32<NT>(rF1, vf, (unsigned)q * PB, true));
+    for (int q = 0; q < 9; ++q) f[q] = load_f32<NT>(rF1, vf, (unsigned)q * PB);
 #pragma unroll
-    for (int q = 0; q < 9; ++q) f[9 + q] = __uint_as_float(load_b32<NT>(rF2, vf, (unsigned)q * PB, true));
+    for (int q = 0; q < 9; ++q) f[9 + q] = load_f32<NT>(rF2, vf, (unsigned)q * PB);
     if (crow) {
       if (SOLUTE) {
         const unsigned vg = owner ? vf : NONE;
 #pragma unroll
-        for (int q = 0; q < 5; ++q) g[q] = __uint_as_float(load_b32<NT>(rGin, vg, (unsigned)q * PB, true));
+        for (int q = 0; q < 5; ++q) g[q] = load_f32<NT>(rGin, vg, (unsigned)q * PB);
       }
       if (REACT) {
         const lanes_t here = __ballot(m0 & SCUR);
@@ -1177,7 +1175,7 @@ __device__ __forceinline__ void run_tile(const StepArgs& a, int strip, int seg, 
   if constexpr (KIND == KIND_MM)
     mom_wave<SOLUTE, REACT, VAR, R, NT, BATCH>(a, strip, seg);
   else if constexpr (KIND == KIND_MM_SHORT)
-    mom_rows<SOLUTE, REACT, VAR, R, NT>(a, strip, seg, lds_raw);
+    mom_rows<SOLUTE, REACT, VAR, R>(a, strip, seg, lds_raw);
   else
     pop_rows<SOLUTE, REACT, VAR, R, KIND == KIND_PM, NT>(a, strip, seg, lds_raw);
 }
@@ -1716,8 +1714,9 @@ void launch_step_t(const StepArgs& a, int T, int tx, size_t lds, hipStream_t st)
     hipLaunchKernelGGL((k_step<false, false, false, R, KIND, NT>), step_grid(KIND, a.sy, T), dim3(tx), lds, st, a);
 }
 
-// nt: the non-temporal load hint, compiled for the moment and population
-// steps (the one-off PM step ignores it).  The arithmetic is FP64 throughout.
+// nt: the non-temporal load hint, compiled for the marching moment step and the
+// population step (moment_kind says why not for short tiles; the one-off PM step
+// ignores it too).  The arithmetic is FP64 throughout.
 hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st) {
   const int T = a.nstrips * a.nsegs;
   const int tx = step_threads(kind, a.sy);
@@ -1725,8 +1724,8 @@ hipError_t launch_step(const StepArgs& a, int kind, int nt, hipStream_t st) {
   switch (kind + (nt ? 8 : 0)) {
     case KIND_MM: launch_step_t<double, KIND_MM, false>(a, T, tx, lds, st); break;
     case KIND_MM + 8: launch_step_t<double, KIND_MM, true>(a, T, tx, lds, st); break;
-    case KIND_MM_SHORT: launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st); break;
-    case KIND_MM_SHORT + 8: launch_step_t<double, KIND_MM_SHORT, true>(a, T, tx, lds, st); break;
+    case KIND_MM_SHORT:
+    case KIND_MM_SHORT + 8: launch_step_t<double, KIND_MM_SHORT, false>(a, T, tx, lds, st); break;
     case KIND_POP: launch_step_t<double, KIND_POP, false>(a, T, tx, lds, st); break;
     case KIND_POP + 8: launch_step_t<double, KIND_POP, true>(a, T, tx, lds, st); break;
     default: launch_step_t<double, KIND_PM, false>(a, T, tx, lds, st);
