@@ -225,8 +225,9 @@ lbm_status lbm_set_scheme(lbm_sim* sim, int32_t scheme);
  * one with the lowest median and report its shape and median time per step
  * (the hint is read with lbm_get_load_hint).  When the environment variable
  * LBM_AUTOTUNE_CACHE names a file, a cached choice for the same (GPU
- * architecture, nx x ny, solute/reaction switches, scheme) is used without
- * timing, and new choices are appended to it as JSON lines
+ * architecture, nx x ny, solute/reaction switches, scheme, generation of the
+ * library's step kernels) is used without timing, and new choices are appended
+ * to it as JSON lines
  * {"key": ..., "tx": ..., "sy": ..., "ms": ..., "nt": ...}. */
 lbm_status lbm_autotune(lbm_sim* sim, int32_t steps_per_candidate, int32_t* tx, int32_t* sy,
                         double* best_ms_per_step);

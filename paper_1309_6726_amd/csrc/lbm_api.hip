@@ -624,9 +624,14 @@ lbm_status lbm_get_tile(const lbm_sim* s, int32_t* tx, int32_t* sy) {
 
 namespace {
 
-// Autotune cache: a JSON-lines file named by LBM_AUTOTUNE_CACHE, one object
-// per line {"key": "<arch>:<nx>x<ny>:<flags>:<scheme>", "tx": .., "sy": .., "ms": ..,
-// "nt": ..} (a line without "nt" means the default load policy).
+// Autotune cache: a JSON-lines file named by LBM_AUTOTUNE_CACHE, one object per line
+// {"key": "<arch>:<nx>x<ny>:<flags>:<scheme>:k<kernels>", "tx": .., "sy": .., "ms": ..,
+// "nt": ..} (a line without "nt" means the default load policy).  TUNED_KERNELS
+// counts the generations of step kernels and of the rules between them: a shape and
+// its time hold for the ones that it was timed with, and a lattice tuned on others
+// is tuned again.  256x32 at the 16 rows that suited a marching wavefront best takes
+// 5.4 us a step, at the one row that suits a wavefront per row 4.2.
+constexpr int TUNED_KERNELS = 2;  // the first generation's keys had no count
 std::string tune_key(const lbm_sim* s) {
   hipDeviceProp_t prop{};
   int dev = 0;
@@ -637,8 +642,9 @@ std::string tune_key(const lbm_sim* s) {
       if (*c == ':' || *c == '"' || *c == ' ') *c = '_';
   }
   char buf[160];
-  snprintf(buf, sizeof buf, "%s:%dx%d:%d:%s", arch, s->p.nx, s->p.ny,
-           (s->L.solute ? 1 : 0) | (s->L.react ? 2 : 0), use_moments(s->scheme, s->p) ? "mom" : "pop");
+  snprintf(buf, sizeof buf, "%s:%dx%d:%d:%s:k%d", arch, s->p.nx, s->p.ny,
+           (s->L.solute ? 1 : 0) | (s->L.react ? 2 : 0), use_moments(s->scheme, s->p) ? "mom" : "pop",
+           TUNED_KERNELS);
   return buf;
 }
 
