@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -363,6 +364,14 @@ lbm_status surr_gradients(surr_net* s, const float* x, const float* y, int32_t n
 lbm_status surr_predict(surr_net* s, const float* x, int32_t n, float* y) {
   if (!s || !x || !y || n < 0) return fail(LBM_EINVAL, "bad arguments");
   if (n == 0) return LBM_OK;
+  // a chunk's answers may lie over the queries of later ones
+  std::unique_ptr<float[]> own;
+  if (n > HOST_ROWS && overlap(x, y, n)) {
+    own.reset(new (std::nothrow) float[(size_t)n * NIN]);
+    if (!own) return fail(LBM_ENOMEM, "copy of %d queries", n);
+    memcpy(own.get(), x, (size_t)n * NIN * 4);
+    x = own.get();
+  }
   CallBuffer host;
   lbm_status st = host.take();
   if (st != LBM_OK) return st;

@@ -84,7 +84,13 @@ struct PackArgs {
   int first[NL], rn[NL], rk[NL], n[NL], k[NL];
 };
 
-// y [rows x NOUT] (host-visible or device memory).
+// Whether n queries at x and their answers at y share memory.
+inline bool overlap(const float* x, const float* y, size_t n) {
+  return (uintptr_t)x < (uintptr_t)(y + n * NOUT) && (uintptr_t)y < (uintptr_t)(x + n * NIN);
+}
+
+// y [rows x NOUT] (host-visible or device memory; with at most 1024 rows it may
+// overlap the queries).
 hipError_t predict(const NetArgs& net, const RowArgs& r, float* y, hipStream_t st);
 hipError_t forward_backward(const NetArgs& net, const RowArgs& r, const TrainArgs& t, hipStream_t st);
 hipError_t update(const UpdateArgs& u, hipStream_t st);

@@ -490,8 +490,46 @@ __global__ void k_pack(const PackArgs a) {
                                       : a.p[l][a.n[l] * a.k[l] + i - nw];
 }
 
+// Moves `count` values, which may overlap where they go: every thread holds its
+// own until all are read.
+constexpr int MOVE = 10;  // values per thread: 1024 queries
+__global__ void __launch_bounds__(512) k_move(const float* x, float* to, int count) {
+  float v[MOVE];
+#pragma unroll
+  for (int i = 0; i < MOVE; ++i) {
+    const int e = threadIdx.x + 512 * i;
+    v[i] = e < count ? x[e] : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < MOVE; ++i) asm volatile("" : "+v"(v[i]));  // arrived
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < MOVE; ++i) {
+    const int e = threadIdx.x + 512 * i;
+    if (e < count) to[e] = v[i];
+  }
+}
+
 // ---- launchers ------------------------------------------------------------
+// Answers over their own queries: the queries are moved to the end of the answers
+// and taken 32 at a time, first to last.  Of n rows, the first k answers end at
+// value k NOUT and the queries after the first k begin at n (NOUT - NIN) + k NIN, which is
+// no less for k <= n: a launch overwrites no query of a later one.
+static hipError_t predict_in_place(const NetArgs& net, const RowArgs& r, float* y, hipStream_t st) {
+  if (r.idx || r.rows * NIN > MOVE * 512) return hipErrorInvalidValue;
+  float* const x = y + (size_t)r.rows * (NOUT - NIN);
+  hipLaunchKernelGGL(k_move, dim3(1), dim3(512), 0, st, r.X, x, r.rows * NIN);
+  for (int first = 0; first < r.rows; first += ROWS) {
+    const RowArgs part{x + (size_t)first * NIN, nullptr, r.rows - first < ROWS ? r.rows - first : ROWS};
+    hipLaunchKernelGGL(k_rows<false>, dim3(1), dim3(512), 0, st, net, part, TrainArgs{}, y + (size_t)first * NOUT);
+  }
+  return hipGetLastError();
+}
+
 hipError_t predict(const NetArgs& net, const RowArgs& r, float* y, hipStream_t st) {
+  // one workgroup reads all its queries before it answers, several do not wait
+  // for each other
+  if (r.rows > ROWS && overlap(r.X, y, r.rows)) return predict_in_place(net, r, y, st);
   hipLaunchKernelGGL(k_rows<false>, dim3((r.rows + ROWS - 1) / ROWS), dim3(512), 0, st, net, r, TrainArgs{}, y);
   return hipGetLastError();
 }
