@@ -24,6 +24,15 @@
  *   - `stream` (a hipStream_t) and `workspace` (device memory) are borrowed:
  *     the caller keeps both alive until lbm_destroy.  All device work of a
  *     handle is queued on that stream.
+ *   - The library allocates no device memory.  lbm_fields and lbm_batch_fields
+ *     into ordinary host memory, and every surr_* call that returns or takes
+ *     parameters, gradients, losses or predictions in host memory, pass the data
+ *     through pinned host memory that the library allocates when it is first
+ *     needed, lends to one call at a time and keeps for later ones (eight blocks
+ *     of 1 MB and two of 8 MB at most, until the process ends).  Without it
+ *     fields are copied more slowly, and a surr_* call returns LBM_ENOMEM.  From
+ *     16 MB on, fields are copied by four threads that end with the call.
+ *   - Destroying a handle does not wait for work of other streams.
  *   - lbm_step only queues work.  Faults of queued kernels surface at the
  *     next synchronising call (lbm_observe, lbm_fields, lbm_events,
  *     lbm_save), which returns LBM_EDEVICE.
@@ -42,7 +51,7 @@ extern "C" {
 typedef enum {
   LBM_OK = 0,
   LBM_EINVAL = -1,     /* bad argument, parameter, mask value or buffer size */
-  LBM_ENOMEM = -2,     /* host allocation failed */
+  LBM_ENOMEM = -2,     /* host allocation (pinned memory included) failed */
   LBM_EDEVICE = -3,    /* a HIP call or a queued kernel failed */
   LBM_ENONFINITE = -4, /* a density or concentration is NaN/Inf: handle poisoned */
   LBM_ESTATE = -5      /* handle poisoned by an earlier LBM_ENONFINITE/LBM_EDEVICE */
@@ -182,12 +191,13 @@ lbm_status lbm_events(lbm_sim* sim, int64_t first, lbm_event* buf, int64_t cap, 
 lbm_status lbm_save(lbm_sim* sim, void* blob, size_t cap, size_t* n);
 lbm_status lbm_load(lbm_sim* sim, const void* blob, size_t n);
 
-/* Launch shape of the fused step: sy owned rows per workgroup (1..4096).  A
- * workgroup covers 62 owned columns (60 in the moment scheme) with one
- * wavefront per row, or with one wavefront per tile where the moment step finds
- * that faster; tx (64, 128 or 256) is accepted and reported but decides nothing.
- * Until a shape is set, one is chosen from the lattice.  The shape changes no
- * result bit. */
+/* Launch shape of the fused step: tiles of 62 owned columns (60 in the moment
+ * scheme) by sy rows (1..4096), run with one wavefront per row, or with one
+ * wavefront per tile where the moment step finds that faster.  With one per row
+ * a workgroup takes at most 14 rows (in the moment scheme 12, on larger lattices
+ * 8 or 9), and several share a taller tile.  tx (64, 128 or 256) is accepted and
+ * reported but decides nothing.  Until a shape is set, one is chosen from the
+ * lattice.  The shape changes no result bit. */
 lbm_status lbm_set_tile(lbm_sim* sim, int32_t tx, int32_t sy);
 lbm_status lbm_get_tile(const lbm_sim* sim, int32_t* tx, int32_t* sy);
 
@@ -255,7 +265,8 @@ lbm_status lbm_batch_init(int32_t n, const lbm_params* p, const uint8_t* const* 
                           const double* const* conc, int32_t nslots, void* stream,
                           void* workspace, size_t ws_bytes, lbm_batch** out);
 
-/* Launch shape (tx 64/128/256, sy >= 8); changes no result bit. */
+/* Launch shape as in lbm_set_tile (tx 64/128/256, sy >= 8); changes no result
+ * bit. */
 lbm_status lbm_batch_set_tile(lbm_batch* b, int32_t tx, int32_t sy);
 lbm_status lbm_batch_get_tile(const lbm_batch* b, int32_t* tx, int32_t* sy);
 
@@ -331,15 +342,16 @@ lbm_status surr_train_epoch(surr_net* s, const int32_t* perm, int32_t batch, flo
 /* Loss and packed parameter gradients for one batch (n <= max_batch), no update. */
 lbm_status surr_gradients(surr_net* s, const float* x, const float* y, int32_t n, float* grad,
                           double* loss);
-/* y [n x 65] for x [n x 5] (host arrays). */
+/* y [n x 65] for x [n x 5] (host arrays; y may lie over x). */
 lbm_status surr_predict(surr_net* s, const float* x, int32_t n, float* y);
 /* For callers that cannot allocate device memory or synchronise (code under
  * HIP graph capture, serving loops, harnesses that forbid hipMalloc): the
  * same prediction as surr_predict, with x [n x 5] and y [n x 65] FP32 arrays
  * in device memory, queued on `stream` (whose device must be current) without
- * waiting for it, as one kernel.  n is 1..1024 per call (more is LBM_EINVAL);
- * no memory is allocated and calls share no scratch memory, so they may
- * overlap.  The handle is only read; it must not be trained concurrently. */
+ * waiting for it, as one kernel (one for each 32 rows where y lies over x).  n is
+ * 1..1024 per call (more is LBM_EINVAL); no memory is allocated and calls share
+ * no scratch memory, so they may overlap in time.  The handle is only read; it
+ * must not be trained concurrently. */
 lbm_status surr_predict_noalloc(const surr_net* s, const float* x, int32_t n, float* y,
                                 void* stream);
 void surr_destroy(surr_net* s);

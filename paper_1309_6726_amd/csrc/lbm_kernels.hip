@@ -580,9 +580,10 @@ __device__ __forceinline__ void collide_moments(const StepArgs& a, const MomentO
 // the caches, so the single-lattice step takes it as an autotuned choice.
 //
 // BATCH: rows that are nothing but wall (a sixth of a capillary sweep's) are
-// skipped.  A single lattice that this kernel gets is too large to have any,
-// and the branch alone costs it 2% (2048^2, 12 rows: 104.0 us with it, 102.0
-// without).
+// skipped.  A single lattice streams them: there the branch costs more than it
+// saves, on a preform that has no such rows (2048^2 with the hint, 12 rows: 100.1
+// us with it, 97.8 without) and on a capillary a third of which is wall (16384x256
+// with the hint, 9 rows: 96.4, 94.6; without the hint 96.0, 95.8).
 template <bool SOLUTE, bool REACT, bool VAR, typename R, bool NT, bool BATCH>
 __device__ __forceinline__ void mom_wave(const StepArgs& a, int strip, int seg) {
   // prefetch slots per buffer: 0..5 moments, 6..10 solute, 11..12 precipitate
