@@ -195,7 +195,7 @@ lbm_status lbm_load(lbm_sim* sim, const void* blob, size_t n);
  * scheme) by sy rows (1..4096), run with one wavefront per row, or with one
  * wavefront per tile where the moment step finds that faster.  With one per row
  * a workgroup takes at most 14 rows (in the moment scheme 12, on larger lattices
- * 8 or 9), and several share a taller tile.  tx (64, 128 or 256) is accepted and
+ * 8), and several share a taller tile.  tx (64, 128 or 256) is accepted and
  * reported but decides nothing.  Until a shape is set, one is chosen from the
  * lattice.  The shape changes no result bit. */
 lbm_status lbm_set_tile(lbm_sim* sim, int32_t tx, int32_t sy);

@@ -838,10 +838,6 @@ struct lbm_batch {
 
 namespace {
 
-// A batch's tiles have at least eight rows, and shared ones at least five (nine
-// rows as five and four).
-constexpr int LOWEST_BATCH_ROWS = 5;
-
 struct BatchLayout {
   size_t insts, tiles, capi, stepc, table, partial, out, common, total;
   std::vector<Layout> L;
@@ -882,7 +878,7 @@ lbm_status batch_layout(int n, const lbm_params* p, int nslots, BatchLayout* B) 
       return fail(LBM_EINVAL, "instance %d: tau, G and accel must be shared by the batch", i);
     if ((p[i].tau_g > 0.0) != solute || (p[i].k_r > 0.0) != react)
       return fail(LBM_EINVAL, "instance %d: solute/reaction switches must be shared", i);
-    B->max_tiles += moment_tiles(p[i], LOWEST_BATCH_ROWS);
+    B->max_tiles += moment_tiles(p[i], 8);  // launch_rows never goes below
     B->max_blocks = std::max(B->max_blocks, (int)std::min<long long>(1024, ((long long)p[i].nx * p[i].ny + 255) / 256));
   }
   size_t off = 0;

@@ -96,19 +96,18 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 //
 // That is the best height's line; a set height has its own.  Eight rows and up to
 // four fill a CU with two and three workgroups (24 wavefronts), five and six leave
-// places empty (20 and 18) and repeat half as much again.  us per step, short
+// places empty (18 and 20) and repeat half as much again.  us per step, short
 // against marching, without solute in brackets: five rows 1150^2 39.9, 40.9,
 // 1600^2 71.2, 67.5 (52.3, 52.1), 2100^2 (86.5, 82.5); six rows 1250^2 44.5, 45.6
-// (33.3, 35.6), 1448^2 59.2, 53.9 (43.8, 41.4), 2100^2 (84.7, 76.4).  Workgroups of
-// five to eight share a tile of ten rows and more (launch_rows): ten rows 1024^2
-// 33.0, 33.4, 1150^2 39.9, 42.5, 1250^2 45.0, 43.2 (33.3, 33.7), 1448^2 (46, 41.7);
-// twelve rows 1024^2 32.5, 38.3, 1150^2 39.5, 38.3, 1600^2 (52, 47.7).
+// (33.3, 35.6), 1448^2 59.2, 53.9 (43.8, 41.4), 2100^2 (84.7, 76.4).  More than
+// eight are launched as eight (launch_rows): ten rows 1024^2 26.1, 33.4, twelve rows
+// 1150^2 31.6, 38.3, but 34 capillaries (2.0 million nodes) 50.0, 48.3, 2100^2 (71.0,
+// 67.9).
 //
 // Marching needs a wavefront for every SIMD: with fewer tiles than that the step
 // is one wavefront's chain of rows, and tiles are short on a lattice of any size.
-// us per step, marching against shared: 256x32 at 16 rows 32 against 5.7, 1024^2 at
-// 24 rows 50.5 against 26, 1448^2 at 64 rows 122 against 45, 2500^2 at 128 rows 260
-// against 177.
+// us per step, marching against eight short rows: 256x32 at 16 rows 32, 5.4, 1024^2
+// at 24 rows 50.5, 25.9, 1448^2 at 64 rows 122, 45.9, 2500^2 at 128 rows 260, 177.
 //
 // nt: the non-temporal load hint is set.  Short tiles, whose neighbours read their
 // halo rows at the same time, are slower with it and run without; where there are
@@ -119,7 +118,8 @@ enum StepKind { KIND_POP = 0, KIND_PM = 1, KIND_MM = 2, KIND_MM_SHORT = 3 };
 // 34.1, at eight 37.1, 25.6, 1600^2 at eight (5400) 67.6, 55.0 (72.2 with the hint).
 constexpr int SHORT_TILE = 12, SHORT_ROWS = 8, SIMDS = 1024;
 inline int moment_kind(long long nodes, bool solute, int sy, long long tiles, int nt) {
-  constexpr long long SHORT_BYTES = 240ll << 20, SHARED_NODES = 1400000, LOOSE_NODES = 2000000, HINTED_TILES = 9000;
+  constexpr long long SHORT_BYTES = 240ll << 20, SHARED_NODES = 1400000, LOOSE_NODES = 2000000,
+                      HINTED_TILES = 9000;
   if (tiles < SIMDS) return KIND_MM_SHORT;
   if (nodes * (solute ? 88 : 48) > SHORT_BYTES || (nt && tiles > HINTED_TILES)) return KIND_MM;
   if (sy > SHORT_ROWS) return nodes <= SHARED_NODES ? KIND_MM_SHORT : KIND_MM;
@@ -127,25 +127,23 @@ inline int moment_kind(long long nodes, bool solute, int sy, long long tiles, in
 }
 
 // Rows of the tiles that a step of this kind is launched with where `tiles` tiles of
-// sy rows are set.  The workgroups that share a tall tile get rows as even as may
-// be (which is launched as lower tiles).
+// sy rows are set: several workgroups share a tall tile, which is launched as lower
+// ones.
 //
-// Population tiles, at most POP_ROWS rows a workgroup: 16 rows as 8 and 8 against
-// 14 and 2, us per step: 1024^2 38.6, 54.1; 2048x1100 with the hint 113, 130; 2500^2
-// 397, 425.
+// Population tiles, at most POP_ROWS rows a workgroup, in parts as even as may be:
+// 16 rows as 8 and 8 against 14 and 2, us per step: 1024^2 38.6, 54.1; 2048x1100 with
+// the hint 113, 130; 2500^2 397, 425.
 //
-// Short moment tiles: ten rows and more leave a CU one workgroup with no more rows
-// than two of five to eight have, which pays while there are hardly two for each
-// CU.  Whole against shared, us per step, without solute in brackets: 2048x76 at
-// 12 rows (245 tiles) 6.9, 7.1, 512^2 at 10 rows (468 tiles) 11.2, 11.8, 800^2 at 10
-// rows (1120 tiles) 25.0, 21.9, 1024^2 at 10 rows 38.0, 33.0 and at 9 rows 33.3, 33.0
-// (23.9, 24.7).
+// Short moment tiles: nine rows and more leave a CU one workgroup with fewer rows than
+// two of SHORT_ROWS have, which pays while there are hardly two for each CU.  Whole
+// against eight rows, us per step, without solute in brackets: 2048x76 at 12 rows
+// (245 tiles) 6.9, 7.6, 800^2 at 10 rows (1120 tiles) 25.0, 18.2, 1024^2 at 9 rows
+// 33.3, 25.6 (23.9, 20.5), at 10 rows 38.0, 26.1 (30.3, 20.7).
 constexpr int POP_ROWS = 14;
 inline int launch_rows(int kind, int sy, long long tiles) {
-  int most = POP_ROWS;
-  if (kind == KIND_MM || (kind == KIND_MM_SHORT && sy <= (tiles <= 512 ? SHORT_TILE : 9))) most = sy;
-  else if (kind == KIND_MM_SHORT) most = SHORT_ROWS;
-  const int parts = (sy + most - 1) / most;
+  if (kind == KIND_MM) return sy;
+  if (kind == KIND_MM_SHORT) return sy <= (tiles <= 512 ? SHORT_TILE : SHORT_ROWS) ? sy : SHORT_ROWS;
+  const int parts = (sy + POP_ROWS - 1) / POP_ROWS;
   return (sy + parts - 1) / parts;
 }
 
